@@ -115,11 +115,17 @@ ERI_DEV int eri_quantize(double x, double eps, double inv, double qmax)
 }
 
 // eq. 10 when 1/eps is finite: round half away from zero, clamp to
-// +-qmax (eps = 0 comes with inv = 0, hence code 0, as eri_quantize gives)
+// +-qmax (eps = 0 comes with inv = 0, hence code 0, as eri_quantize gives).
+// Adding the largest double below 1/2 in the value's direction and truncating
+// rounds halves away from zero for every |y| < 2^52, and the conversion to int
+// truncates (NaN to 0): five instructions instead of round()'s
+// trunc / subtract / compare / select / add and two FP64 clamps.
 ERI_DEV int eri_quantize_mul(double x, double inv, double qmax)
 {
-    const double y = round(x * inv);
-    return (int)fmin(fmax(y, -qmax), qmax);
+    const double y = x * inv;
+    const int q = (int)(y + __builtin_copysign(0.49999999999999994, y));
+    const int m = (int)qmax;
+    return min(max(q, -m), m);
 }
 
 // ---------------------------------------------------------------------------
