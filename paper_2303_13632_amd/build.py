@@ -57,6 +57,7 @@ def _compile(src, obj, deps):
 def build(jobs=None, verbose=True, precisions=("fp64", "mixed", "rys", "rys32"), classes=None):
     sys.path.insert(0, CSRC)
     import codegen  # noqa: E402
+    import codegen_coulomb  # noqa: E402
     import gen_boys_table  # noqa: E402
     import gen_rys_table  # noqa: E402
     sys.path.pop(0)
@@ -77,12 +78,15 @@ def build(jobs=None, verbose=True, precisions=("fp64", "mixed", "rys", "rys32"),
         if verbose:
             print("  Rys rule tables: max relative error %.2e" % err, flush=True)
     files, _ = codegen.generate(GEN, precisions=precisions, classes=classes)
+    ck = os.path.join(GEN, "eri_coulomb_k.hip")
+    codegen.write_if_changed(ck, codegen_coulomb.generate())
     # generated kernel TUs see the device headers only; the host TUs also the
     # plan internals and the C ABI header
     kdeps = [os.path.join(CSRC, f) for f in ("eri_device.h", "eri_plan_types.h", "eri_dispatch.h")] + [bt]
     hdeps = kdeps + [os.path.join(CSRC, "eri_internal.h"), os.path.join(ROOT, "include", "eri.h")]
-    host = [os.path.join(CSRC, "eri_lib.hip"), os.path.join(CSRC, "eri_backward.hip")]
-    srcs = files + host
+    host = [os.path.join(CSRC, f) for f in ("eri_lib.hip", "eri_backward.hip", "eri_coulomb.hip")]
+    cdep = [os.path.join(CSRC, "eri_coulomb.h")]
+    srcs = files + [ck] + host
     jobs = jobs or min(16, os.cpu_count() or 4)
     objs = []
     t0 = time.time()
@@ -92,6 +96,7 @@ def build(jobs=None, verbose=True, precisions=("fp64", "mixed", "rys", "rys32"),
         for s in srcs:
             obj = os.path.join(OBJ, os.path.basename(s) + ".o")
             deps = hdeps if s in host else (rdeps if os.path.basename(s).startswith("eri_rys") else kdeps)
+            deps = deps + cdep if "eri_coulomb" in s else deps
             futs[ex.submit(_compile, s, obj, deps)] = s
         for fu in cf.as_completed(futs):
             obj, dt, did = fu.result()

@@ -887,6 +887,12 @@ extern "C" int eri_backward(eri_plan* p, void* stream, const double* dl_deri, co
     ERI_HIP_TRY(hipGetDevice(&cur));
     if (cur != p->device) ERI_HIP_TRY(hipSetDevice(p->device));
     int rc = ERI_OK;
+    if (p->batched && density) {
+        // every quartet of the screened set with Gbar = D D: Hermite potentials
+        rc = eri_coul_backward(p, (hipStream_t)stream, density, nbf, grad_centers, grad_exps, energy);
+        if (cur != p->device) (void)hipSetDevice(cur);
+        return rc;
+    }
     if (p->bwd && grad_centers && !p->bwd->full) {
         eri_bwd_free(p->bwd);
         p->bwd = nullptr;

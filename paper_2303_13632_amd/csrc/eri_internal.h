@@ -110,6 +110,8 @@ struct eri_batch_class {
 
 struct eri_bwd_state;               // adjoint tables, built at the first eri_backward call
 void eri_bwd_free(eri_bwd_state* b);
+struct eri_coul_state;              // the density form's tables (screened plans), built at its first call
+void eri_coul_free(eri_coul_state* s);
 
 struct eri_plan {
     int device = 0;
@@ -158,7 +160,12 @@ struct eri_plan {
     std::vector<double> sh_xyz, sh_exps, sh_coefs;
     std::vector<int64_t> sh_off;
     eri_bwd_state* bwd = nullptr;
+    eri_coul_state* coul = nullptr;
 };
+
+// The density form of eri_backward for screened plans (eri_coulomb.hip).
+int eri_coul_backward(eri_plan* p, hipStream_t strm, const double* density, int64_t nbf, double* grad_c, double* grad_e,
+                      double* energy);
 
 // Segment expansion of a batched class chunk (defined with the plan code).
 __global__ __launch_bounds__(256) void eri_expand_kernel(const int64_t* __restrict__ seg_off, const int32_t* __restrict__ seg_p1,
