@@ -123,13 +123,13 @@ def main():
                          "int12 (12-bit codes packed into 512-bit words, pack kernel included), "
                          "fp64_out / int8 / int32 (same workload with FP64 output or 8-/32-bit codes), "
                          "gradient (fwd+grad on the 64-atom basis), molecule (every screened quartet of the "
-                         "384-atom molecule-like basis in one graph launch), rys (the Rys-quadrature kernels, "
+                         "384-atom molecule-like basis in one call), rys (the Rys-quadrature kernels, "
                          "FP64 and with FP32 stages, against the Obara-Saika ones on every class, K~U{1,2,3} "
                          "and K = 1); 'none' for the headline only")
     ap.add_argument("--per-class-out", default="", help="write per-class times/GERIS to this JSON file")
     ap.add_argument("--workload", default="classes", choices=["classes", "molecule", "gradient", "copy", "lattice"],
                     help="classes: 256 classes x quartets-per-class; molecule: every Schwarz-screened "
-                         "unique quartet of the 384-atom molecule-like basis in one graph launch; "
+                         "unique quartet of the 384-atom molecule-like basis in one call; "
                          "gradient: E = sum D D (ab|cd) and its gradient on the 64-atom basis")
     ap.add_argument("--molecule-scale", type=float, default=1.0, help="fraction of the molecule's atoms")
     ap.add_argument("--schwarz", type=float, default=1e-10)
@@ -566,7 +566,7 @@ def bench_copy(args):
 
 def bench_molecule(args):
     """Every unique quartet of the molecule-like basis with Q_ab Q_cd >= tau,
-    computed with int16 compression in one hipGraph launch per step."""
+    computed with int16 compression in one call per step."""
     import torch
     from paper_2303_13632_amd import eri, workloads as W
     n_heavy = max(1, int(round(128 * args.molecule_scale)))
@@ -607,7 +607,7 @@ def bench_molecule(args):
         "dtype": "f32+f64" if args.precision in ("mixed", "rys32") else "f64", "data": "synthetic",
         "config": {"workload": "molecule-like basis: %d heavy (s,s,s,p,p,d; K 1-6; exps log-U[0.1,5000]) + %d H "
                                "(s,s,p) atoms on a jittered 3.5 Bohr lattice; all unique quartets with "
-                               "Q_ab Q_cd >= %g in one graph launch; int%d codes, %.0f GB output ring"
+                               "Q_ab Q_cd >= %g in one call; int%d codes, %.0f GB output ring"
                                % (n_heavy, n_h, args.schwarz, args.bits, args.ring_gb),
                    "n_shells": int(len(sh["L"])), "n_quartets": int(plan.n_quartets),
                    "n_eri": int(plan.n_eri), "n_prim_quartets": int(plan.n_prim_quartets)},
@@ -620,7 +620,7 @@ def bench_molecule(args):
 def bench_gradient(args, steps=None, warmup=None):
     """Forward + adjoint on the 64-atom basis (22 heavy + 42 H on a 4x4x4
     lattice, s-d shells): every unique Schwarz-screened quartet computed with
-    int16 codes (one graph launch), then E = sum D D (ab|cd) with the
+    int16 codes (one call), then E = sum D D (ab|cd) with the
     gradient for all centres and exponents (eri_backward, density form)."""
     import torch
     from paper_2303_13632_amd import eri, workloads as W

@@ -192,15 +192,18 @@ int eri_plan_quartets(const eri_plan* plan, int32_t class_id, int64_t first, int
  * two's-complement bits, unused bits zero.  The kernels stage each quartet's
  * codes in LDS and write its words themselves (no container array, no
  * second pass); out_codes holds class_word_off[256] * 64 bytes.
- * Returns ERI_EINVAL if no output is requested.  For ERI_PLAN_ALL_QUARTETS
- * plans all launches are captured once into a hipGraph (per output pointer
- * set) and replayed as a single graph launch. */
+ * Returns ERI_EINVAL if no output is requested.  The work is ordered on
+ * `stream`: it starts after what the stream holds and the stream waits for all
+ * of it.  In between, the launches of a plan with several classes may run side
+ * by side on streams of the library's own (one set per GPU, kept until the
+ * process ends); a call that is being captured, or that finds those streams at
+ * work for another stream, launches on `stream` alone. */
 int eri_compute(eri_plan* plan, void* stream, double* out_eri, void* out_codes, double* out_scales);
 
 /* eri_compute for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * it calls no hipMalloc, hipFree or allocating library routine and builds no
- * graph; every class launch is made on `stream` in turn.  Same outputs,
+ * it calls no hipMalloc, hipFree or allocating library routine; every class
+ * launch is made on `stream` in turn.  Same outputs,
  * bit for bit, as eri_compute.  ERI_PLAN_ALL_QUARTETS plans expand each
  * launch chunk's quartet items into a static device array of
  * ERI_NOALLOC_MAX_ITEMS items (32 MiB, one copy per GPU the library runs on,
@@ -236,8 +239,7 @@ int eri_compute_class(eri_plan* plan, int32_t class_id, void* stream, double* ou
  * allocates and frees; the plan's codes width is kept) and the fastest mean
  * time wins.  With cache_path, choices stored there under the key
  * "<precision>:<class id>:<bits>" are used without timing, and the file is
- * rewritten with every choice made.  Synchronises the stream; invalidates the
- * captured graph of ERI_PLAN_ALL_QUARTETS plans.  All variants of a class
+ * rewritten with every choice made.  Synchronises the stream.  All variants of a class
  * compute the same integrals in the same orientation and layout; their
  * values may differ in the last bits (other operation order).
  * Returns ERI_EINVAL for sample_quartets < 1 or trials < 1, ERI_EHIP /

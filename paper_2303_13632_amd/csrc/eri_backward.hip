@@ -805,15 +805,7 @@ int run_class(eri_plan* p, eri_bwd_state* st, int c, hipStream_t strm, const bwd
         const int64_t q0 = ps.lo, m = ps.hi - ps.lo;
         const eri_item* uitems;
         if (ps.bc) {
-            const eri_batch_class* bc = ps.bc;
-            const int64_t e0 = ps.lo - bc->qoff, e1 = ps.hi - bc->qoff;
-            const auto sbeg = p->h_seg_off.begin();
-            const int64_t s0 = (int64_t)(std::upper_bound(sbeg + bc->seg_lo, sbeg + bc->seg_hi, e0) - sbeg) - 1;
-            const int64_t s1 = (int64_t)(std::lower_bound(sbeg + bc->seg_lo, sbeg + bc->seg_hi, e1) - sbeg);
-            if (s1 - s0 > INT32_MAX) return ERI_EUNSUPPORTED;
-            hipLaunchKernelGGL(eri_expand_kernel, dim3((unsigned)(s1 - s0)), dim3(256), 0, strm, p->d_seg_off,
-                               p->d_seg_p1, s0, bc->ket_lo, e0, e1, 0, st->d_uitems);
-            ERI_HIP_TRY(hipGetLastError());
+            ERI_TRY(eri_expand_items(p, c, ps.lo, ps.hi, 0, st->d_uitems, strm));
             uitems = st->d_uitems;
         } else {
             uitems = st->d_uall + p->class_qoff[c] + q0;

@@ -108,6 +108,12 @@ struct eri_batch_class {
                                     // one launch share a ring slot)
 };
 
+// One row per entry on the device: its segments, and where they lie.
+struct eri_entry_row {
+    int64_t seg_lo;                 // first segment (entries follow each other; each closes with p1 = -1)
+    int64_t qoff, ket_lo;
+};
+
 struct eri_bwd_state;               // adjoint tables, built at the first eri_backward call
 void eri_bwd_free(eri_bwd_state* b);
 struct eri_coul_state;              // the density form's tables (screened plans), built at its first call
@@ -127,6 +133,7 @@ struct eri_plan {
     std::vector<uint64_t> pair_keys;  // explicit plans: (a << 32) | b of each pair record, in table order
     int64_t class_count[256] = {};
     int64_t class_ring[256] = {};
+    int64_t class_maxpq[256] = {};   // most primitive quartets of one quartet
     int64_t class_qoff[257] = {};
     int64_t class_eoff[257] = {};
     double class_flops[256] = {};
@@ -144,6 +151,8 @@ struct eri_plan {
     std::vector<int32_t> h_seg_p1;
     int64_t* d_seg_off = nullptr;
     int32_t* d_seg_p1 = nullptr;
+    eri_entry_row* d_entries = nullptr;
+    int64_t items_cap = 0;              // items that d_items holds
     int64_t chunk_cap = 0;
     int64_t pass_cap = 0;               // opts->chunk_quartets: bound on an adjoint pass (0 = default)
     int32_t scale_block = 1;            // quartets per scale block
@@ -153,8 +162,6 @@ struct eri_plan {
     double* d_stage = nullptr;          // scale_block > 1: FP64 values of one class (when out_eri is NULL)
     double schwarz = 0.0;
     std::vector<double> pair_q;
-    hipGraphExec_t graph = nullptr;
-    const void* graph_key[4] = {nullptr, nullptr, nullptr, nullptr};
     // host copy of the shell set (the adjoint builds derived shells from it)
     std::vector<int32_t> sh_L, sh_K;
     std::vector<double> sh_xyz, sh_exps, sh_coefs;
@@ -167,7 +174,5 @@ struct eri_plan {
 int eri_coul_backward(eri_plan* p, hipStream_t strm, const double* density, int64_t nbf, double* grad_c, double* grad_e,
                       double* energy);
 
-// Segment expansion of a batched class chunk (defined with the plan code).
-__global__ __launch_bounds__(256) void eri_expand_kernel(const int64_t* __restrict__ seg_off, const int32_t* __restrict__ seg_p1,
-                                  int64_t seg_lo, int64_t ket_lo, int64_t q_lo, int64_t q_hi, int swap,
-                                  eri_item* __restrict__ items);
+// Items of class quartets [q_lo, q_hi) of a batched plan (defined with the plan code).
+int eri_expand_items(const eri_plan* p, int c, int64_t q_lo, int64_t q_hi, int swap, eri_item* items, hipStream_t st);

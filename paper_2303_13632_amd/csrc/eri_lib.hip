@@ -147,17 +147,104 @@ int upload(eri_plan* p, void** dst, const void* src, size_t bytes)
 
 using namespace eri_detail;
 
+// ---------------------------------------------------------------------------
+// Class launches side by side.  A launch of a few quartets per class lasts as
+// long as its deepest contraction takes one lane or slot (a [dd|dd] quartet of
+// 81 primitive quartets: 0.13 ms) and leaves most of the 256 CUs idle, and a
+// large one ends with a part of them idle; one after the other these add up
+// over the classes (57 launches for the unique quartets of ten shells: 2.7 ms).
+// So the classes go to ERI_SIDE_STREAMS side streams, longest first, each to
+// the stream with the least work so far.  The side streams wait for the
+// caller's stream (fork) and it waits for them (join), so the call orders its
+// work on the caller's stream as before.
+//   Four is the number of hardware queues that a process's ordinary streams
+// share, and two launches whose streams share one run in turn.  Streams made
+// one after the other get the queues in turn, once every queue has been taken:
+// so three are made and dropped before the four that stay (measured: any two
+// of these four overlap, whether the program had made 0, 1 or 3 streams before;
+// of the first four, the third and fourth share a queue).  Six streams with
+// hardware queues of their own (CU masks) were slower: such streams also wait
+// for the null stream.
+//   There is one set per device, made at the first call that needs it and kept
+// until the process ends (making it takes 8 ms, most of it for the queues).  It
+// is lent to one caller's stream at a time: a call that finds it at work for
+// another stream or thread, and a call that is being captured, launches on its
+// own stream alone, so that no call waits for another stream's work.
+// ---------------------------------------------------------------------------
+constexpr int ERI_SIDE_STREAMS = 4;
+struct side_set {
+    std::mutex mu;
+    bool made = false, used = false;
+    hipStream_t last = nullptr;              // caller's stream of the work in flight
+    hipStream_t st[ERI_SIDE_STREAMS] = {};
+    hipEvent_t fork = nullptr, join[ERI_SIDE_STREAMS] = {};
+};
+static side_set g_side[ERI_NOALLOC_MAX_DEVICES];
+
+static void side_clear(side_set& s)
+{
+    for (int k = 0; k < ERI_SIDE_STREAMS; ++k) {
+        if (s.st[k]) (void)hipStreamDestroy(s.st[k]);
+        if (s.join[k]) (void)hipEventDestroy(s.join[k]);
+        s.st[k] = nullptr;
+        s.join[k] = nullptr;
+    }
+    if (s.fork) (void)hipEventDestroy(s.fork);
+    s.fork = nullptr;
+    s.made = s.used = false;
+}
+
+static hipError_t side_make(side_set& s)
+{
+    hipStream_t drop[ERI_SIDE_STREAMS - 1] = {};
+    hipError_t e = hipEventCreateWithFlags(&s.fork, hipEventDisableTiming);
+    for (hipStream_t& d : drop)
+        if (e == hipSuccess) e = hipStreamCreateWithFlags(&d, hipStreamNonBlocking);
+    for (int k = 0; k < ERI_SIDE_STREAMS && e == hipSuccess; ++k) {
+        e = hipStreamCreateWithFlags(&s.st[k], hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&s.join[k], hipEventDisableTiming);
+    }
+    for (hipStream_t d : drop)
+        if (d) (void)hipStreamDestroy(d);
+    s.made = e == hipSuccess;
+    return e;
+}
+
+// The device's set for a call on `st`, locked; nullptr: the call keeps to its
+// own stream.  (On the plan's device; errors of the attempt are no errors of
+// the call.)
+static side_set* side_take(eri_plan* p, hipStream_t st)
+{
+    if (p->device < 0 || p->device >= ERI_NOALLOC_MAX_DEVICES) return nullptr;
+    side_set& s = g_side[p->device];
+    if (!s.mu.try_lock()) return nullptr;
+    hipError_t e = hipSuccess;
+    bool busy = false;
+    if (!s.made) e = side_make(s);
+    if (e == hipSuccess && s.used && s.last != st)
+        for (int k = 0; k < ERI_SIDE_STREAMS && !busy; ++k) busy = hipEventQuery(s.join[k]) != hipSuccess;
+    if (e != hipSuccess || busy) {
+        (void)hipGetLastError();
+        if (!s.made) side_clear(s);
+        s.mu.unlock();
+        return nullptr;
+    }
+    s.used = true;
+    s.last = st;
+    return &s;
+}
+
 static void plan_free(eri_plan* p)
 {
     if (!p) return;
     int cur = 0;
     if (hipGetDevice(&cur) == hipSuccess && cur != p->device) (void)hipSetDevice(p->device);
-    if (p->graph) (void)hipGraphExecDestroy(p->graph);
     if (p->d_pairs) (void)hipFree(p->d_pairs);
     if (p->d_prims) (void)hipFree(p->d_prims);
     if (p->d_items) (void)hipFree(p->d_items);
     if (p->d_seg_off) (void)hipFree(p->d_seg_off);
     if (p->d_seg_p1) (void)hipFree(p->d_seg_p1);
+    if (p->d_entries) (void)hipFree(p->d_entries);
     if (p->d_stage) (void)hipFree(p->d_stage);
     if (p->bwd) eri_bwd_free(p->bwd);
     if (p->coul) eri_coul_free(p->coul);
@@ -249,6 +336,7 @@ static int create_explicit(eri_plan* p, const shell_set& s, const int32_t* quart
         p->class_count[cls[t]] += 1;
         const int64_t npq = (int64_t)pairs[bra[t]].nprim * pairs[ket[t]].nprim;
         p->n_prim_quartets += npq;
+        p->class_maxpq[cls[t]] = std::max(p->class_maxpq[cls[t]], npq);
         p->class_flops[cls[t]] += (double)npq * tab[class_id5_of(cls[t])].flops_pq + (double)tab[class_id5_of(cls[t])].flops_q;
     }
     p->class_qoff[0] = 0;
@@ -275,24 +363,59 @@ static int create_explicit(eri_plan* p, const shell_set& s, const int32_t* quart
 // Batched plans: all unique Schwarz-screened quartets of a shell set
 // ---------------------------------------------------------------------------
 // Writes the items (computed bra, computed ket) of class quartets [q_lo, q_hi)
-// that fall in segments [seg_lo, seg_lo + gridDim.x); seg_off holds quartet
-// offsets within the class.
+// that fall in segments [seg_lo, seg_hi), which may span several entries:
+// one wavefront per segment, its entry found by a binary search (uniform).
 __global__ __launch_bounds__(256) void eri_expand_kernel(const int64_t* __restrict__ seg_off,
-                                                         const int32_t* __restrict__ seg_p1, int64_t seg_lo,
-                                                         int64_t ket_lo, int64_t q_lo, int64_t q_hi, int swap,
-                                                         eri_item* __restrict__ items)
+                                                         const int32_t* __restrict__ seg_p1,
+                                                         const eri_entry_row* __restrict__ rows, int e_lo, int e_hi,
+                                                         int64_t seg_lo, int64_t seg_hi, int64_t q_lo, int64_t q_hi,
+                                                         int swap, eri_item* __restrict__ items)
 {
-    const int64_t s = seg_lo + blockIdx.x;
-    const int64_t sb = seg_off[s], se = seg_off[s + 1];
-    const int64_t beg = sb > q_lo ? sb : q_lo, end = se < q_hi ? se : q_hi;
+    const int64_t s = seg_lo + (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (s >= seg_hi) return;
     const int32_t p1 = seg_p1[s];
-    for (int64_t t = beg + threadIdx.x; t < end; t += 256) {
-        const int32_t p2 = (int32_t)(ket_lo + (t - sb));
+    if (p1 < 0) return;   // the closing segment of an entry
+    int lo = e_lo, hi = e_hi;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (rows[mid].seg_lo <= s) lo = mid; else hi = mid;
+    }
+    const int64_t sb = rows[lo].qoff + seg_off[s], se = rows[lo].qoff + seg_off[s + 1];
+    const int64_t beg = sb > q_lo ? sb : q_lo, end = se < q_hi ? se : q_hi;
+    const int64_t k0 = rows[lo].ket_lo - sb;
+    for (int64_t t = beg + (threadIdx.x & 63); t < end; t += 64) {
+        const int32_t p2 = (int32_t)(k0 + t);
         eri_item it;
         it.bra = swap ? p2 : p1;
         it.ket = swap ? p1 : p2;
         items[t - q_lo] = it;
     }
+}
+
+int eri_expand_items(const eri_plan* p, int c, int64_t q_lo, int64_t q_hi, int swap, eri_item* items, hipStream_t st)
+{
+    // the class's entries (they follow each other) that overlap the range
+    int e0 = 0, e1;
+    while (e0 < (int)p->bclass.size() && (p->bclass[e0].cid != c || p->bclass[e0].qoff + p->bclass[e0].n_quartets <= q_lo)) ++e0;
+    for (e1 = e0; e1 < (int)p->bclass.size() && p->bclass[e1].cid == c && p->bclass[e1].qoff < q_hi; ++e1) {}
+    if (e1 == e0) return ERI_OK;
+    const auto sbeg = p->h_seg_off.begin();
+    const eri_batch_class &b0 = p->bclass[e0], &b1 = p->bclass[e1 - 1];
+    const int64_t s0 = (int64_t)(std::upper_bound(sbeg + b0.seg_lo, sbeg + b0.seg_hi, q_lo - b0.qoff) - sbeg) - 1;
+    const int64_t s1 = (int64_t)(std::lower_bound(sbeg + b1.seg_lo, sbeg + b1.seg_hi, q_hi - b1.qoff) - sbeg);
+    const int64_t grid = (s1 - s0 + 3) / 4;
+    if (grid > INT32_MAX) return ERI_EUNSUPPORTED;
+    hipLaunchKernelGGL(eri_expand_kernel, dim3((unsigned)grid), dim3(256), 0, st, p->d_seg_off, p->d_seg_p1,
+                       p->d_entries, e0, e1, s0, s1, q_lo, q_hi, swap, items);
+    ERI_HIP_TRY(hipGetLastError());
+    return ERI_OK;
+}
+
+// Most quartets of a class in one launch of a batched plan: no two of a launch
+// share a ring slot.
+static int64_t class_piece(const eri_plan* p, int c)
+{
+    return std::min(p->class_count[c], std::min(p->chunk_cap, p->class_ring[c]));
 }
 
 static int create_batched(eri_plan* p, const shell_set& s, const eri_plan_opts* o)
@@ -399,7 +522,6 @@ static int create_batched(eri_plan* p, const shell_set& s, const eri_plan_opts* 
     //      once, as (P1 | P2) with P2 <= P1 in the sorted order --------------
     const int64_t cap = o->chunk_quartets > 0 ? o->chunk_quartets : ((int64_t)1 << 25);
     p->chunk_cap = cap;
-    int64_t maxchunk = 1;
     for (int cb = 0; cb < 16; ++cb) {
         for (int ck = 0; ck <= cb; ++ck) {
             const int cid = (cb / 4) * 64 + (cb % 4) * 16 + (ck / 4) * 4 + (ck % 4);
@@ -435,6 +557,7 @@ static int create_batched(eri_plan* p, const shell_set& s, const eri_plan_opts* 
                         p->h_seg_p1.push_back((int32_t)b);
                         q += n;
                         const int64_t npq = (int64_t)p->h_pairs[b].nprim * kprim[n];
+                        p->class_maxpq[cid] = std::max(p->class_maxpq[cid], npq / n);
                         p->n_prim_quartets += npq;
                         flops += (double)npq * tab[class_id5_of(cid)].flops_pq + (double)n * tab[class_id5_of(cid)].flops_q;
                     }
@@ -465,7 +588,6 @@ static int create_batched(eri_plan* p, const shell_set& s, const eri_plan_opts* 
     for (auto& bc : p->bclass) {
         bc.ring = p->class_ring[bc.cid];
         bc.chunk = std::min(cap, bc.ring);
-        maxchunk = std::max(maxchunk, bc.chunk);
     }
     p->class_qoff[0] = 0;
     p->class_eoff[0] = 0;
@@ -482,7 +604,13 @@ static int create_batched(eri_plan* p, const shell_set& s, const eri_plan_opts* 
                    p->h_seg_off.size() * sizeof(int64_t)));
     ERI_TRY(upload(p, (void**)&p->d_seg_p1, p->h_seg_p1.empty() ? nullptr : p->h_seg_p1.data(),
                    p->h_seg_p1.size() * sizeof(int32_t)));
-    ERI_TRY(upload(p, (void**)&p->d_items, nullptr, (size_t)maxchunk * sizeof(eri_item)));
+    std::vector<eri_entry_row> rows;
+    for (const auto& bc : p->bclass) rows.push_back({bc.seg_lo, bc.qoff, bc.ket_lo});
+    ERI_TRY(upload(p, (void**)&p->d_entries, rows.empty() ? nullptr : rows.data(), rows.size() * sizeof(eri_entry_row)));
+    // items of one round of launches: every class's whole work where it fits
+    for (int c = 0; c < 256; ++c) p->items_cap += class_piece(p, c);
+    p->items_cap = std::max<int64_t>(1, std::min(p->items_cap, cap));
+    ERI_TRY(upload(p, (void**)&p->d_items, nullptr, (size_t)p->items_cap * sizeof(eri_item)));
     return ERI_OK;
 }
 
@@ -762,8 +890,10 @@ __global__ __launch_bounds__(256) void eri_compress_blocks_kernel(const double* 
     for (int64_t i = lo + threadIdx.x; i < hi; i += 256) codes[i] = (CT)eri_quantize(x[i], eps, inv, qmax);
 }
 
+// item_buf: where a batched plan's items go (`room` of them), by default the
+// plan's own buffer.
 static int launch_class(eri_plan* p, int c, hipStream_t st, double* out_eri, void* out_codes, double* out_scales,
-                        eri_item* item_buf = nullptr)
+                        eri_item* item_buf = nullptr, int64_t room = 0)
 {
     const int64_t n = p->class_count[c];
     if (n == 0) return ERI_OK;
@@ -797,25 +927,16 @@ static int launch_class(eri_plan* p, int c, hipStream_t st, double* out_eri, voi
         ERI_HIP_TRY(hipGetLastError());
         return ERI_OK;
     }
-    const auto sbeg = p->h_seg_off.begin();
-    for (const auto& b : p->bclass) {
-      if (b.cid != c) continue;
-      const eri_batch_class* bc = &b;
-      for (int64_t q0 = 0; q0 < bc->n_quartets; q0 += bc->chunk) {
-        const int64_t q1 = std::min(bc->n_quartets, q0 + bc->chunk);
-        // segments overlapping [q0, q1)
-        const int64_t s0 = (int64_t)(std::upper_bound(sbeg + bc->seg_lo, sbeg + bc->seg_hi, q0) - sbeg) - 1;
-        const int64_t s1 = (int64_t)(std::lower_bound(sbeg + bc->seg_lo, sbeg + bc->seg_hi, q1) - sbeg);
-        if (s1 - s0 > INT32_MAX) return ERI_EUNSUPPORTED;
-        eri_item* items = item_buf ? item_buf : p->d_items;
-        hipLaunchKernelGGL(eri_expand_kernel, dim3((unsigned)(s1 - s0)), dim3(256), 0, st, p->d_seg_off, p->d_seg_p1,
-                           s0, bc->ket_lo, q0, q1, kernel_swap(ki) ? 1 : 0, items);
-        ERI_HIP_TRY(hipGetLastError());
+    // pieces of the class's quartets, across its entries
+    const int64_t piece = std::min(class_piece(p, c), item_buf ? room : p->items_cap);
+    eri_item* items = item_buf ? item_buf : p->d_items;
+    for (int64_t q0 = 0; q0 < n; q0 += piece) {
+        const int64_t q1 = std::min(n, q0 + piece);
+        ERI_TRY(eri_expand_items(p, c, q0, q1, kernel_swap(ki) ? 1 : 0, items, st));
         a.items = items;
         a.n_items = q1 - q0;
-        a.qbase = bc->qoff + q0;
+        a.qbase = q0;
         ERI_TRY(launch_items(ki, a, st));
-      }
     }
     return ERI_OK;
 }
@@ -828,45 +949,95 @@ static int compute_check(eri_plan* p, double* out_eri, void* out_codes, double* 
     return ERI_OK;
 }
 
-static int launch_all(eri_plan* p, hipStream_t st, double* out_eri, void* out_codes, double* out_scales)
+// Seconds of a class launch: its deepest contraction through one lane or slot
+// plus its whole work at the chip's rate (measured: 5e-9 s per FLOP of a lane's
+// own work, 8e-11 s through a slot of lanes, 1e13 FLOP/s in all).  Only the
+// order and the balance of the streams depend on it.
+static double launch_seconds(const eri_plan* p, int c)
 {
-    for (int c = 0; c < 256; ++c) ERI_TRY(launch_class(p, c, st, out_eri, out_codes, out_scales));
+    const eri_kernel_info& ki = class_kernel(p, c);
+    return (double)p->class_maxpq[c] * ki.flops_pq * (ki.mode == 0 ? 5e-9 : 8e-11) + p->class_flops[c] * 1e-13 + 5e-6;
+}
+
+// What the side streams must gain over one stream to be worth the events
+// between them (about 20 us of waiting at either end).
+constexpr double ERI_FORK_SECONDS = 40e-6;
+
+// Every class of the plan, on `st` alone (side = nullptr) or on `st` and the
+// side streams; batched plans in rounds of as many items as their buffer holds.
+static int launch_all(eri_plan* p, hipStream_t st, side_set* side, double* out_eri, void* out_codes,
+                      double* out_scales)
+{
+    std::pair<double, int> order[256];
+    int n = 0;
+    double total = 0.0;
+    for (int c = 0; c < 256; ++c)
+        if (p->class_count[c]) {
+            order[n] = {launch_seconds(p, c), c};
+            total += order[n++].first;
+        }
+    if (n == 0) return ERI_OK;
+    std::sort(order, order + n, [](const auto& x, const auto& y) {
+        return x.first != y.first ? x.first > y.first : x.second < y.second;
+    });
+    // scale blocks over several quartets share the plan's staging buffer
+    const bool staged = p->scale_block > 1 && out_codes && !out_eri;
+    const double best = std::max(order[0].first, total / ERI_SIDE_STREAMS);
+    if (!side || staged || total - best < ERI_FORK_SECONDS) {
+        for (int i = 0; i < n; ++i) ERI_TRY(launch_class(p, order[i].second, st, out_eri, out_codes, out_scales));
+        return ERI_OK;
+    }
+    int next = 0;
+    while (next < n) {
+        ERI_HIP_TRY(hipEventRecord(side->fork, st));
+        for (int k = 0; k < ERI_SIDE_STREAMS; ++k) ERI_HIP_TRY(hipStreamWaitEvent(side->st[k], side->fork, 0));
+        double load[ERI_SIDE_STREAMS] = {};
+        int64_t used = 0;
+        int rc = ERI_OK;
+        for (; next < n && rc == ERI_OK; ++next) {
+            const int c = order[next].second;
+            eri_item* items = nullptr;
+            int64_t room = 0;
+            if (p->batched) {
+                // a class goes in one piece where there is room, else in several through what is left,
+                // in a round of its own
+                const int64_t want = class_piece(p, c);
+                if (used > 0 && used + want > p->items_cap) break;
+                items = p->d_items + used;
+                room = std::min(want, p->items_cap - used);
+                used += room;
+            }
+            const int k = (int)(std::min_element(load, load + ERI_SIDE_STREAMS) - load);
+            load[k] += order[next].first;
+            rc = launch_class(p, c, side->st[k], out_eri, out_codes, out_scales, items, room);
+        }
+        // the caller's stream waits for every side stream also after a failure
+        for (int k = 0; k < ERI_SIDE_STREAMS; ++k) {
+            ERI_HIP_TRY(hipEventRecord(side->join[k], side->st[k]));
+            ERI_HIP_TRY(hipStreamWaitEvent(st, side->join[k], 0));
+        }
+        if (rc != ERI_OK) return rc;
+    }
     return ERI_OK;
 }
 
-// Batched plans: every launch (item expansion + class kernels, all chunks) is
-// captured once into a graph, then replayed as one launch per call.
-static int graph_launch(eri_plan* p, hipStream_t st, double* out_eri, void* out_codes, double* out_scales)
+// A call that is being captured keeps to the caller's stream.
+static bool is_capturing(hipStream_t st)
 {
-    const void* key[4] = {out_eri, out_codes, out_scales, nullptr};
-    if (!p->graph || std::memcmp(key, p->graph_key, sizeof(key)) != 0) {
-        if (p->graph) {
-            (void)hipGraphExecDestroy(p->graph);
-            p->graph = nullptr;
-        }
-        hipStream_t cap = nullptr;
-        ERI_HIP_TRY(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
-        hipGraph_t g = nullptr;
-        int rc = ERI_OK;
-        hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
-        if (e == hipSuccess) {
-            rc = launch_all(p, cap, out_eri, out_codes, out_scales);
-            hipError_t e2 = hipStreamEndCapture(cap, &g);
-            if (rc == ERI_OK) e = e2;
-        }
-        if (e == hipSuccess && rc == ERI_OK) e = hipGraphInstantiate(&p->graph, g, nullptr, nullptr, 0);
-        if (g) (void)hipGraphDestroy(g);
-        (void)hipStreamDestroy(cap);
-        if (rc != ERI_OK) return rc;
-        if (e != hipSuccess) {
-            p->graph = nullptr;
-            g_last_hip = (int)e;
-            return ERI_EHIP;
-        }
-        std::memcpy(p->graph_key, key, sizeof(key));
-    }
-    ERI_HIP_TRY(hipGraphLaunch(p->graph, st));
-    return ERI_OK;
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+static int compute_on(eri_plan* p, hipStream_t st, double* out_eri, void* out_codes, double* out_scales)
+{
+    int classes = 0;
+    for (int c = 0; c < 256; ++c) classes += p->class_count[c] > 0;
+    side_set* side = classes > 1 && !is_capturing(st) ? side_take(p, st) : nullptr;
+    const int rc = launch_all(p, st, side, out_eri, out_codes, out_scales);
+    if (side) side->mu.unlock();
+    return rc;
 }
 
 extern "C" int eri_compute(eri_plan* p, void* stream, double* out_eri, void* out_codes, double* out_scales)
@@ -877,7 +1048,7 @@ extern "C" int eri_compute(eri_plan* p, void* stream, double* out_eri, void* out
     ERI_HIP_TRY(hipGetDevice(&cur));
     if (cur != p->device) ERI_HIP_TRY(hipSetDevice(p->device));
     hipStream_t st = (hipStream_t)stream;
-    rc = p->batched ? graph_launch(p, st, out_eri, out_codes, out_scales) : launch_all(p, st, out_eri, out_codes, out_scales);
+    rc = compute_on(p, st, out_eri, out_codes, out_scales);
     if (cur != p->device) (void)hipSetDevice(cur);
     return rc;
 }
@@ -885,7 +1056,7 @@ extern "C" int eri_compute(eri_plan* p, void* stream, double* out_eri, void* out
 // ---------------------------------------------------------------------------
 // Entry point that allocates nothing: the expanded quartet items of a
 // screened plan's launch chunk go to a file-scope device array instead of
-// the plan's item buffer, and the launches are made one by one (no graph).
+// the plan's item buffer, and the launches are made one by one on the caller's stream.
 // ---------------------------------------------------------------------------
 static __device__ __align__(256) eri_item scratch[ERI_NOALLOC_MAX_ITEMS];
 
@@ -920,7 +1091,7 @@ extern "C" int eri_compute_noalloc(eri_plan* p, void* stream, double* out_eri, v
     eri_item* items = nullptr;
     if (p->batched) rc = scratch_items(p->device, &items);
     for (int c = 0; c < 256 && rc == ERI_OK; ++c)
-        rc = launch_class(p, c, (hipStream_t)stream, out_eri, out_codes, out_scales, items);
+        rc = launch_class(p, c, (hipStream_t)stream, out_eri, out_codes, out_scales, items, ERI_NOALLOC_MAX_ITEMS);
     if (cur != p->device) (void)hipSetDevice(cur);
     return rc;
 }
@@ -1001,7 +1172,7 @@ static int tune_plan(eri_plan* p, hipStream_t st, int64_t sample, int trials, co
         if (!sentry[b.cid] || b.n_quartets > sentry[b.cid]->n_quartets) sentry[b.cid] = &b;
     for (int c = 0; c < 256; ++c) {
         int64_t n = std::min(p->class_count[c], sample);
-        if (p->batched) n = sentry[c] ? std::min({n, sentry[c]->n_quartets, sentry[c]->chunk}) : 0;
+        if (p->batched) n = sentry[c] ? std::min({n, sentry[c]->n_quartets, sentry[c]->chunk, p->items_cap}) : 0;
         nsample[c] = n;
         max_vals = std::max(max_vals, n * (int64_t)kernel_table(p->precision)[class_id5_of(c)].n_eriq);
         max_q = std::max(max_q, n);
@@ -1071,13 +1242,8 @@ static int tune_plan(eri_plan* p, hipStream_t st, int64_t sample, int trials, co
                 rc = orient_items(p, c, ki, st);
                 a.items = p->d_items + p->class_qoff[c];
             } else {
-                const eri_batch_class* bc = sentry[c];
-                const auto sbeg = p->h_seg_off.begin();
-                const int64_t s1 = (int64_t)(std::lower_bound(sbeg + bc->seg_lo, sbeg + bc->seg_hi, n) - sbeg);
-                hipLaunchKernelGGL(eri_expand_kernel, dim3((unsigned)(s1 - bc->seg_lo)), dim3(256), 0, st,
-                                   p->d_seg_off, p->d_seg_p1, bc->seg_lo, bc->ket_lo, (int64_t)0, n,
-                                   kernel_swap(ki) ? 1 : 0, p->d_items);
-                hip(hipGetLastError());
+                const int64_t q0 = sentry[c]->qoff;
+                rc = eri_expand_items(p, c, q0, q0 + n, kernel_swap(ki) ? 1 : 0, p->d_items, st);
                 a.items = p->d_items;
             }
             if (rc != ERI_OK) break;
@@ -1102,10 +1268,6 @@ static int tune_plan(eri_plan* p, hipStream_t st, int64_t sample, int trials, co
     if (o_eri) (void)hipFree(o_eri);
     if (o_codes) (void)hipFree(o_codes);
     if (o_scales) (void)hipFree(o_scales);
-    if (p->graph) {
-        (void)hipGraphExecDestroy(p->graph);
-        p->graph = nullptr;
-    }
     if (rc == ERI_OK && cache_path && !write_tune_cache(cache_path, cache)) rc = ERI_EINVAL;
     return rc;
 }
@@ -1137,10 +1299,6 @@ extern "C" int eri_plan_set_variants(eri_plan* p, const int32_t* v)
         if (!var[class_id5_of(c) * ERI_MAXVAR + v[c]].fn && (v[c] != 0 || p->class_count[c])) return ERI_EINVAL;
     }
     for (int c = 0; c < 256; ++c) p->class_var[c] = v[c];
-    if (p->graph) {
-        (void)hipGraphExecDestroy(p->graph);
-        p->graph = nullptr;
-    }
     return ERI_OK;
 }
 
