@@ -283,8 +283,10 @@ int eri_decompress(int32_t bits, const void* codes, const double* scales, int64_
  * FP64 whatever the plan's precision.  For ERI_PLAN_ALL_QUARTETS plans with a
  * density they are contracted, primitive pair by primitive pair, with the
  * pair's potential in Hermite Gaussians, which is summed over all quartets of
- * the plan that hold the pair.  Otherwise they are contracted ERIs of derived
- * shells computed by the FP64 class kernels, which multiply each derived ERI
+ * the plan that hold the pair; for an explicit plan's classes of at most 2048
+ * quartets with the potential of the quartet's other pair under Gbar, all of
+ * them in one launch.  Otherwise they are contracted ERIs of derived shells
+ * computed by the FP64 class kernels, which multiply each derived ERI
  * into Gbar as it is produced (no derived integral is stored), the fourth
  * centre's derivative following from translation invariance.  Gradient
  * accumulation uses FP64 atomics (into slices that a last kernel adds up in

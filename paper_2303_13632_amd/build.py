@@ -84,7 +84,7 @@ def build(jobs=None, verbose=True, precisions=("fp64", "mixed", "rys", "rys32"),
     # plan internals and the C ABI header
     kdeps = [os.path.join(CSRC, f) for f in ("eri_device.h", "eri_plan_types.h", "eri_dispatch.h")] + [bt]
     hdeps = kdeps + [os.path.join(CSRC, "eri_internal.h"), os.path.join(ROOT, "include", "eri.h")]
-    host = [os.path.join(CSRC, f) for f in ("eri_lib.hip", "eri_backward.hip", "eri_coulomb.hip")]
+    host = [os.path.join(CSRC, f) for f in ("eri_lib.hip", "eri_backward.hip", "eri_coulomb.hip", "eri_adjoint.hip")]
     cdep = [os.path.join(CSRC, "eri_coulomb.h")]
     srcs = files + [ck] + host
     jobs = jobs or min(16, os.cpu_count() or 4)
@@ -96,7 +96,7 @@ def build(jobs=None, verbose=True, precisions=("fp64", "mixed", "rys", "rys32"),
         for s in srcs:
             obj = os.path.join(OBJ, os.path.basename(s) + ".o")
             deps = hdeps if s in host else (rdeps if os.path.basename(s).startswith("eri_rys") else kdeps)
-            deps = deps + cdep if "eri_coulomb" in s else deps
+            deps = deps + cdep if "eri_coulomb" in s or "eri_adjoint" in s else deps
             futs[ex.submit(_compile, s, obj, deps)] = s
         for fu in cf.as_completed(futs):
             obj, dt, did = fu.result()

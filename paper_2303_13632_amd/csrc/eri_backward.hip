@@ -17,6 +17,9 @@
 // above).  Centres A, B, C are differentiated this way; the derivative with
 // respect to D follows from translation invariance, dA + dB + dC + dD = 0.
 //
+// (The density form of screened plans and classes of few quartets go other
+// ways: eri_coulomb.hip, eri_adjoint.hip.)
+//
 // Pipeline per class and chunk of quartets: user items (P1, P2) -> for each
 // derivative kind a derived item list (derive kernel; for the exponent kinds
 // one item per primitive of the differentiated shell, compacted by a scan) ->
@@ -879,9 +882,21 @@ extern "C" int eri_backward(eri_plan* p, void* stream, const double* dl_deri, co
     ERI_HIP_TRY(hipGetDevice(&cur));
     if (cur != p->device) ERI_HIP_TRY(hipSetDevice(p->device));
     int rc = ERI_OK;
+    hipStream_t strm = (hipStream_t)stream;
+    bool listed = false, other = false;
+    for (int c = 0; c < 256; ++c) {
+        listed = listed || adj_listed(p, c);
+        other = other || (p->class_count[c] && !adj_listed(p, c));
+    }
     if (p->batched && density) {
-        // every quartet of the screened set with Gbar = D D: Hermite potentials
-        rc = eri_coul_backward(p, (hipStream_t)stream, density, nbf, grad_centers, grad_exps, energy);
+        // every quartet of a screened set with Gbar = D D: Hermite potentials
+        rc = eri_coul_backward(p, strm, density, nbf, grad_centers, grad_exps, energy);
+        other = false;
+    } else if (listed || !other) {
+        // classes of few quartets: all in one launch
+        rc = eri_adj_backward(p, strm, dl_deri, density, nbf, grad_centers, grad_exps, energy);
+    }
+    if (rc != ERI_OK || !other) {
         if (cur != p->device) (void)hipSetDevice(cur);
         return rc;
     }
@@ -898,7 +913,6 @@ extern "C" int eri_backward(eri_plan* p, void* stream, const double* dl_deri, co
     }
     if (rc == ERI_OK && density && nbf != p->bwd->nbf) rc = ERI_EINVAL;
     eri_bwd_state* st = p->bwd;
-    hipStream_t strm = (hipStream_t)stream;
     const bwd_call call{dl_deri, density, grad_centers, grad_exps, energy};
     if (rc == ERI_OK && grad_centers) {
         hipLaunchKernelGGL(eri_bwd_zero_kernel, dim3(1024), dim3(256), 0, strm, st->d_part,
@@ -910,7 +924,7 @@ extern "C" int eri_backward(eri_plan* p, void* stream, const double* dl_deri, co
         if (hipGetLastError() != hipSuccess) rc = ERI_EHIP;
     }
     for (int c = 0; c < 256 && rc == ERI_OK; ++c)
-        if (p->class_count[c]) rc = run_class(p, st, c, strm, call);
+        if (p->class_count[c] && !adj_listed(p, c)) rc = run_class(p, st, c, strm, call);
     if (rc == ERI_OK && grad_centers) {
         hipLaunchKernelGGL(eri_bwd_reduce_kernel, dim3((unsigned)((st->n_grad + 255) / 256)), dim3(256), 0, strm,
                            st->d_part, st->n_slices, st->n_grad, 3 * (int64_t)p->sh_L.size(), grad_centers,

@@ -436,7 +436,9 @@ int launch(const void* fn, int64_t grid, int rows, int block, void* args, hipStr
     return ERI_OK;
 }
 
-int zero(double* x, int64_t n, hipStream_t strm)
+}  // namespace
+
+int eri_grad_zero(double* x, int64_t n, hipStream_t strm)
 {
     if (n <= 0) return ERI_OK;
     const unsigned g = (unsigned)std::min<int64_t>((n + 255) / 256, 4096);
@@ -445,7 +447,22 @@ int zero(double* x, int64_t n, hipStream_t strm)
     return ERI_OK;
 }
 
-}  // namespace
+int eri_grad_reduce(const double* part, int n_slices, int64_t n_grad, int64_t ns3, double* grad_c, double* grad_e,
+                    hipStream_t strm)
+{
+    if (n_grad <= 0) return ERI_OK;
+    hipLaunchKernelGGL(coul_reduce_kernel, dim3((unsigned)((n_grad + 255) / 256)), dim3(256), 0, strm, part, n_slices,
+                       n_grad, ns3, grad_c, grad_e);
+    ERI_HIP_TRY(hipGetLastError());
+    return ERI_OK;
+}
+
+int eri_energy_add(const double* shares, int64_t n, double* energy, hipStream_t strm)
+{
+    hipLaunchKernelGGL(coul_energy_kernel, dim3(1), dim3(1024), 0, strm, shares, n, energy);
+    ERI_HIP_TRY(hipGetLastError());
+    return ERI_OK;
+}
 
 int eri_coul_backward(eri_plan* p, hipStream_t strm, const double* density, int64_t nbf, double* grad_c, double* grad_e,
                       double* energy)
@@ -492,7 +509,7 @@ int eri_coul_backward(eri_plan* p, hipStream_t strm, const double* density, int6
         return (int)ERI_OK;
     };
     ERI_TRY(per_class(CHARGE, false));
-    if (grad_c) ERI_TRY(zero(st->d_pot, st->n_pot, strm));
+    if (grad_c) ERI_TRY(eri_grad_zero(st->d_pot, st->n_pot, strm));
     for (int k = 24; k >= 0; --k) {   // the longest first
         eri_coul_args c;
         c.jobs = st->d_jobs + st->job0[k];
@@ -505,15 +522,10 @@ int eri_coul_backward(eri_plan* p, hipStream_t strm, const double* density, int6
         ERI_TRY(launch(eri_coul_kernel(k / 5, k % 5, grad_c != nullptr), (c.n_jobs + 3) / 4, 1, 256, &c, strm));
     }
     if (grad_c) {
-        ERI_TRY(zero(st->d_part, (int64_t)st->n_slices * st->n_grad, strm));
+        ERI_TRY(eri_grad_zero(st->d_part, (int64_t)st->n_slices * st->n_grad, strm));
         ERI_TRY(per_class(GRADIENT, true));
-        hipLaunchKernelGGL(coul_reduce_kernel, dim3((unsigned)((st->n_grad + 255) / 256)), dim3(256), 0, strm, st->d_part,
-                           st->n_slices, st->n_grad, a.ns3, grad_c, grad_e);
-        ERI_HIP_TRY(hipGetLastError());
+        ERI_TRY(eri_grad_reduce(st->d_part, st->n_slices, st->n_grad, a.ns3, grad_c, grad_e, strm));
     }
-    if (energy) {
-        hipLaunchKernelGGL(coul_energy_kernel, dim3(1), dim3(1024), 0, strm, st->d_energy, st->job0[25], energy);
-        ERI_HIP_TRY(hipGetLastError());
-    }
+    if (energy) ERI_TRY(eri_energy_add(st->d_energy, st->job0[25], energy, strm));
     return ERI_OK;
 }

@@ -116,6 +116,8 @@ struct eri_entry_row {
 
 struct eri_bwd_state;               // adjoint tables, built at the first eri_backward call
 void eri_bwd_free(eri_bwd_state* b);
+struct eri_adj_state;               // short explicit lists: built at the first eri_backward call
+void eri_adj_free(eri_adj_state* s);
 struct eri_coul_state;              // the density form's tables (screened plans), built at its first call
 void eri_coul_free(eri_coul_state* s);
 
@@ -168,11 +170,29 @@ struct eri_plan {
     std::vector<int64_t> sh_off;
     eri_bwd_state* bwd = nullptr;
     eri_coul_state* coul = nullptr;
+    eri_adj_state* adj = nullptr;
 };
 
 // The density form of eri_backward for screened plans (eri_coulomb.hip).
 int eri_coul_backward(eri_plan* p, hipStream_t strm, const double* density, int64_t nbf, double* grad_c, double* grad_e,
                       double* energy);
+
+// eri_backward of an explicit plan's classes of at most ERI_ADJ_MAX quartets
+// (eri_adjoint.hip; the others go through eri_backward.hip).  The line lies where
+// one class alone takes as long either way: at 1024 / 4096 / 16384 quartets of
+// [pp|pp] 0.31 / 0.89 / 3.28 ms here, 0.96 / 0.94 / 1.50 ms there, of [dp|dp] 0.76 / 2.41 /
+// 9.21 and 1.34 / 1.83 / 4.13 ms, of [dd|dd] 1.69 / 5.53 / 21.3 and 3.37 / 7.87 / 27.7 ms.
+constexpr int64_t ERI_ADJ_MAX = 2048;
+inline bool adj_listed(const eri_plan* p, int c) { return !p->batched && p->class_count[c] && p->class_count[c] <= ERI_ADJ_MAX; }
+int eri_adj_backward(eri_plan* p, hipStream_t strm, const double* dl, const double* density, int64_t nbf, double* grad_c,
+                     double* grad_e, double* energy);
+
+// Clears n doubles; adds n_slices slices of a gradient into the caller's arrays
+// in slice order; adds n (high, low) shares of L to *energy in a fixed order.
+int eri_grad_zero(double* x, int64_t n, hipStream_t strm);
+int eri_grad_reduce(const double* part, int n_slices, int64_t n_grad, int64_t ns3, double* grad_c, double* grad_e,
+                    hipStream_t strm);
+int eri_energy_add(const double* shares, int64_t n, double* energy, hipStream_t strm);
 
 // Items of class quartets [q_lo, q_hi) of a batched plan (defined with the plan code).
 int eri_expand_items(const eri_plan* p, int c, int64_t q_lo, int64_t q_hi, int swap, eri_item* items, hipStream_t st);

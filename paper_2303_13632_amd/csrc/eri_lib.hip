@@ -248,6 +248,7 @@ static void plan_free(eri_plan* p)
     if (p->d_stage) (void)hipFree(p->d_stage);
     if (p->bwd) eri_bwd_free(p->bwd);
     if (p->coul) eri_coul_free(p->coul);
+    if (p->adj) eri_adj_free(p->adj);
     if (cur != p->device) (void)hipSetDevice(cur);
     delete p;
 }
