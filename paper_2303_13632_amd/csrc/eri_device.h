@@ -119,9 +119,12 @@ ERI_DEV int eri_quantize(double x, double eps, double inv, double qmax)
 // Adding the largest double below 1/2 in the value's direction and truncating
 // rounds halves away from zero for every |y| < 2^52, and the conversion to int
 // truncates (NaN to 0): five instructions instead of round()'s
-// trunc / subtract / compare / select / add and two FP64 clamps.
+// trunc / subtract / compare / select / add and two FP64 clamps.  The product is
+// rounded before the addition (no fma), as eq. 10 and eri_quantize have it: a
+// product that rounds to a half is one.
 ERI_DEV int eri_quantize_mul(double x, double inv, double qmax)
 {
+#pragma clang fp contract(off)
     const double y = x * inv;
     const int q = (int)(y + __builtin_copysign(0.49999999999999994, y));
     const int m = (int)qmax;

@@ -53,3 +53,31 @@ def test_not_finite():
     c, s = c.cpu().numpy(), s.cpu().numpy()
     assert s[0] == 2.0 * (1.0 / 32767) and np.isinf(s[1]) and s[2] == 0.0
     assert list(c[:4]) == [0, 16384, -32767, 8192] and not c[4:].any()
+
+
+def _tie_products(n, seed):
+    """Pairs (b_max, x) at 16 bits whose product x * (1/eps) rounds to a half in
+    FP64 while the exact product lies off it."""
+    from fractions import Fraction
+    rng = np.random.default_rng(seed)
+    out = []
+    while len(out) < n:
+        b = rng.uniform(0.5, 2.0)
+        inv = 1.0 / (b * (1.0 / 32767.0))
+        h = float(rng.integers(0, 32766)) + 0.5
+        x = h / inv
+        if x * inv == h and Fraction(x) * Fraction(inv) != Fraction(h):
+            out.append((b, x))
+    return out
+
+
+def test_products_that_round_to_a_half():
+    """The code is the rounding of the rounded product (eq. 10), not of a fused
+    one: half away from zero, bit for bit the oracle's."""
+    pairs = _tie_products(3000, 3)
+    x = np.array([v for b, y in pairs for v in (b, y, -y, 0.0)])
+    off = np.arange(0, len(x) + 1, 4, dtype=np.int64)
+    c, s = eri.compress(16, torch.from_numpy(x).cuda(), torch.from_numpy(off).cuda())
+    oc, oe = O.compress(16, x, off)
+    assert np.array_equal(s.cpu().numpy(), oe)
+    assert np.array_equal(c.cpu().numpy().astype(np.int64), oc.astype(np.int64))
