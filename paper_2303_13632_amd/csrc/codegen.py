@@ -354,7 +354,7 @@ def emit_mode_T(cp, prec, name):
     em("// class [%d%d|%d%d] computed as shells %s = [%d%d|%d%d], mode T, %s" % (cp.user + (cp.perm, a, b, c, d, prec)))
     em("__global__ __launch_bounds__(256) void %s(eri_class_args A)" % name)
     em.block("")
-    em("const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;")
+    em("const int64_t t = ERI_BID * blockDim.x + threadIdx.x;")
     em("if (t >= A.n_items) return;")
     em("const eri_item it = A.items[t];")
     em("const bool sb = it.bra < 0, sk = it.ket < 0;   // pair stored in swapped order")
@@ -477,7 +477,7 @@ def emit_mode_R(cp, name, real="double"):
        % (cp.user + (cp.perm, a, b, c, d, N)))
     em("__global__ __launch_bounds__(256) void %s(eri_class_args A)" % name)
     em.block("")
-    em("const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;")
+    em("const int64_t t = ERI_BID * blockDim.x + threadIdx.x;")
     em("if (t >= A.n_items) return;")
     em("const eri_item it = A.items[t];")
     em("const bool sb = it.bra < 0, sk = it.ket < 0;   // pair stored in swapped order")
@@ -680,7 +680,7 @@ def emit_mode_RW(cp, name, lds_budget=RYSW_LDS, occupancy=1, real="double", nt_s
     em("__shared__ double s_q[%d];   // per primitive quartet: nodes, weights, C00/C00' parts, B parts" % (NB * NQ))
     em("__shared__ double s_red[%d];" % (NT // 64))
     em("const int tid = threadIdx.x;")
-    em("const int64_t qi = blockIdx.x;")
+    em("const int64_t qi = ERI_BID;")
     em("if (qi >= A.n_items) return;   // uniform over the workgroup")
     em("const eri_item it = A.items[qi];")
     em("const bool sb = it.bra < 0, sk = it.ket < 0;   // pair stored in swapped order")
@@ -1059,6 +1059,92 @@ def emit_codes_pass(em, NCH, ket_hrr_chunk, bra_hrr_chunk, slow_expr, pack_tail,
     em.end()
 
 
+# Values of a quartet that a lane keeps in registers between b_max and the codes
+# (single-chunk slot kernels): up to 128 (256 VGPRs; the accumulators are dead by
+# then) at full registers, 60 at half.  The HRR runs once instead of once for
+# b_max and again for the codes, and its code is there once: with the deepest
+# contractions first (ERI_BID) and 64 lanes on the ket columns of one-slot kernels,
+# 16384 [dd|dd] quartets went from 601 to 310 us (280 -> 240 VGPRs, so two wavefronts
+# a SIMD), 65536 [pp|pp] from 109 to 75, 8192 [ff|ff] from 1470 to 1288 (512 VGPRs with
+# 140 bytes of spills -> 387 without).
+HELD_MAX = {1: 128, 2: 60}
+
+
+def hold_values(NCH, NCD, step, nab, waves):
+    return NCH == 1 and (NCD + step - 1) // step * nab <= HELD_MAX[waves]
+
+
+def emit_held_hrr(em, cp, n, step, lane, staged, ab_list, coefs=None):
+    """Bra HRR of every ket index this lane owns (j = lane, lane + step, ...)
+    into registers xv, b_max over them, and the FP64 values if requested."""
+    NIT = (n + step - 1) // step
+    em("double xv[%d][%d];" % (NIT, len(ab_list)))
+    em("#pragma unroll")
+    em.block("for (int it = 0; it < %d; ++it)" % NIT)
+    em("const int j = %s + it * %d;" % (lane, step))
+    em.block("if (active && j < %d)" % n)
+    if coefs is not None:
+        coefs()
+    for k, (ai, bi) in enumerate(ab_list):
+        em("xv[it][%d] = (double)(%s);" % (k, hrr_expr(bi, ai, staged, "ab")))
+        em("bmax = fmax(bmax, fabs(xv[it][%d]));" % k)
+    em.end()
+    em.end()
+    em.block("if (A.out_eri)")
+    emit_held_loop(em, cp, n, step, lane, len(ab_list),
+                   lambda k, ix: "A.out_eri[obase + %s] = xv[it][%d];" % (ix, k))
+    em.end()
+
+
+def emit_held_loop(em, cp, n, step, lane, nab, stmt):
+    """stmt(k, user-layout index) for every held value xv[it][k]."""
+    cb = comps(cp.b)
+    em("#pragma unroll")
+    em.block("for (int it = 0; it < %d; ++it)" % ((n + step - 1) // step))
+    em("const int j = %s + it * %d;" % (lane, step))
+    em.block("if (active && j < %d)" % n)
+    em("const int kcd = j;")
+    emit_kx(em, cp)
+    for k in range(nab):
+        ia_, ib_ = divmod(k, len(cb))
+        bra, _ = index_parts(cp, ia_, ib_, 0, 0)
+        em(stmt(k, "%s + kx" % bra))
+    em.end()
+    em.end()
+
+
+def emit_held_codes(em, cp, n, step, lane, ab_list, stage_base, slow_expr, pack_tail):
+    """Codes of the held values.  The container width and whether any 1/eps of
+    the workgroup overflows are uniform over it, so they are decided once."""
+    nab = len(ab_list)
+    em("const int slow = %s;" % slow_expr)
+    em.block("if (A.pack_bits)")
+    em("const int wide = A.pack_bits > 16;")
+    em("__syncthreads();   // every lane has read the ket-HRR staging; the codes go over it")
+    for cond, t, q in (("!slow && wide", "int32_t", "eri_quantize_mul(xv[it][%d], inv, A.qmax)"),
+                       ("!slow", "int16_t", "eri_quantize_mul(xv[it][%d], inv, A.qmax)"),
+                       (None, None, "eri_quantize(xv[it][%d], eps, inv, A.qmax)")):
+        em.block("if (%s)" % cond if t == "int32_t" else "else if (%s)" % cond if cond else "else")
+        if t:
+            emit_held_loop(em, cp, n, step, lane, nab, lambda k, ix: "reinterpret_cast<%s*>(s_u)[%s(int)(%s)] = (%s)%s;"
+                           % (t, stage_base, ix, t, q % k))
+        else:
+            emit_held_loop(em, cp, n, step, lane, nab, lambda k, ix: "eri_stage_code(s_u, %s(int)(%s), wide, %s);"
+                           % (stage_base, ix, q % k))
+        em.end()
+    pack_tail("s_u")
+    em.end()
+    for ct, nb in (("int16_t", 2), ("int8_t", 1), ("int32_t", 4)):
+        em.block("else if (!slow && A.code_bytes == %d)" % nb)
+        emit_held_loop(em, cp, n, step, lane, nab, lambda k, ix: "reinterpret_cast<%s*>(A.out_codes)[obase + %s] = (%s)"
+                       "eri_quantize_mul(xv[it][%d], inv, A.qmax);" % (ct, ix, ct, k))
+        em.end()
+    em.block("else")
+    emit_held_loop(em, cp, n, step, lane, nab, lambda k, ix: "eri_store_code(A.out_codes, obase + %s, A.code_bytes, "
+                   "eri_quantize(xv[it][%d], eps, inv, A.qmax));" % (ix, k))
+    em.end()
+
+
 def adjoint_form(cp, prec):
     """Kernels that the adjoint launches: FP64 classes reached from user
     shells up to d by one derivative shift (L+1, L-1 or L+2 on one centre),
@@ -1179,6 +1265,10 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
     subs, EP = wave_layout(cp)
     S = len(subs)
     NSLOT = 64 // EP
+    # lanes of a slot outside the recurrences (staging, bra HRR): with one slot
+    # the whole wavefront, also where it has more lanes than bra indices
+    # ([dd|dd]: 36 ket columns in one turn of 64 lanes instead of two of 35)
+    LW = 64 if NSLOT == 1 else EP
     if lds_budget is None:
         # 32 KB of HRR staging, or 40 KB where that makes it a single chunk,
         # which the codes pass then reuses (for bras of L >= 3 such kernels are
@@ -1195,7 +1285,7 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
     src_sub = [0] if S == 1 else [1, 0]
     # per-lane table: for each subslot: ex, ey, ez, valid, tgt, src_x, src_y, src_z
     rows = []
-    for ls in range(EP):
+    for ls in range(LW):
         row = []
         for s in range(S):
             if ls < len(subs[s]):
@@ -1213,7 +1303,7 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
     tbl = "eri_tbl_" + name[4:]
     em("// class [%d%d|%d%d] computed as shells %s = [%d%d|%d%d], mode W: %d lanes/slot, %d slot(s), %d subslot(s), %s"
        % (cp.user + (cp.perm, a, b, c, d, EP, NSLOT, S, prec)))
-    em("static __constant__ signed char %s[%d][%d] = {" % (tbl, EP, 8 * S))
+    em("static __constant__ signed char %s[%d][%d] = {" % (tbl, LW, 8 * S))
     for row in rows:
         em("  {" + ", ".join(str(v) for v in row) + "},")
     em("};")
@@ -1236,9 +1326,9 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
            % (NTE, nar[0], NTE, nar[0]))
     em("__shared__ double s_red[64];")
     em("const int lane = threadIdx.x;")
-    em("const int slot = lane / %d;" % EP)
-    em("const int ls = lane - slot * %d;" % EP)
-    em("const int64_t qi = (int64_t)blockIdx.x * %d + slot;" % NSLOT)
+    em("const int slot = %s;" % ("lane / %d" % EP if NSLOT > 1 else "0"))
+    em("const int ls = %s;" % ("lane - slot * %d" % EP if NSLOT > 1 else "lane"))
+    em("const int64_t qi = ERI_BID * %d + slot;" % NSLOT)
     em("const bool active = slot < %d && qi < A.n_items;" % NSLOT)
     em("const eri_item it = A.items[active ? qi : 0];")
     em("const bool sb = it.bra < 0, sk = it.ket < 0;   // pair stored in swapped order")
@@ -1261,7 +1351,7 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
         for f in cp.F_T:
             acc[(s_, f)] = "acc%d_%d%d%d" % ((s_,) + f)
             em("double %s = 0.0;" % acc[(s_, f)])
-    # Primitive quartets go through the slot in batches of EP: lane ls does
+    # Primitive quartets go through the slot in batches of LW: lane ls does
     # the setup and Boys evaluation of quartet j0 + ls once and stages the
     # results in LDS; then every lane runs the recurrences of each staged
     # quartet.  Trip counts are wave-uniform (max over the slots), staged
@@ -1269,7 +1359,7 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
     em("const int npq = nbra * nket;")
     em("int npq_w = npq;")
     em("for (int o = 32; o > 0; o >>= 1) npq_w = max(npq_w, __shfl_xor(npq_w, o));")
-    em.block("for (int j0 = 0; j0 < npq_w; j0 += %d)" % EP)
+    em.block("for (int j0 = 0; j0 < npq_w; j0 += %d)" % LW)
     em("__syncthreads();")
     em.block("")
     em("double g[%d];" % NF)
@@ -1297,7 +1387,7 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
     em("for (int q = 0; q < %d; ++q) s_u[q * 64 + lane] = g[q];" % NF)
     em.end()
     em("__syncthreads();")
-    em("const int nb = min(%d, npq_w - j0);" % EP)
+    em("const int nb = min(%d, npq_w - j0);" % LW)
     em.block("for (int jj = 0; jj < nb; ++jj)")
     em("const double* u = s_u + pbase + jj;")
     names = ["PAx", "PAy", "PAz", "WPx", "WPy", "WPz", "QCx", "QCy", "QCz", "WQx", "WQy", "WQz",
@@ -1412,11 +1502,11 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
         lo, hi = ch * CH, min(NCD, (ch + 1) * CH)
         n = hi - lo
         if pass_no == 4:
-            emit_pack_regs(em, cp, n, EP, "ls", "active && ",
+            emit_pack_regs(em, cp, n, LW, "ls", "active && ",
                            lambda e: "(%s)%s[slot][%d][j]" % (real, st, tgt_index[e]), ab_list, stage_base,
                            (lambda: emit_hrr_coefs(em, "ab", "BP.AB", cb, real)) if per_use else None)
             return
-        em.block("for (int j = ls; j < %d; j += %d)" % (n, EP))
+        em.block("for (int j = ls; j < %d; j += %d)" % (n, LW))
         em.block("if (active)")
         if per_use:
             emit_hrr_coefs(em, "ab", "BP.AB", cb, real)
@@ -1456,13 +1546,18 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
         em.end()
 
     if adjoint_form(cp, prec):
-        emit_adj_slot(em, ket_hrr_chunk, bra_hrr_chunk, NCH, "lane", "ls", "sbase", EP, "active", "slot", NSLOT,
+        emit_adj_slot(em, ket_hrr_chunk, bra_hrr_chunk, NCH, "lane", "ls", "sbase", LW, "active", "slot", NSLOT,
                       NSLOT * NTE * CH, NSU - NSLOT * NTE * CH)
     em("double bmax = 0.0;")
-    # first pass: b_max, and the FP64 values when requested, decided once (the
+    held = hold_values(NCH, NCD, LW, NAB, waves)
+    if held:
+        ket_hrr_chunk(0)
+        emit_held_hrr(em, cp, NCD, LW, "ls", lambda e: "(%s)s_t[slot][%d][j]" % (real, tgt_index[e]), ab_list,
+                      (lambda: emit_hrr_coefs(em, "ab", "BP.AB", cb, real)) if per_use else None)
+    # two passes: b_max, and the FP64 values when requested, decided once (the
     # output pointer is uniform) except in the half-register kernels, where
     # the duplicated code measured slower than a branch per value
-    if waves == 1:
+    elif waves == 1:
         for store in (True, False):
             em.block("if (A.out_eri)" if store else "else")
             for ch in range(NCH):
@@ -1478,7 +1573,7 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
     em("__syncthreads();")
     em.block("if (A.out_codes)")
     em("double m = 0.0;")
-    em("if (slot < %d) for (int k = 0; k < %d; ++k) m = fmax(m, s_red[sbase + k]);" % (NSLOT, EP))
+    em("if (slot < %d) for (int k = 0; k < %d; ++k) m = fmax(m, s_red[sbase + k]);" % (NSLOT, LW))
     em("const double eps = m * A.cn;")
     em("const double inv = eri_inverse_scale(eps);")
     em("if (active && ls == 0 && A.out_scales) A.out_scales[oslot] = eps;")
@@ -1493,13 +1588,16 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
     def pack_tail(stage):
         # every lane of the workgroup packs the words of all its quartets
         em("__syncthreads();")
-        em("eri_pack_group(%s, %d, (int)min((int64_t)%d, A.n_items - (int64_t)blockIdx.x * %d), A.pack_bits, "
+        em("eri_pack_group(%s, %d, (int)min((int64_t)%d, A.n_items - ERI_BID * %d), A.pack_bits, "
            "A.pack_per, (int)A.pack_wpq, reinterpret_cast<uint32_t*>(A.out_codes), "
-           "A.qbase + (int64_t)blockIdx.x * %d, A.ring, lane, 64);"
+           "A.qbase + ERI_BID * %d, A.ring, lane, 64);"
            % (stage, cp.n_eriq, NSLOT, NSLOT, NSLOT))
 
-    emit_codes_pass(em, NCH, ket_hrr_chunk, bra_hrr_chunk, "__syncthreads_or(__builtin_isinf(inv) ? 1 : 0)", pack_tail,
-                    narrow_arg(G, nar, CH))
+    slow = "__syncthreads_or(__builtin_isinf(inv) ? 1 : 0)"
+    if held:
+        emit_held_codes(em, cp, NCD, LW, "ls", ab_list, stage_base, slow, pack_tail)
+    else:
+        emit_codes_pass(em, NCH, ket_hrr_chunk, bra_hrr_chunk, slow, pack_tail, narrow_arg(G, nar, CH))
     em.end()
     em.end()
     return name, em.text()
@@ -1626,7 +1724,7 @@ def emit_mode_W2(cp, prec, name, lds_budget=None, waves=1, layout="parity"):
     em("const int tid = threadIdx.x;")
     em("const int wv = tid >> 6;")
     em("const int ls = tid & 63;")
-    em("const int64_t qi = blockIdx.x;")
+    em("const int64_t qi = ERI_BID;")
     em("const bool active = qi < A.n_items;")
     em("const eri_item it = A.items[active ? qi : 0];")
     em("const bool sb = it.bra < 0, sk = it.ket < 0;   // pair stored in swapped order")
@@ -1832,14 +1930,20 @@ def emit_mode_W2(cp, prec, name, lds_budget=None, waves=1, layout="parity"):
         emit_adj_slot(em, ket_hrr_chunk, bra_hrr_chunk, NCH, "tid", "tid", "0", 128, "active", "0", 1,
                       NTE * CH, NSU - NTE * CH)
     em("double bmax = 0.0;")
-    # first pass: b_max, and the FP64 values when requested (decided once:
-    # the output pointer is uniform)
-    for store in (True, False):
-        em.block("if (A.out_eri)" if store else "else")
-        for ch in range(NCH):
-            ket_hrr_chunk(ch)
-            bra_hrr_chunk(ch, 1, store_values=store)
-        em.end()
+    held = hold_values(NCH, NCD, 128, len(ab_list), waves)
+    if held:
+        ket_hrr_chunk(0)
+        emit_held_hrr(em, cp, NCD, 128, "tid", lambda e: "(%s)s_t[%d][j]" % (real, tgt_index[e]), ab_list,
+                      (lambda: emit_hrr_coefs(em, "ab", "BP.AB", cb, real)) if per_use else None)
+    else:
+        # two passes: b_max, and the FP64 values when requested (decided once:
+        # the output pointer is uniform)
+        for store in (True, False):
+            em.block("if (A.out_eri)" if store else "else")
+            for ch in range(NCH):
+                ket_hrr_chunk(ch)
+                bra_hrr_chunk(ch, 1, store_values=store)
+            em.end()
     em("__syncthreads();")
     em("s_red[tid] = bmax;")
     em("__syncthreads();")
@@ -1861,8 +1965,11 @@ def emit_mode_W2(cp, prec, name, lds_budget=None, waves=1, layout="parity"):
            "reinterpret_cast<uint32_t*>(A.out_codes), A.qbase + qi, A.ring, tid, 128);"
            % (stage, cp.n_eriq))
 
-    emit_codes_pass(em, NCH, ket_hrr_chunk, bra_hrr_chunk, "__builtin_isinf(inv) ? 1 : 0", pack_tail,
-                    narrow_arg(G, nar, CH))
+    if held:
+        emit_held_codes(em, cp, NCD, 128, "tid", ab_list, stage_base, "__builtin_isinf(inv) ? 1 : 0", pack_tail)
+    else:
+        emit_codes_pass(em, NCH, ket_hrr_chunk, bra_hrr_chunk, "__builtin_isinf(inv) ? 1 : 0", pack_tail,
+                        narrow_arg(G, nar, CH))
     em.end()
     em.end()
     return name, em.text()

@@ -10,6 +10,12 @@
 
 #define ERI_DEV __device__ __forceinline__
 
+// Index of a class kernel's workgroup in plan order, the last one dispatched
+// first: a class is ordered by primitive counts, so the deepest contractions
+// start first and the launch does not end with them (8192 [ff|ff] quartets:
+// BID_AFTER).
+#define ERI_BID ((int64_t)(gridDim.x - 1u - blockIdx.x))
+
 // 2 pi^(5/2)
 #define ERI_TWO_PI_52 34.98683665524972497
 
