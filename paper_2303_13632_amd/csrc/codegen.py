@@ -19,6 +19,8 @@ Two work mappings are emitted:
 
   mode T  one lane computes one contracted quartet; every intermediate is a
           named register value of straight-line code.
+  mode P  mode T's code with a primitive quartet per lane, 16 lanes to a
+          contracted quartet, for launches too small for a lane per quartet.
   mode W  one group of lanes ("slot") computes one quartet: lane l owns one
           bra index e of [e0|..] (two when a slot would exceed 64 lanes,
           split by the parity of |e|).  Each lane builds [e0|00]^(m) along
@@ -346,30 +348,10 @@ def hrr_expr(b, a, getter, prefix):
 # ---------------------------------------------------------------------------
 # Mode T kernel
 # ---------------------------------------------------------------------------
-def emit_mode_T(cp, prec, name):
+def emit_T_vrr(em, cp, prec):
+    """Setup, Boys function and the VRR of one primitive quartet (pairs B, K) as
+    straight-line code; returns the C name of every element."""
     real = REALS[prec]
-    mixed = prec == "mixed"
-    em = Emitter()
-    a, b, c, d = cp.a, cp.b, cp.c, cp.d
-    em("// class [%d%d|%d%d] computed as shells %s = [%d%d|%d%d], mode T, %s" % (cp.user + (cp.perm, a, b, c, d, prec)))
-    em("__global__ __launch_bounds__(256) void %s(eri_class_args A)" % name)
-    em.block("")
-    em("const int64_t t = ERI_BID * blockDim.x + threadIdx.x;")
-    em("if (t >= A.n_items) return;")
-    em("const eri_item it = A.items[t];")
-    em("const bool sb = it.bra < 0, sk = it.ket < 0;   // pair stored in swapped order")
-    em("const eri_shell_pair BP = A.pairs[it.bra & 0x7fffffff];")
-    em("const eri_shell_pair KP = A.pairs[it.ket & 0x7fffffff];")
-    # accumulators
-    acc = {}
-    for e in cp.E_T:
-        for f in cp.F_T:
-            acc[(e, f)] = "acc_%d_%d_%d__%d_%d_%d" % (e + f)
-            em("double %s = 0.0;" % acc[(e, f)])
-    em.block("for (int ib = 0; ib < BP.nprim; ++ib)")
-    em("const eri_prim_pair B = A.prims[BP.prim_off + ib];")
-    em.block("for (int ik = 0; ik < KP.nprim; ++ik)")
-    em("const eri_prim_pair K = A.prims[KP.prim_off + ik];")
     em("eri_pq_fp64 S;")
     em("eri_pq_setup(B, K, S);")
     em("double F[%d];" % (cp.Ltot + 1))
@@ -407,14 +389,14 @@ def emit_mode_T(cp, prec, name):
             if e[i] >= 1:
                 expr += " + (%s * hpq) * %s" % (lit(e[i]), names[(vsub(e, UNIT[i]), fp, m + 1)])
         em("const %s %s = %s;" % (real, names[el], expr))
-    for e in cp.E_T:
-        for f in cp.F_T:
-            if mixed:
-                em("%s += (double)%s;" % (acc[(e, f)], names[(e, f, 0)]))
-            else:
-                em("%s += %s;" % (acc[(e, f)], names[(e, f, 0)]))
-    em.end()
-    em.end()
+    return names
+
+
+def emit_T_hrr(em, cp, prec, acc):
+    """HRR of one quartet from its contracted sums acc[(e, f)]; returns the ERIs
+    as (C name, computed component indices)."""
+    real = REALS[prec]
+    a, b, c, d = cp.a, cp.b, cp.c, cp.d
     # HRR: ket first over every target e, then bra
     ca, cb, cc, cd = comps(a), comps(b), comps(c), comps(d)
     emit_hrr_coefs(em, "ab", "BP.AB", cb, real)
@@ -436,7 +418,144 @@ def emit_mode_T(cp, prec, name):
                     expr = hrr_expr(bi, ai, lambda e, ci=ci, di=di: y[(e, ci, di)], "ab")
                     em("const double %s = (double)(%s);" % (nm, expr))
                     outs.append((nm, (ia, ib_, ic, id_)))
+    return outs
+
+
+def emit_mode_T(cp, prec, name):
+    real = REALS[prec]
+    mixed = prec == "mixed"
+    em = Emitter()
+    a, b, c, d = cp.a, cp.b, cp.c, cp.d
+    em("// class [%d%d|%d%d] computed as shells %s = [%d%d|%d%d], mode T, %s" % (cp.user + (cp.perm, a, b, c, d, prec)))
+    em("__global__ __launch_bounds__(256) void %s(eri_class_args A)" % name)
+    em.block("")
+    em("const int64_t t = ERI_BID * blockDim.x + threadIdx.x;")
+    em("if (t >= A.n_items) return;")
+    em("const eri_item it = A.items[t];")
+    em("const bool sb = it.bra < 0, sk = it.ket < 0;   // pair stored in swapped order")
+    em("const eri_shell_pair BP = A.pairs[it.bra & 0x7fffffff];")
+    em("const eri_shell_pair KP = A.pairs[it.ket & 0x7fffffff];")
+    # accumulators
+    acc = {}
+    for e in cp.E_T:
+        for f in cp.F_T:
+            acc[(e, f)] = "acc_%d_%d_%d__%d_%d_%d" % (e + f)
+            em("double %s = 0.0;" % acc[(e, f)])
+    em.block("for (int ib = 0; ib < BP.nprim; ++ib)")
+    em("const eri_prim_pair B = A.prims[BP.prim_off + ib];")
+    em.block("for (int ik = 0; ik < KP.nprim; ++ik)")
+    em("const eri_prim_pair K = A.prims[KP.prim_off + ik];")
+    names = emit_T_vrr(em, cp, prec)
+    for e in cp.E_T:
+        for f in cp.F_T:
+            if mixed:
+                em("%s += (double)%s;" % (acc[(e, f)], names[(e, f, 0)]))
+            else:
+                em("%s += %s;" % (acc[(e, f)], names[(e, f, 0)]))
+    em.end()
+    em.end()
+    outs = emit_T_hrr(em, cp, prec, acc)
     emit_store_T(em, cp, outs, prec)
+    em.end()
+    return name, em.text()
+
+
+PRIM_LANES = 16    # lanes per quartet of the primitive-parallel kernels
+PRIM_GROUPS = 4    # most quartets that such a slot of lanes takes in turn
+
+
+def emit_mode_P(cp, prec, name):
+    """Kernel of a small class for launches that do not fill the chip with a
+    lane per quartet: 16 lanes per quartet, one primitive quartet per lane and
+    turn (the code of mode T), so a lane's serial chain is a sixteenth of the
+    contraction.  The elements of a turn go through LDS to the lanes that own the
+    contracted sums, which add them in the order of mode T (the sums have mode
+    T's bits).  A wavefront takes four quartets at a time, A.groups times; then
+    one lane per quartet does the HRR and the store.
+    Bound by latency at a few thousand quartets: 4096 [ss|ss] quartets of 81
+    primitive quartets each took 44 us with a lane per quartet and take 8.4.  At
+    half a million the gain is in the loads (a slot's lanes read consecutive
+    primitive pairs): 252 and 143 us."""
+    real = REALS[prec]
+    em = Emitter()
+    a, b, c, d = cp.a, cp.b, cp.c, cp.d
+    keys = [(e, f) for e in cp.E_T for f in cp.F_T]
+    NA = len(keys)
+    R = (NA + PRIM_LANES - 1) // PRIM_LANES
+    SL = 64 // PRIM_LANES
+    # [ss|ss]: mode T adds pref * F_0 in one fma, so the factors are staged
+    base = cp.Ltot == 0 and prec == "fp64"
+    rows = NA + (1 if base else 0)
+    nstage = max(rows * 65, (PRIM_GROUPS * SL * cp.n_eriq * 4 + 7) // 8)
+    em("// class [%d%d|%d%d] computed as shells %s = [%d%d|%d%d], %d lanes per quartet over its primitive quartets, %s"
+       % (cp.user + (cp.perm, a, b, c, d, PRIM_LANES, prec)))
+    em("__global__ __launch_bounds__(64) void %s(eri_class_args A)" % name)
+    em.block("")
+    em("__shared__ double s_v[%d];   // [element][lane], 65 to a row; the packed path's codes" % nstage)
+    em("__shared__ double s_a[%d];   // [contracted sum][quartet], %d to a row" % (NA * (PRIM_GROUPS * SL + 1), PRIM_GROUPS * SL + 1))
+    em("const int lane = threadIdx.x, slot = lane / %d, ls = lane %% %d;" % (PRIM_LANES, PRIM_LANES))
+    em.block("for (int g = 0; g < A.groups; ++g)")
+    em("const int64_t qi = (ERI_BID * A.groups + g) * %d + slot;" % SL)
+    em("const bool active = qi < A.n_items;")
+    em("const eri_item it = A.items[active ? qi : 0];")
+    em("const eri_shell_pair BP = A.pairs[it.bra & 0x7fffffff];")
+    em("const eri_shell_pair KP = A.pairs[it.ket & 0x7fffffff];")
+    em("const int nket = KP.nprim;")
+    em("const int npq = active ? BP.nprim * nket : 0;")
+    em("int npq_w = npq;")
+    em("for (int o = 32; o >= %d; o >>= 1) npq_w = max(npq_w, __shfl_xor(npq_w, o));" % PRIM_LANES)
+    em("double sum[%d];" % R)
+    em("#pragma unroll")
+    em("for (int r = 0; r < %d; ++r) sum[r] = 0.0;" % R)
+    em.block("for (int j0 = 0; j0 < npq_w; j0 += %d)" % PRIM_LANES)
+    em("const int j = j0 + ls;")
+    em.block("if (j < npq)")
+    em("const int ib = j / nket, ik = j - ib * nket;")
+    em("const eri_prim_pair B = A.prims[BP.prim_off + ib];")
+    em("const eri_prim_pair K = A.prims[KP.prim_off + ik];")
+    names = emit_T_vrr(em, cp, prec)
+    for k, (e, f) in enumerate(keys):
+        if base:
+            em("s_v[lane] = S.pref;")
+            em("s_v[65 + lane] = F[0];")
+        else:
+            em("s_v[%d + lane] = (double)%s;" % (65 * k, names[(e, f, 0)]))
+    em.end()
+    em("__syncthreads();")
+    em("const int cnt = min(%d, npq - j0);" % PRIM_LANES)
+    em("#pragma unroll")
+    em.block("for (int r = 0; r < %d; ++r)" % R)
+    em("const int k = ls + %d * r;" % PRIM_LANES)
+    em("const double* v = s_v + (k < %d ? k : 0) * 65 + slot * %d;" % (NA, PRIM_LANES))
+    add = "sum[r] = fma(v[t], v[t + 65], sum[r])" if base else "sum[r] += v[t]"
+    em.block("if (__all(cnt >= %d))" % PRIM_LANES)
+    em("#pragma unroll")
+    em("for (int t = 0; t < %d; ++t) %s;" % (PRIM_LANES, add))
+    em.end()
+    em.block("else")
+    em("for (int t = 0; t < cnt; ++t) %s;" % add)
+    em.end()
+    em.end()
+    em("__syncthreads();")
+    em.end()
+    em("#pragma unroll")
+    em("for (int r = 0; r < %d; ++r) if (ls + %d * r < %d) s_a[(ls + %d * r) * %d + g * %d + slot] = sum[r];"
+       % (R, PRIM_LANES, NA, PRIM_LANES, PRIM_GROUPS * SL + 1, SL))
+    em.end()
+    em("__syncthreads();")
+    em("const int64_t t = ERI_BID * A.groups * %d + lane;" % SL)
+    em("if (lane >= A.groups * %d || t >= A.n_items) return;" % SL)
+    em("const eri_item it = A.items[t];")
+    em("const bool sb = it.bra < 0, sk = it.ket < 0;   // pair stored in swapped order")
+    em("const eri_shell_pair BP = A.pairs[it.bra & 0x7fffffff];")
+    em("const eri_shell_pair KP = A.pairs[it.ket & 0x7fffffff];")
+    acc = {}
+    for k, (e, f) in enumerate(keys):
+        acc[(e, f)] = "acc_%d_%d_%d__%d_%d_%d" % (e + f)
+        em("const double %s = s_a[%d + lane];" % (acc[(e, f)], k * (PRIM_GROUPS * SL + 1)))
+    outs = emit_T_hrr(em, cp, prec, acc)
+    PACK_DYNAMIC_LDS[name] = 0
+    emit_store_T(em, cp, outs, prec, adjoint=False, stage="s_v", stride=str(PRIM_GROUPS * SL), at="lane")
     em.end()
     return name, em.text()
 
@@ -1202,14 +1321,15 @@ def emit_adj_slot(em, ket_hrr_chunk, bra_hrr_chunk, NCH, lane, ls, base, n, acti
     em.end()
 
 
-def emit_store_T(em, cp, outs, prec):
+def emit_store_T(em, cp, outs, prec, adjoint=True, stage="eri_pack_lds", stride="(int)blockDim.x",
+                 at="(int)threadIdx.x"):
     n = cp.n_eriq
     emit_slot(em, "t")
     em("const int64_t obase = oslot * %d;" % n)
     for k, (nm, ix) in enumerate(outs):
         bra, ket = index_parts(cp, *ix)
         em("const int i%d = %s + %s;" % (k, bra, ket))
-    if adjoint_form(cp, prec):
+    if adjoint and adjoint_form(cp, prec):
         emit_adj_T(em, outs)
     em.block("if (A.out_eri)")
     for k, (nm, ix) in enumerate(outs):
@@ -1226,10 +1346,9 @@ def emit_store_T(em, cp, outs, prec):
     # packed stream: this lane's codes go to its LDS column, then it packs its quartet's words
     em("const int wide = A.pack_bits > 16;")
     for k, (nm, ix) in enumerate(outs):
-        em("eri_stage_code(eri_pack_lds, i%d * (int)blockDim.x + (int)threadIdx.x, wide, "
-           "eri_quantize(%s, eps, inv, A.qmax));" % (k, nm))
-    em("eri_pack_words(eri_pack_lds, %d, (int)threadIdx.x, (int)blockDim.x, A.pack_bits, A.pack_per, "
-       "(int)A.pack_wpq, reinterpret_cast<uint32_t*>(A.out_codes) + oslot * A.pack_wpq * 16);" % n)
+        em("eri_stage_code(%s, i%d * %s + %s, wide, eri_quantize(%s, eps, inv, A.qmax));" % (stage, k, stride, at, nm))
+    em("eri_pack_words(%s, %d, %s, %s, A.pack_bits, A.pack_per, "
+       "(int)A.pack_wpq, reinterpret_cast<uint32_t*>(A.out_codes) + oslot * A.pack_wpq * 16);" % (stage, n, at, stride))
     em.end()
     em.block("else")
     for k, (nm, ix) in enumerate(outs):
@@ -2053,6 +2172,7 @@ HEADER = """// Generated by codegen.py -- class-specialised ERI kernels.
 TAG_DEFAULT, TAG_ALT, TAG_OCC2, TAG_TWO_WAVES, TAG_SWAP = 0, 1, 2, 3, 4
 TAG_TWO_WAVES_OCC2 = 5
 TAG_TWO_WAVES_XCOL_OCC2 = 6
+TAG_PRIM = 13        # primitive-parallel kernel of a small class (chosen by launch size, no tuner variant)
 # workgroup Rys kernels (RYSW_VARIANTS): 7 larger batches; 8, 9 twice the threads at 4 or 2 waves per
 # SIMD; 10, 11, 12 the node loop not unrolled (at 1 and 2 waves per SIMD, and twice the threads at 2)
 
@@ -2149,6 +2269,13 @@ def generate(outdir, precisions=("fp64",), classes=None, group=8, overrides=None
                 parts.append(src)
                 lines_.append("    t[%d] = %s;" % (c5, with_flags(kernel_info_init(cp, name))))
                 infos = variant_infos(cp, name)
+            if cp.mode == "T" and max(user) <= 3:
+                pname = name + "_p"
+                parts.append(emit_mode_P(cp, prec, pname)[1])
+                per_pq, per_q = cp.flops()
+                pk = cp.perm[0] | (cp.perm[1] << 2) | (cp.perm[2] << 4) | (cp.perm[3] << 6)
+                lines_.append("    p[%d] = %s;" % (c5, with_flags("{(const void*)%s, 1, 64, %d, %d, %d, %d, %d, %d}" % (
+                    pname, 64 // PRIM_LANES, cp.n_eriq, per_pq, per_q, pk, TAG_PRIM))))
             am = alternate_mode(cp) if max(user) <= 3 else None
             if am is not None:
                 acp = ClassPlan(*user, mode=am, perm=cp.perm)
@@ -2189,7 +2316,7 @@ def generate(outdir, precisions=("fp64",), classes=None, group=8, overrides=None
                 lines_.append("    v[%d] = %s;" % (c5 * MAXVAR + k, with_flags(info)))
         for prec, lines_ in reg.items():
             fname = "eri_register_%s_g%03d" % (prec, g // group)
-            parts.append("void %s(eri_kernel_info* t, eri_kernel_info* v)\n{\n%s\n}\n" % (fname, "\n".join(lines_)))
+            parts.append("void %s(eri_kernel_info* t, eri_kernel_info* v, eri_kernel_info* p)\n{\n%s\n}\n" % (fname, "\n".join(lines_)))
             regs.append((prec, fname))
         fn = os.path.join(outdir, "eri_k%03d.hip" % (g // group))
         write_if_changed(fn, "\n".join(parts))
@@ -2217,7 +2344,7 @@ def generate(outdir, precisions=("fp64",), classes=None, group=8, overrides=None
                     lines_.append("    t[%d] = %s;" % (c5, info))
                 lines_.append("    v[%d] = %s;" % (c5 * MAXVAR + k, info))
         fname = "eri_register_%s" % rprec
-        parts.append("void %s(eri_kernel_info* t, eri_kernel_info* v)\n{\n%s\n}\n" % (fname, "\n".join(lines_)))
+        parts.append("void %s(eri_kernel_info* t, eri_kernel_info* v, eri_kernel_info* p)\n{\n%s\n}\n" % (fname, "\n".join(lines_)))
         fn = os.path.join(outdir, "eri_%s.hip" % rprec)
         write_if_changed(fn, "\n".join(parts))
         files.append(fn)
@@ -2249,18 +2376,19 @@ def generate(outdir, precisions=("fp64",), classes=None, group=8, overrides=None
                     lines_.append("    v[%d] = %s;" % (c5 * MAXVAR + k, info))
                     k += 1
             fname = "eri_register_%sw_g%02d" % (rprec, gi // 24)
-            parts.append("void %s(eri_kernel_info* t, eri_kernel_info* v)\n{\n%s\n}\n" % (fname, "\n".join(lines_)))
+            parts.append("void %s(eri_kernel_info* t, eri_kernel_info* v, eri_kernel_info* p)\n{\n%s\n}\n" % (fname, "\n".join(lines_)))
             fn = os.path.join(outdir, "eri_%sw_g%02d.hip" % (rprec, gi // 24))
             write_if_changed(fn, "\n".join(parts))
             files.append(fn)
             regs.append((rprec, fname))
     lines = ['#include "eri_dispatch.h"', "#include <mutex>"]
     for prec, fname in regs:
-        lines.append("void %s(eri_kernel_info* t, eri_kernel_info* v);" % fname)
+        lines.append("void %s(eri_kernel_info* t, eri_kernel_info* v, eri_kernel_info* p);" % fname)
     lines.append("static eri_kernel_info g_fp64[ERI_NCLASS5], g_mixed[ERI_NCLASS5], g_rys[ERI_NCLASS5], "
                  "g_rys32[ERI_NCLASS5];")
     lines.append("static eri_kernel_info v_fp64[ERI_NCLASS5 * ERI_MAXVAR], v_mixed[ERI_NCLASS5 * ERI_MAXVAR],")
     lines.append("    v_rys[ERI_NCLASS5 * ERI_MAXVAR], v_rys32[ERI_NCLASS5 * ERI_MAXVAR];")
+    lines.append("static eri_kernel_info p_fp64[ERI_NCLASS5], p_mixed[ERI_NCLASS5], p_rys[ERI_NCLASS5], p_rys32[ERI_NCLASS5];")
     lines.append("static std::once_flag g_once;")
     routed = [class_id5(*c) for c in classes if class_id(*c) not in fp32_ok] if "mixed" in precisions else []
     lines.append("// classes whose FP32-mixed entries are their FP64 kernels")
@@ -2269,10 +2397,11 @@ def generate(outdir, precisions=("fp64",), classes=None, group=8, overrides=None
     lines.append("{")
     lines.append("    std::call_once(g_once, [] {")
     for prec, fname in regs:
-        lines.append("        %s(g_%s, v_%s);" % (fname, prec, prec))
+        lines.append("        %s(g_%s, v_%s, p_%s);" % (fname, prec, prec, prec))
     lines.append("        for (int c5 : g_mixed_fp64) {")
     lines.append("            if (c5 < 0) continue;")
     lines.append("            g_mixed[c5] = g_fp64[c5];")
+    lines.append("            p_mixed[c5] = p_fp64[c5];")
     lines.append("            for (int k = 0; k < ERI_MAXVAR; ++k) v_mixed[c5 * ERI_MAXVAR + k] = v_fp64[c5 * ERI_MAXVAR + k];")
     lines.append("        }")
     lines.append("    });")
@@ -2286,6 +2415,11 @@ def generate(outdir, precisions=("fp64",), classes=None, group=8, overrides=None
     lines.append("{")
     lines.append("    fill();")
     lines.append("    return precision == 3 ? v_rys32 : precision == 2 ? v_rys : precision == 1 ? v_mixed : v_fp64;")
+    lines.append("}")
+    lines.append("const eri_kernel_info* eri_kernel_prim(int precision)")
+    lines.append("{")
+    lines.append("    fill();")
+    lines.append("    return precision == 3 ? p_rys32 : precision == 2 ? p_rys : precision == 1 ? p_mixed : p_fp64;")
     lines.append("}")
     fn = os.path.join(outdir, "eri_dispatch_table.hip")
     write_if_changed(fn, "\n".join(lines) + "\n")

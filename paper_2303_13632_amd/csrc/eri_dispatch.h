@@ -17,7 +17,7 @@ struct eri_kernel_info {
                          // registers (the default of an f-f bra is the two-wavefront x-column form);
                          // workgroup Rys kernels: 7 larger batches of primitive quartets, 8 twice the threads
                          // at 4 waves per SIMD, 9 twice the threads at 2; 10, 11, 12 the node loop not
-                         // unrolled (1 and 2 waves per SIMD, twice the threads at 2)
+                         // unrolled (1 and 2 waves per SIMD, twice the threads at 2); 13 primitive-parallel
     int32_t fp32;        // 1: VRR/HRR in FP32 (FP32-mixed kernel); 0: FP64
     int32_t pack_dyn;    // packed stream stages codes in dynamic LDS: 0 never, 1 always, 2 for n > 16
 };
@@ -36,3 +36,8 @@ const eri_kernel_info* eri_kernel_table(int precision);
 // and ket exchanged (perm), which the plan's items must follow.
 #define ERI_MAXVAR 8
 const eri_kernel_info* eri_kernel_variants(int precision);
+
+// Primitive-parallel kernels of the classes that take a lane per quartet
+// (per_block quartets a workgroup for each of its eri_class_args.groups turns;
+// the default kernel's orientation and bits); fn == nullptr for other classes.
+const eri_kernel_info* eri_kernel_prim(int precision);

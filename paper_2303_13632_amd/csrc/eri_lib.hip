@@ -805,7 +805,7 @@ static void fill_args(eri_plan* p, int c, eri_class_args& a, double* out_eri, vo
     a.cn = p->cn;
     a.qmax = p->qmax;
     a.code_bytes = p->code_bytes;
-    a.pad = 0;
+    a.groups = 1;
     a.ring = p->class_ring[c];
     a.qbase = 0;
 }
@@ -820,9 +820,38 @@ static size_t pack_lds(const eri_kernel_info& ki, const eri_class_args& a)
     return (size_t)ki.per_block * ki.n_eriq * (a.pack_bits > 16 ? 4 : 2);
 }
 
+// Whether a class that takes a lane per quartet runs its primitive-parallel
+// kernel for n quartets of up to maxpq primitive quartets.  A lane per quartet
+// walks its contraction in series and reads primitive pairs that lie apart
+// between the lanes; 16 lanes per quartet cost an LDS round trip per turn and
+// leave lanes idle in the HRR.  Measured (us, lane per quartet / 16 lanes, K
+// 1..3 a shell): [ss|ss] 48 / 10 at 1024 quartets, 54 / 33 at 32767, 252 / 143
+// at 524288; [pp|ps] 78 / 18, 86 / 54, 297 / 403; [dp|ps] (48 contracted sums)
+// 110 / 27, 116 / 74, 387 / 860, and at 131072 139 / 220; K = 12, 16384 quartets
+// of [dp|ps]: 29.8 / 12.4 ms.  With K = 1 there is no contraction to
+// split ([dp|ps], 32767 quartets: 17 / 52).
+constexpr int ERI_TAG_PRIM = 13;
+constexpr int64_t ERI_PRIM_MAX = 65536;   // classes of more than 32 contracted sums
+static bool prim_better(int c, int64_t n, int64_t maxpq)
+{
+    auto sums = [](int x, int y) {
+        int s = 0;
+        for (int l = std::max(x, y); l <= x + y; ++l) s += ncart(l);
+        return s;
+    };
+    return maxpq >= 4 && (n < ERI_PRIM_MAX || sums(c >> 6, (c >> 4) & 3) * sums((c >> 2) & 3, c & 3) <= 32);
+}
+
+// Turns of its workgroups: one while that leaves the chip room (four quartets
+// a wavefront, sixteen wavefronts a CU), else four, which fill the lanes of the
+// HRR and the store better.
+static int prim_groups(int64_t n) { return n <= 16384 ? 1 : 4; }
+
 static int launch_items(const eri_kernel_info& ki, eri_class_args& a, hipStream_t st)
 {
-    const int64_t grid = (a.n_items + ki.per_block - 1) / ki.per_block;
+    a.groups = ki.tag == ERI_TAG_PRIM ? prim_groups(a.n_items) : 1;
+    const int64_t per = (int64_t)ki.per_block * a.groups;
+    const int64_t grid = (a.n_items + per - 1) / per;
     if (grid == 0) return ERI_OK;
     if (grid > INT32_MAX) return ERI_EUNSUPPORTED;
     void* args[] = {&a};
@@ -857,6 +886,27 @@ static int orient_items(eri_plan* p, int c, const eri_kernel_info& ki, hipStream
     return ERI_OK;
 }
 
+// Default kernel of a class of the plan for launches of n quartets: a kernel
+// with the bits of variant 0.  Above a chip full of workgroups the
+// half-register forms of the largest kernels, which hold twice as many, are
+// ahead where they spill little: two wavefronts of an f-f bra with a ket of L
+// 2..4 (averages at 1024 / 8192 quartets: [ff|dd]-like 146 / 634 us at full registers,
+// 166 / 481 at half), and [fd|fd] (237 / 483 and 243 / 373).
+constexpr int64_t ERI_HALF_MIN = 2048;
+static const eri_kernel_info& default_kernel(const eri_plan* p, int c, int64_t n)
+{
+    if (n >= ERI_HALF_MIN) {
+        const int lb = (c >> 6) + ((c >> 4) & 3), lk = ((c >> 2) & 3) + (c & 3);
+        const int hi = std::max(lb, lk), lo = std::min(lb, lk);
+        const int tag = hi == 6 && lo >= 2 && lo <= 4 ? 6 : hi == 5 && lo == 5 ? 2 : 0;
+        const eri_kernel_info* v = eri_kernel_variants(table_index(p->precision)) + (int64_t)class_id5_of(c) * ERI_MAXVAR;
+        for (int k = 1; k < ERI_MAXVAR && tag && p->precision <= ERI_FP32_MIXED; ++k)
+            if (v[k].fn && v[k].tag == tag) return v[k];
+    }
+    const eri_kernel_info& prim = eri_kernel_prim(table_index(p->precision))[class_id5_of(c)];
+    return prim.fn && prim_better(c, n, p->class_maxpq[c]) ? prim : kernel_table(p->precision)[class_id5_of(c)];
+}
+
 // Kernel of a class launch: the autotuner's variant, else the default.
 static const eri_kernel_info& class_kernel(const eri_plan* p, int c)
 {
@@ -865,7 +915,7 @@ static const eri_kernel_info& class_kernel(const eri_plan* p, int c)
         const eri_kernel_info& v = eri_kernel_variants(table_index(p->precision))[c5 * ERI_MAXVAR + p->class_var[c]];
         if (v.fn) return v;
     }
-    return kernel_table(p->precision)[c5];
+    return default_kernel(p, c, p->batched ? class_piece(p, c) : p->class_count[c]);
 }
 
 // Compression of one class's FP64 values in blocks of S consecutive values
@@ -957,7 +1007,7 @@ static int compute_check(eri_plan* p, double* out_eri, void* out_codes, double* 
 static double launch_seconds(const eri_plan* p, int c)
 {
     const eri_kernel_info& ki = class_kernel(p, c);
-    return (double)p->class_maxpq[c] * ki.flops_pq * (ki.mode == 0 ? 5e-9 : 8e-11) + p->class_flops[c] * 1e-13 + 5e-6;
+    return (double)p->class_maxpq[c] * ki.flops_pq * (ki.mode == 0 ? 5e-9 : ki.tag == ERI_TAG_PRIM ? 4e-10 : 8e-11) + p->class_flops[c] * 1e-13 + 5e-6;
 }
 
 // What the side streams must gain over one stream to be worth the events
@@ -1236,8 +1286,8 @@ static int tune_plan(eri_plan* p, hipStream_t st, int64_t sample, int trials, co
         double best = 0.0;
         int bestk = 0;
         for (int k = 0; k < ERI_MAXVAR && rc == ERI_OK; ++k) {
-            const eri_kernel_info& ki = var[c5 * ERI_MAXVAR + k];
-            if (!ki.fn) continue;
+            if (!var[c5 * ERI_MAXVAR + k].fn) continue;
+            const eri_kernel_info& ki = k ? var[c5 * ERI_MAXVAR + k] : default_kernel(p, c, n);
             // the sample's items in this variant's orientation
             if (!p->batched) {
                 rc = orient_items(p, c, ki, st);

@@ -72,7 +72,7 @@ struct eri_class_args {
     double cn;                      // 1 / (2^(bits-1) - 1)
     double qmax;                    // 2^(bits-1) - 1
     int32_t code_bytes;             // 1, 2 or 4
-    int32_t pad;
+    int32_t groups;                 // primitive-parallel kernels: turns of a workgroup
     int64_t ring;                   // output slots of the class: quartet q lands in slot q mod ring
     int64_t qbase;                  // class index of this launch's first quartet
     int32_t pack_bits;              // > 0: out_codes is the packed stream of pack_bits-bit codes

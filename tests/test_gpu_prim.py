@@ -1,0 +1,51 @@
+"""Primitive-parallel kernels (default of small launches): the bits of the
+class's other kernels with the same orientation, FP64 values, codes, scales and
+packed words, at the edges of their work split: one quartet, workgroups partly
+filled, contractions that end anywhere in a turn, several turns of a workgroup."""
+import numpy as np
+import pytest
+
+from paper_2303_13632_amd import eri, workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+PRIM = 13
+SAME = (0, 1, 2)     # tags of kernels with the default's operation order
+
+
+def _outputs(plan, cid, variant):
+    v = np.zeros(256, np.int32)
+    v[cid] = variant
+    plan.set_variants(v)
+    out = [t.zero_() for t in plan.alloc(eri=True)]
+    plan.compute(*out)
+    torch.cuda.synchronize()
+    return int(plan.class_tag[cid]), out
+
+
+def _compare(L, n, k, precision="fp64", forms=((16, False),)):
+    cid = W.class_id(*L)
+    kw = {"k_fixed": k} if k else {}
+    shells, quartets = W.random_class_quartets(*L, n, 7 * n + cid, **kw)
+    for bits, packed in forms:
+        plan = eri.Plan(shells, quartets, precision=precision, bits=bits, packed=packed)
+        tag, got = _outputs(plan, cid, 0)
+        assert tag == PRIM
+        others = 0
+        for variant in range(1, int(plan.class_n_variants[cid])):
+            tag, ref = _outputs(plan, cid, variant)
+            if tag in SAME:
+                others += 1
+                for g, r in zip(got, ref):
+                    assert torch.equal(g, r), (L, n, k, bits, packed, variant)
+        assert others
+
+
+@pytest.mark.parametrize("L", [(0, 0, 0, 0), (0, 1, 0, 0), (1, 0, 0, 2), (1, 1, 0, 1), (2, 1, 0, 1), (0, 0, 3, 1),
+                               (2, 2, 0, 0), (2, 0, 0, 2)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_lane_per_quartet_classes(L, precision):
+    for n, k in ((1, 16), (3, 5), (4, 4), (5, 3), (17, 0), (65, 0), (16385, 2)):
+        _compare(L, n, k, precision)
+    _compare(L, 67, 0, precision, forms=((3, True), (8, True), (12, True), (24, True), (8, False), (32, False)))
