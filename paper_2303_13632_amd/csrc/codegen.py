@@ -1376,7 +1376,29 @@ def wave_layout(cp):
     return subs, ep
 
 
-def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
+def prim_waves(cp):
+    """Wavefronts over the primitive quartets of a slot kernel (emit_mode_W with
+    pw): four, or two, within 150 KB of LDS; None where there is no such form."""
+    subs, EP = wave_layout(cp)
+    if cp.mode != "W" or len(subs) != 1:
+        return None
+    NSLOT = 64 // EP
+    hrr = NSLOT * len(cp.E_T) * ncart(cp.c) * ncart(cp.d)
+    for pw in (4, 2):
+        if max(hrr, (cp.Ltot + 18) * 64 * pw) + (pw * len(cp.F_T) + pw) * 64 <= 150 * 128:
+            return pw
+    return None
+
+
+def emit_mode_W(cp, prec, name, lds_budget=None, waves=1, pw=1):
+    """pw > 1: launches of few workgroups.  pw wavefronts share the slots; each
+    stages its share of a batch of primitive quartets and then takes every
+    pw-th of them through the recurrences.  After each turn the wavefronts exchange
+    the elements through LDS, and each adds, for its share of the ket indices f,
+    the pw primitive quartets in order (so the sums have the bits of pw = 1).
+    Bound by the length of the chain of primitive quartets at a few hundred
+    quartets: 256 [dd|dd] of K 1..3 took 128 us with one wavefront and take 76,
+    [fd|fd] 234 and 117, [dp|dp] 75 and 42."""
     real = REALS[prec]
     mixed = prec == "mixed"
     em = Emitter()
@@ -1388,7 +1410,9 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
     # the whole wavefront, also where it has more lanes than bra indices
     # ([dd|dd]: 36 ket columns in one turn of 64 lanes instead of two of 35)
     LW = 64 if NSLOT == 1 else EP
-    if lds_budget is None:
+    if pw > 1:
+        lds_budget = 150 * 1024    # one chunk (prim_waves)
+    elif lds_budget is None:
         # 32 KB of HRR staging, or 40 KB where that makes it a single chunk,
         # which the codes pass then reuses (for bras of L >= 3 such kernels are
         # register-bound at four workgroups per CU: the LDS costs no occupancy)
@@ -1426,14 +1450,17 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
     for row in rows:
         em("  {" + ", ".join(str(v) for v in row) + "},")
     em("};")
-    if waves > 1:
+    if pw > 1:
+        em("__global__ __launch_bounds__(%d) void %s(eri_class_args A)" % (64 * pw, name))
+    elif waves > 1:
         # at least `waves` wavefronts per SIMD: the register budget halves
         em("__global__ __launch_bounds__(64, %d) void %s(eri_class_args A)" % (waves, name))
     else:
         em("__global__ __launch_bounds__(64) void %s(eri_class_args A)" % name)
     em.block("")
     NF = cp.Ltot + 1 + 17          # staged fields of one primitive quartet
-    NSU = max(NSLOT * NTE * CH, NF * 64)
+    SG = 64 * pw                   # staged primitive quartets, from field to field
+    NSU = max(NSLOT * NTE * CH, NF * SG)
     # one LDS buffer: primitive-quartet staging during the VRR loop, then the
     # HRR staging s_t[slot][target e][cd chunk]
     em("__shared__ double s_u[%d];" % NSU)
@@ -1443,8 +1470,14 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
     if nar:
         em("double (*s_tp)[%d][%d] = reinterpret_cast<double (*)[%d][%d]>(s_u);   // packed codes pass"
            % (NTE, nar[0], NTE, nar[0]))
-    em("__shared__ double s_red[64];")
-    em("const int lane = threadIdx.x;")
+    em("__shared__ double s_red[%d];" % SG)
+    NFT = len(cp.F_T)
+    if pw > 1:
+        assert S == 1 and NCH == 1
+        em("__shared__ double s_x[%d];   // elements [wavefront][f][lane]; then the contracted sums [f][lane]" % (pw * NFT * 64))
+        em("const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;")
+    else:
+        em("const int lane = threadIdx.x;")
     em("const int slot = %s;" % ("lane / %d" % EP if NSLOT > 1 else "0"))
     em("const int ls = %s;" % ("lane - slot * %d" % EP if NSLOT > 1 else "lane"))
     em("const int64_t qi = ERI_BID * %d + slot;" % NSLOT)
@@ -1467,9 +1500,23 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
     # accumulators per subslot
     acc = {}
     for s_ in range(S):
-        for f in cp.F_T:
+        for k, f in enumerate(cp.F_T):
+            if pw > 1:
+                acc[(s_, f)] = "s_x[%d + lane]" % (64 * k)
+                continue
             acc[(s_, f)] = "acc%d_%d%d%d" % ((s_,) + f)
             em("double %s = 0.0;" % acc[(s_, f)])
+    NR = (NFT + pw - 1) // pw
+    if pw > 1:
+        em("double sum[%d];   // of f = wv, wv + %d, ..." % (NR, pw))
+        em("#pragma unroll")
+        em("for (int r = 0; r < %d; ++r) sum[r] = 0.0;" % NR)
+
+    def add_target(s, f, v):
+        if pw > 1:
+            em("s_x[(wv * %d + %d) * 64 + lane] = (double)%s;" % (NFT, cp.F_T.index(f), v))
+        else:
+            em("%s += %s;" % (acc[(s, f)], ("(double)" + v) if mixed else v))
     # Primitive quartets go through the slot in batches of LW: lane ls does
     # the setup and Boys evaluation of quartet j0 + ls once and stages the
     # results in LDS; then every lane runs the recurrences of each staged
@@ -1478,14 +1525,14 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
     em("const int npq = nbra * nket;")
     em("int npq_w = npq;")
     em("for (int o = 32; o > 0; o >>= 1) npq_w = max(npq_w, __shfl_xor(npq_w, o));")
-    em.block("for (int j0 = 0; j0 < npq_w; j0 += %d)" % LW)
+    em.block("for (int j0 = 0; j0 < npq_w; j0 += %d)" % (LW * pw))
     em("__syncthreads();")
     em.block("")
     em("double g[%d];" % NF)
     em("#pragma unroll")
     em("for (int q = 0; q < %d; ++q) g[q] = 0.0;" % NF)
-    em("const int j = j0 + ls;")
-    em.block("if (active && j < npq)")
+    em("const int j = j0 + %sls;" % ("wv * %d + " % LW if pw > 1 else ""))
+    em.block("if (active && %sj < npq)" % ("ls < %d && " % LW if pw > 1 else ""))
     em("const int ib = j / nket, ik = j - ib * nket;")
     em("const eri_prim_pair B = A.prims[BP.prim_off + ib];")
     em("const eri_prim_pair K = A.prims[KP.prim_off + ik];")
@@ -1503,21 +1550,27 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
         em("g[%d] = %s;" % (o + k, fld))
     em.end()
     em("#pragma unroll")
-    em("for (int q = 0; q < %d; ++q) s_u[q * 64 + lane] = g[q];" % NF)
+    em("for (int q = 0; q < %d; ++q) s_u[q * %d + %s] = g[q];" % (NF, SG, "tid" if pw > 1 else "lane"))
     em.end()
     em("__syncthreads();")
-    em("const int nb = min(%d, npq_w - j0);" % LW)
-    em.block("for (int jj = 0; jj < nb; ++jj)")
-    em("const double* u = s_u + pbase + jj;")
+    em("const int nb = min(%d, npq_w - j0);" % (LW * pw))
+    if pw > 1:
+        em.block("for (int jr = 0; jr < nb; jr += %d)" % pw)
+        em("const int jj = jr + wv;")
+        em.block("if (jj < nb)")
+        em("const double* u = s_u + pbase + (jj / %d) * 64 + jj %% %d;" % (LW, LW))
+    else:
+        em.block("for (int jj = 0; jj < nb; ++jj)")
+        em("const double* u = s_u + pbase + jj;")
     names = ["PAx", "PAy", "PAz", "WPx", "WPy", "WPz", "QCx", "QCy", "QCz", "WQx", "WQy", "WQz",
              "hp", "hq", "hpq", "rp", "rq"]
     for k, nm in enumerate(names):
-        em("const %s %s = (%s)u[%d];" % (real, nm, real, 64 * (o + k)))
+        em("const %s %s = (%s)u[%d];" % (real, nm, real, SG * (o + k)))
     MB = cp.Ltot
     for s_ in range(S):
         em("%s c%d[%d], p%d[%d], nx%d[%d];" % (real, s_, MB + 2, s_, MB + 2, s_, MB + 2))
         em("#pragma unroll")
-        em("for (int m = 0; m <= %d; ++m) { c%d[m] = (%s)u[64 * m]; p%d[m] = (%s)0; }" % (MB, s_, real, s_, real))
+        em("for (int m = 0; m <= %d; ++m) { c%d[m] = (%s)u[%d * m]; p%d[m] = (%s)0; }" % (MB, s_, real, SG, s_, real))
         em("const %s cex%d = (%s)ex%d * hpq, cey%d = (%s)ey%d * hpq, cez%d = (%s)ez%d * hpq;"
            % (real, s_, real, s_, s_, real, s_, s_, real, s_))
     # bra path: step t builds level t along z, then y, then x; lanes already
@@ -1555,7 +1608,7 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
         if f == ZERO:
             if ZERO in tset:
                 for s in range(S):
-                    em("%s += %s;" % (acc[(s, f)], ("(double)" + V[(s, f, 0)]) if mixed else V[(s, f, 0)]))
+                    add_target(s, f, V[(s, f, 0)])
             continue
         L = sum(f)
         i = 0 if f[0] > 0 else (1 if f[1] > 0 else 2)
@@ -1579,10 +1632,24 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
                 V[(s, f, m)] = nm
         if f in tset:
             for s in range(S):
-                v = V[(s, f, 0)]
-                em("%s += %s;" % (acc[(s, f)], ("(double)" + v) if mixed else v))
+                add_target(s, f, V[(s, f, 0)])
     em.end()
+    if pw > 1:
+        em("__syncthreads();")
+        em("const int nw = min(%d, nb - jr);" % pw)
+        em("#pragma unroll")
+        em.block("for (int r = 0; r < %d; ++r)" % NR)
+        em("const double* x = s_x + min(wv + %d * r, %d) * 64 + lane;" % (pw, NFT - 1))
+        em("#pragma unroll")
+        em("for (int t = 0; t < %d; ++t) if (t < nw) sum[r] += x[t * %d];" % (pw, NFT * 64))
+        em.end()
+        em("__syncthreads();")
+        em.end()
     em.end()
+    if pw > 1:
+        em("#pragma unroll")
+        em("for (int r = 0; r < %d; ++r) if (wv + %d * r < %d) s_x[(wv + %d * r) * 64 + lane] = sum[r];"
+           % (NR, pw, NFT, pw))
     # HRR
     emit_slot(em, "qi")
     em("const int64_t obase = oslot * %d;" % cp.n_eriq)
@@ -1607,10 +1674,17 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
             em.block("if (active && tg%d >= 0)" % s)
             if per_use:
                 emit_hrr_coefs(em, "cd", "KP.AB", cd, real)
-            for k in range(lo, hi):
-                ci, di = cd_list[k]
-                expr = hrr_expr(di, ci, lambda f, s=s: "(%s)%s" % (real, acc[(s, f)]), "cd")
-                em("%s[slot][tg%d][%d] = (double)(%s);" % (st, s, k - lo, expr))
+            # with pw > 1 the wavefronts take shares of the ket columns
+            share = (hi - lo + pw - 1) // pw
+            for v in range(pw):
+                if pw > 1:
+                    em.block("if (wv == %d)" % v)
+                for k in range(lo + v * share, min(hi, lo + (v + 1) * share)):
+                    ci, di = cd_list[k]
+                    expr = hrr_expr(di, ci, lambda f, s=s: "(%s)%s" % (real, acc[(s, f)]), "cd")
+                    em("%s[slot][tg%d][%d] = (double)(%s);" % (st, s, k - lo, expr))
+                if pw > 1:
+                    em.end()
             em.end()
         em("__syncthreads();")
 
@@ -1664,14 +1738,16 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
         em.end()
         em.end()
 
-    if adjoint_form(cp, prec):
+    if adjoint_form(cp, prec) and pw == 1:
         emit_adj_slot(em, ket_hrr_chunk, bra_hrr_chunk, NCH, "lane", "ls", "sbase", LW, "active", "slot", NSLOT,
                       NSLOT * NTE * CH, NSU - NSLOT * NTE * CH)
     em("double bmax = 0.0;")
-    held = hold_values(NCH, NCD, LW, NAB, waves)
+    held = hold_values(NCH, NCD, LW * pw, NAB, waves)
+    hl = "(ls + %d * wv)" % LW if pw > 1 else "ls"   # first ket index of a lane
+    assert held or pw == 1, name
     if held:
         ket_hrr_chunk(0)
-        emit_held_hrr(em, cp, NCD, LW, "ls", lambda e: "(%s)s_t[slot][%d][j]" % (real, tgt_index[e]), ab_list,
+        emit_held_hrr(em, cp, NCD, LW * pw, hl, lambda e: "(%s)s_t[slot][%d][j]" % (real, tgt_index[e]), ab_list,
                       (lambda: emit_hrr_coefs(em, "ab", "BP.AB", cb, real)) if per_use else None)
     # two passes: b_max, and the FP64 values when requested, decided once (the
     # output pointer is uniform) except in the half-register kernels, where
@@ -1688,14 +1764,16 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
             ket_hrr_chunk(ch)
             bra_hrr_chunk(ch, 1, store_values=None)
     em("__syncthreads();")
-    em("s_red[lane] = bmax;")
+    em("s_red[%s] = bmax;" % ("tid" if pw > 1 else "lane"))
     em("__syncthreads();")
     em.block("if (A.out_codes)")
     em("double m = 0.0;")
     em("if (slot < %d) for (int k = 0; k < %d; ++k) m = fmax(m, s_red[sbase + k]);" % (NSLOT, LW))
+    for v in range(1, pw):
+        em("if (slot < %d) for (int k = 0; k < %d; ++k) m = fmax(m, s_red[%d + sbase + k]);" % (NSLOT, LW, 64 * v))
     em("const double eps = m * A.cn;")
     em("const double inv = eri_inverse_scale(eps);")
-    em("if (active && ls == 0 && A.out_scales) A.out_scales[oslot] = eps;")
+    em("if (active && ls == 0 %s&& A.out_scales) A.out_scales[oslot] = eps;" % ("&& wv == 0 " if pw > 1 else ""))
     # with a single chunk its ket-HRR staging is still in LDS: only the bra
     # HRR is repeated (with several chunks, re-ordering them measured slower)
     # 0: codes over the kernel's own LDS; 1: dynamic LDS; 2: dynamic LDS only
@@ -1709,12 +1787,12 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1):
         em("__syncthreads();")
         em("eri_pack_group(%s, %d, (int)min((int64_t)%d, A.n_items - ERI_BID * %d), A.pack_bits, "
            "A.pack_per, (int)A.pack_wpq, reinterpret_cast<uint32_t*>(A.out_codes), "
-           "A.qbase + ERI_BID * %d, A.ring, lane, 64);"
-           % (stage, cp.n_eriq, NSLOT, NSLOT, NSLOT))
+           "A.qbase + ERI_BID * %d, A.ring, %s, %d);"
+           % (stage, cp.n_eriq, NSLOT, NSLOT, NSLOT, "tid" if pw > 1 else "lane", SG))
 
     slow = "__syncthreads_or(__builtin_isinf(inv) ? 1 : 0)"
     if held:
-        emit_held_codes(em, cp, NCD, LW, "ls", ab_list, stage_base, slow, pack_tail)
+        emit_held_codes(em, cp, NCD, LW * pw, hl, ab_list, stage_base, slow, pack_tail)
     else:
         emit_codes_pass(em, NCH, ket_hrr_chunk, bra_hrr_chunk, slow, pack_tail, narrow_arg(G, nar, CH))
     em.end()
@@ -2276,6 +2354,12 @@ def generate(outdir, precisions=("fp64",), classes=None, group=8, overrides=None
                 pk = cp.perm[0] | (cp.perm[1] << 2) | (cp.perm[2] << 4) | (cp.perm[3] << 6)
                 lines_.append("    p[%d] = %s;" % (c5, with_flags("{(const void*)%s, 1, 64, %d, %d, %d, %d, %d, %d}" % (
                     pname, 64 // PRIM_LANES, cp.n_eriq, per_pq, per_q, pk, TAG_PRIM))))
+            npw = prim_waves(cp)
+            if npw and max(user) <= 3:
+                pname = name + "_p"
+                parts.append(emit_mode_W(cp, prec, pname, pw=npw)[1])
+                info = kernel_info_init(cp, pname, tag=TAG_PRIM)
+                lines_.append("    p[%d] = %s;" % (c5, with_flags(info.replace(", 1, 64, ", ", 1, %d, " % (64 * npw), 1))))
             am = alternate_mode(cp) if max(user) <= 3 else None
             if am is not None:
                 acp = ClassPlan(*user, mode=am, perm=cp.perm)

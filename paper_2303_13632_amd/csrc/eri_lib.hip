@@ -847,9 +847,13 @@ static bool prim_better(int c, int64_t n, int64_t maxpq)
 // HRR and the store better.
 static int prim_groups(int64_t n) { return n <= 16384 ? 1 : 4; }
 
+// A primitive-parallel kernel with 16 lanes per quartet (one wavefront; those of
+// the slot kernels have several).
+static bool prim_lanes(const eri_kernel_info& ki) { return ki.tag == ERI_TAG_PRIM && ki.block == 64; }
+
 static int launch_items(const eri_kernel_info& ki, eri_class_args& a, hipStream_t st)
 {
-    a.groups = ki.tag == ERI_TAG_PRIM ? prim_groups(a.n_items) : 1;
+    a.groups = prim_lanes(ki) ? prim_groups(a.n_items) : 1;
     const int64_t per = (int64_t)ki.per_block * a.groups;
     const int64_t grid = (a.n_items + per - 1) / per;
     if (grid == 0) return ERI_OK;
@@ -886,6 +890,14 @@ static int orient_items(eri_plan* p, int c, const eri_kernel_info& ki, hipStream
     return ERI_OK;
 }
 
+// Slot kernels: workgroups up to which several wavefronts share the primitive
+// quartets of a slot.  Below a chip full of workgroups the contraction's length is
+// the time (us, one wavefront / several, 256 quartets of K 1..3: [pp|pp] 39 / 31,
+// [dp|dp] 75 / 42, [dd|dd] 128 / 76, [fd|fd] 234 / 117); at 1024 quartets the two
+// are equal for [dd|dd] and [fd|fd], and beyond that the exchange is only a cost.
+// Contractions of fewer than 8 primitive quartets have too few turns to gain.
+constexpr int64_t ERI_PRIM_GROUPS = 512;
+
 // Default kernel of a class of the plan for launches of n quartets: a kernel
 // with the bits of variant 0.  Above a chip full of workgroups the
 // half-register forms of the largest kernels, which hold twice as many, are
@@ -904,7 +916,9 @@ static const eri_kernel_info& default_kernel(const eri_plan* p, int c, int64_t n
             if (v[k].fn && v[k].tag == tag) return v[k];
     }
     const eri_kernel_info& prim = eri_kernel_prim(table_index(p->precision))[class_id5_of(c)];
-    return prim.fn && prim_better(c, n, p->class_maxpq[c]) ? prim : kernel_table(p->precision)[class_id5_of(c)];
+    const bool better = prim_lanes(prim) ? prim_better(c, n, p->class_maxpq[c])
+                                         : n <= ERI_PRIM_GROUPS * prim.per_block && p->class_maxpq[c] >= 8;
+    return prim.fn && better ? prim : kernel_table(p->precision)[class_id5_of(c)];
 }
 
 // Kernel of a class launch: the autotuner's variant, else the default.
@@ -1002,12 +1016,14 @@ static int compute_check(eri_plan* p, double* out_eri, void* out_codes, double* 
 
 // Seconds of a class launch: its deepest contraction through one lane or slot
 // plus its whole work at the chip's rate (measured: 5e-9 s per FLOP of a lane's
-// own work, 8e-11 s through a slot of lanes, 1e13 FLOP/s in all).  Only the
+// own work, 8e-11 s through a slot of lanes, 4e-10 and 3e-11 in their primitive-
+// parallel kernels, 1e13 FLOP/s in all).  Only the
 // order and the balance of the streams depend on it.
 static double launch_seconds(const eri_plan* p, int c)
 {
     const eri_kernel_info& ki = class_kernel(p, c);
-    return (double)p->class_maxpq[c] * ki.flops_pq * (ki.mode == 0 ? 5e-9 : ki.tag == ERI_TAG_PRIM ? 4e-10 : 8e-11) + p->class_flops[c] * 1e-13 + 5e-6;
+    const double rate = prim_lanes(ki) ? 4e-10 : ki.tag == ERI_TAG_PRIM ? 3e-11 : ki.mode == 0 ? 5e-9 : 8e-11;
+    return (double)p->class_maxpq[c] * ki.flops_pq * rate + p->class_flops[c] * 1e-13 + 5e-6;
 }
 
 // What the side streams must gain over one stream to be worth the events
