@@ -729,6 +729,144 @@ def rysw_shape(cp, lds_budget=RYSW_LDS, vbytes=8, nt_scale=1):
     return NT, (n + NT - 1) // NT, NB, NI
 
 
+def emit_rys_setup(em, cp, real, NT, NB, n_name):
+    """Opens the loop over batches of NB primitive quartets (n_name: how many
+    this batch has) and emits step 1 of emit_mode_RW: rule entries and setup
+    into s_q."""
+    N = cp.Ltot // 2 + 1
+    NQ = 2 * N + 18
+    f32 = real == "float"
+    em.block("for (int j0 = 0; j0 < npq; j0 += %d)" % NB)
+    em("__syncthreads();   // the previous batch's factors are consumed")
+    em("const int %s = min(%d, npq - j0);" % (n_name, NB))
+    em.block("for (int t = tid; t < %s * %d; t += %d)" % (n_name, 2 * N, NT))
+    em("const int jb = t / %d, e = t - jb * %d;" % (2 * N, 2 * N))
+    em("const int j = j0 + jb;")
+    em("const int ib = j / nket, ik = j - ib * nket;")
+    em("const eri_prim_pair B = A.prims[BP.prim_off + ib];")
+    em("const eri_prim_pair K = A.prims[KP.prim_off + ik];")
+    em("eri_pq_fp64 S;")
+    em("eri_pq_setup(B, K, S);")
+    em("const double v = eri_rys_rule_entry<%d>(S.T, e);" % N)
+    em("double* q = s_q + jb * %d;" % NQ)
+    if f32:
+        em("q[e] = v;")
+    else:
+        em("q[e] = e < %d ? v : v * S.pref;" % N)
+    em.block("if (e == 0)")
+    em("q[%d] = S.pref;" % (2 * N + 17))
+    for i in range(3):
+        em("q[%d] = B.PA[%d]; q[%d] = S.WP[%d]; q[%d] = K.PA[%d]; q[%d] = S.WQ[%d];"
+           % (2 * N + i, i, 2 * N + 3 + i, i, 2 * N + 6 + i, i, 2 * N + 9 + i, i))
+    em("q[%d] = S.hpq; q[%d] = B.hp; q[%d] = S.rho_p; q[%d] = K.hp; q[%d] = S.rho_q;"
+       % tuple(2 * N + 12 + i for i in range(5)))
+    em.end()
+    em.end()
+
+
+def emit_rys_factors(em, cp, flops, real, NT, NI, idx1, barriers=False, batch="jb", half=False):
+    """Step 2 of emit_mode_RW: the 1D factors of each node and axis of the nb
+    primitive quartets of s_q from `batch` into s_I at idx1(a', b', c', d');
+    half: before the transfers to B, at idx1(e, c', d') with e up to La + Lb."""
+    a, b, c, d = cp.a, cp.b, cp.c, cp.d
+    f32 = real == "float"
+    N = cp.Ltot // 2 + 1
+    NQ = 2 * N + 18
+    dims = (a + 1, b + 1, c + 1, d + 1)
+
+    def rl(x):
+        return lit(x) + ("f" if f32 else "")
+
+    def count(expr):
+        # one (node, axis) task: every node and axis of a primitive quartet runs it
+        flops[0] += 3 * N * (expr.count("*") + expr.count(" + ") + expr.count(" - "))
+    em("__syncthreads();")
+    em.block("for (int t = tid; t < nb * %d; t += %d)" % (3 * N, NT))
+    em("const int jb = t / %d, rr = t - jb * %d;" % (3 * N, 3 * N))
+    em("const int r = rr / 3, ax = rr - 3 * r;")
+    em("const double* q = s_q + %s * %d;" % (batch, NQ))
+    em("const double u = q[r];")
+    R = real
+    em("const %s B00 = (%s)(u * q[%d]);" % (R, R, 2 * N + 12))
+    em("const %s B10 = (%s)(q[%d] - q[%d] * q[%d] * u);" % (R, R, 2 * N + 13, 2 * N + 13, 2 * N + 14))
+    em("const %s B01 = (%s)(q[%d] - q[%d] * q[%d] * u);" % (R, R, 2 * N + 15, 2 * N + 15, 2 * N + 16))
+    em("const %s C00 = (%s)(q[%d + ax] + u * q[%d + ax]);" % (R, R, 2 * N, 2 * N + 3))
+    em("const %s D00 = (%s)(q[%d + ax] + u * q[%d + ax]);" % (R, R, 2 * N + 6, 2 * N + 9))
+    em("const %s AB = (%s)(ax == 0 ? BP.AB[0] : ax == 1 ? BP.AB[1] : BP.AB[2]);" % (R, R))
+    em("const %s CD = (%s)(ax == 0 ? KP.AB[0] : ax == 1 ? KP.AB[1] : KP.AB[2]);" % (R, R))
+    em("const %s g_0_0 = ax == 2 ? (%s)q[%d + r] : %s;" % (R, R, N, rl(1)))
+    flops[0] += N * (5 + 3 * 4)
+    defined = {"g_0_0"}
+
+    def g(nn, m):
+        nm = "g_%d_%d" % (nn, m)
+        if nm in defined:
+            return nm
+        if m == 0:
+            expr = "C00 * %s" % g(nn - 1, 0)
+            if nn - 1 >= 1:
+                expr += " + %s * B10 * %s" % (rl(nn - 1), g(nn - 2, 0))
+        else:
+            expr = "D00 * %s" % g(nn, m - 1)
+            if m - 1 >= 1:
+                expr += " + %s * B01 * %s" % (rl(m - 1), g(nn, m - 2))
+            if nn >= 1:
+                expr += " + %s * B00 * %s" % (rl(nn), g(nn - 1, m - 1))
+        count(expr)
+        if cp.Ltot <= RYS_LMAX and (nn, m) in ((2, 0), (1, 1), (0, 2)):
+            # emit_mode_R's rounding: G(0, 0) = 1 of x and y leaves one product there
+            one = ("C00", "g_1_0", "B10") if m == 0 else ("D00", "g_1_0", "B00") if nn else ("D00", "g_0_1", "B01")
+            expr = "ax == 2 ? %s : fma(%s, %s, %s)" % ((expr,) + one)
+        em("const %s %s = %s;" % (real, nm, expr))
+        defined.add(nm)
+        return nm
+
+    def kh(nn, cx, dx):
+        if dx == 0:
+            return g(nn, cx)
+        nm = "k_%d_%d_%d" % (nn, cx, dx)
+        if nm in defined:
+            return nm
+        expr = "%s + CD * %s" % (kh(nn, cx + 1, dx - 1), kh(nn, cx, dx - 1))
+        em("const %s %s = %s;" % (real, nm, expr))
+        count(expr)
+        defined.add(nm)
+        return nm
+
+    def ih(ax_a, bx, cx, dx):
+        if bx == 0:
+            return kh(ax_a, cx, dx)
+        nm = "i_%d_%d_%d_%d" % (ax_a, bx, cx, dx)
+        if nm in defined:
+            return nm
+        expr = "%s + AB * %s" % (ih(ax_a + 1, bx - 1, cx, dx), ih(ax_a, bx - 1, cx, dx))
+        em("const %s %s = %s;" % (real, nm, expr))
+        count(expr)
+        defined.add(nm)
+        return nm
+    em("%s* I = s_I + ((jb * %d + r) * 3 + ax) * %d;" % (real, N, NI))
+    if half:
+        for cx, dx in itertools.product(range(dims[2]), range(dims[3])):
+            for e in range(dims[0] + dims[1] - 1):
+                em("I[%d] = %s;" % (idx1((e, cx, dx)), kh(e, cx, dx)))
+        # the transfers to B are the owner threads' (counted once per factor here)
+        for bx in range(1, dims[1]):
+            flops[0] += 3 * N * 2 * (dims[0] + dims[1] - 1 - bx) * dims[2] * dims[3]
+    else:
+        # column by column of the ket (c', d'): its transfers to B, stored at once;
+        # in the variants for the largest classes (node loop not unrolled) a
+        # scheduling barrier between columns keeps the compiler from hoisting
+        # every column's work (those ran out of registers); elsewhere it cost time
+        for cdx in itertools.product(range(dims[2]), range(dims[3])):
+            for abx in itertools.product(range(dims[0]), range(dims[1])):
+                t = abx + cdx
+                em("I[%d] = %s;" % (idx1(t), ih(*t)))
+            if barriers:
+                em("__builtin_amdgcn_sched_barrier(0);")
+    em.end()
+    em("__syncthreads();")
+
+
 def emit_mode_RW(cp, name, lds_budget=RYSW_LDS, occupancy=1, real="double", nt_scale=1, unroll=True):
     """Rys-quadrature kernel of a class whose ERIs do not fit one lane (Sec.
     II-C, eqs. 5-8): one workgroup per quartet, in the orientation cp.perm.
@@ -762,9 +900,6 @@ def emit_mode_RW(cp, name, lds_budget=RYSW_LDS, occupancy=1, real="double", nt_s
     NQ = 2 * N + 18
     nbuf = NB * N * 3 * NI
     nbuf = max(nbuf, (4 * n + vb - 1) // vb)      # the packed path stages int32 codes over it
-
-    def rl(x):
-        return lit(x) + ("f" if f32 else "")
     dims = (a + 1, b + 1, c + 1, d + 1)
 
     def idx1(t):
@@ -780,10 +915,6 @@ def emit_mode_RW(cp, name, lds_budget=RYSW_LDS, occupancy=1, real="double", nt_s
     assert 3 * NI <= 1024 and len(tab) == n
     em = Emitter()
     flops = [30 + 2 * N * 3 * RYS_DEG + 2 * N]    # setup, the node/weight series, the weights' prefactor
-
-    def count(expr):
-        # one (node, axis) task: every node and axis of a primitive quartet runs it
-        flops[0] += 3 * N * (expr.count("*") + expr.count(" + ") + expr.count(" - "))
     em("// class [%d%d|%d%d] computed as shells %s = [%d%d|%d%d], Rys quadrature (%d nodes), one workgroup of %d "
        "threads per quartet" % (cp.user + (cp.perm, a, b, c, d, N, NT)))
     em("static __device__ const uint32_t %s_tab[%d] = {" % (name, n))
@@ -815,105 +946,8 @@ def emit_mode_RW(cp, name, lds_budget=RYSW_LDS, occupancy=1, real="double", nt_s
     em("off[s] = k < %d ? %s_tab[k] : 0u;" % (n, name))
     em("acc[s] = 0.0;")
     em.end()
-    em.block("for (int j0 = 0; j0 < npq; j0 += %d)" % NB)
-    em("__syncthreads();   // the previous batch's factors are consumed")
-    em("const int nb = min(%d, npq - j0);" % NB)
-    em.block("for (int t = tid; t < nb * %d; t += %d)" % (2 * N, NT))
-    em("const int jb = t / %d, e = t - jb * %d;" % (2 * N, 2 * N))
-    em("const int j = j0 + jb;")
-    em("const int ib = j / nket, ik = j - ib * nket;")
-    em("const eri_prim_pair B = A.prims[BP.prim_off + ib];")
-    em("const eri_prim_pair K = A.prims[KP.prim_off + ik];")
-    em("eri_pq_fp64 S;")
-    em("eri_pq_setup(B, K, S);")
-    em("const double v = eri_rys_rule_entry<%d>(S.T, e);" % N)
-    em("double* q = s_q + jb * %d;" % NQ)
-    if f32:
-        em("q[e] = v;")
-    else:
-        em("q[e] = e < %d ? v : v * S.pref;" % N)
-    em.block("if (e == 0)")
-    em("q[%d] = S.pref;" % (2 * N + 17))
-    for i in range(3):
-        em("q[%d] = B.PA[%d]; q[%d] = S.WP[%d]; q[%d] = K.PA[%d]; q[%d] = S.WQ[%d];"
-           % (2 * N + i, i, 2 * N + 3 + i, i, 2 * N + 6 + i, i, 2 * N + 9 + i, i))
-    em("q[%d] = S.hpq; q[%d] = B.hp; q[%d] = S.rho_p; q[%d] = K.hp; q[%d] = S.rho_q;"
-       % tuple(2 * N + 12 + i for i in range(5)))
-    em.end()
-    em.end()
-    em("__syncthreads();")
-    em.block("for (int t = tid; t < nb * %d; t += %d)" % (3 * N, NT))
-    em("const int jb = t / %d, rr = t - jb * %d;" % (3 * N, 3 * N))
-    em("const int r = rr / 3, ax = rr - 3 * r;")
-    em("const double* q = s_q + jb * %d;" % NQ)
-    em("const double u = q[r];")
-    R = real
-    em("const %s B00 = (%s)(u * q[%d]);" % (R, R, 2 * N + 12))
-    em("const %s B10 = (%s)(q[%d] - q[%d] * q[%d] * u);" % (R, R, 2 * N + 13, 2 * N + 13, 2 * N + 14))
-    em("const %s B01 = (%s)(q[%d] - q[%d] * q[%d] * u);" % (R, R, 2 * N + 15, 2 * N + 15, 2 * N + 16))
-    em("const %s C00 = (%s)(q[%d + ax] + u * q[%d + ax]);" % (R, R, 2 * N, 2 * N + 3))
-    em("const %s D00 = (%s)(q[%d + ax] + u * q[%d + ax]);" % (R, R, 2 * N + 6, 2 * N + 9))
-    em("const %s AB = (%s)(ax == 0 ? BP.AB[0] : ax == 1 ? BP.AB[1] : BP.AB[2]);" % (R, R))
-    em("const %s CD = (%s)(ax == 0 ? KP.AB[0] : ax == 1 ? KP.AB[1] : KP.AB[2]);" % (R, R))
-    em("const %s g_0_0 = ax == 2 ? (%s)q[%d + r] : %s;" % (R, R, N, rl(1)))
-    flops[0] += N * (5 + 3 * 4)
-    defined = {"g_0_0"}
-
-    def g(nn, m):
-        nm = "g_%d_%d" % (nn, m)
-        if nm in defined:
-            return nm
-        if m == 0:
-            expr = "C00 * %s" % g(nn - 1, 0)
-            if nn - 1 >= 1:
-                expr += " + %s * B10 * %s" % (rl(nn - 1), g(nn - 2, 0))
-        else:
-            expr = "D00 * %s" % g(nn, m - 1)
-            if m - 1 >= 1:
-                expr += " + %s * B01 * %s" % (rl(m - 1), g(nn, m - 2))
-            if nn >= 1:
-                expr += " + %s * B00 * %s" % (rl(nn), g(nn - 1, m - 1))
-        em("const %s %s = %s;" % (real, nm, expr))
-        count(expr)
-        defined.add(nm)
-        return nm
-
-    def kh(nn, cx, dx):
-        if dx == 0:
-            return g(nn, cx)
-        nm = "k_%d_%d_%d" % (nn, cx, dx)
-        if nm in defined:
-            return nm
-        expr = "%s + CD * %s" % (kh(nn, cx + 1, dx - 1), kh(nn, cx, dx - 1))
-        em("const %s %s = %s;" % (real, nm, expr))
-        count(expr)
-        defined.add(nm)
-        return nm
-
-    def ih(ax_a, bx, cx, dx):
-        if bx == 0:
-            return kh(ax_a, cx, dx)
-        nm = "i_%d_%d_%d_%d" % (ax_a, bx, cx, dx)
-        if nm in defined:
-            return nm
-        expr = "%s + AB * %s" % (ih(ax_a + 1, bx - 1, cx, dx), ih(ax_a, bx - 1, cx, dx))
-        em("const %s %s = %s;" % (real, nm, expr))
-        count(expr)
-        defined.add(nm)
-        return nm
-    em("%s* I = s_I + ((jb * %d + r) * 3 + ax) * %d;" % (real, N, NI))
-    # column by column of the ket (c', d'): its transfers to B, stored at once;
-    # in the variants for the largest classes (node loop not unrolled) a
-    # scheduling barrier between columns keeps the compiler from hoisting
-    # every column's work (those ran out of registers); elsewhere it cost time
-    for cdx in itertools.product(range(dims[2]), range(dims[3])):
-        for abx in itertools.product(range(dims[0]), range(dims[1])):
-            t = abx + cdx
-            em("I[%d] = %s;" % (idx1(t), ih(*t)))
-        if NI > 64 and not unroll:
-            em("__builtin_amdgcn_sched_barrier(0);")
-    em.end()
-    em("__syncthreads();")
+    emit_rys_setup(em, cp, real, NT, NB, "nb")
+    emit_rys_factors(em, cp, flops, real, NT, NI, idx1, barriers=NI > 64 and not unroll)
     em.block("for (int jb = 0; jb < nb; ++jb)")
     if f32:
         em("float t[%d];" % S)
@@ -982,6 +1016,225 @@ def emit_mode_RW(cp, name, lds_budget=RYSW_LDS, occupancy=1, real="double", nt_s
     em("#pragma unroll")
     em("for (int s = 0; s < %d; ++s) if (tid + %d * s < %d) eri_store_code(A.out_codes, obase + uix[s], "
        "A.code_bytes, eri_quantize(acc[s], eps, inv, A.qmax));" % (S, NT, n))
+    em.end()
+    em.end()
+    em.end()
+    return name, em.text(), flops[0]
+
+
+# forms of the column kernels: (lanes own the ket pair and the bra's transfer
+# runs in them, shell of the other pair that threads are split over)
+RYSC_HALF, RYSC_WHOLE, RYSC_FULL = (True, 0), (True, None), (False, 0)
+
+
+def rysc_forms(cp):
+    """Forms of a class's column kernels: (default, of small launches), None for
+    the table-driven kernel or no other.  Measured at 30 / 16384 quartets of K 1..3
+    (us): the table-driven kernel, half split, half whole, full split
+      [ff|ff] 772 / 10463, 305 / 4778, 496 / 3536, 543 / 7120
+      [fd|fd] 338 / 3629, 87 / 1910, 132 / 1221, 97 / 1947
+      [dd|dd] 80 / 862, 34 / 526, 80 / 837, 39 / 529
+      [ff|ps] 26 / 266, 37 / 175, 158 / 1732, 21 / 388
+      [dd|ps] 14 / 70, 18 / 94, 33 / 383, 10 / 89
+    A whole column per thread does the transfers once per node, but leaves [fd|fd]
+    60 threads; the split form has ten times as many.  Kets of few components
+    leave either short of threads: a small launch does better with the factors in
+    full and the larger pair's components on the lanes, and up to 108 ERIs a large
+    one with the table."""
+    ket = ncart(cp.c) * ncart(cp.d)
+    few = ket * ncart(cp.a) <= 90 and cp.n_eriq <= 600
+    return (RYSC_WHOLE if min(ket, ncart(cp.a) * ncart(cp.b)) >= 60 else RYSC_HALF if cp.n_eriq > 108 or not few else None,
+            RYSC_FULL if few else RYSC_HALF if min(ket, ncart(cp.a) * ncart(cp.b)) >= 60 else None)
+
+
+def rysc_lane_form(cp):
+    """Form of small launches of a class that emit_mode_R takes a lane per quartet for."""
+    return RYSC_HALF if ncart(cp.c) * ncart(cp.d) >= 9 else RYSC_FULL
+
+
+def rysc_shape(cp, form, vbytes=8):
+    """Work split of a column kernel: (half, lane pair is the ket, lane components,
+    shell of the other pair that threads are split over or None, ERIs per thread,
+    threads, primitive quartets per batch of factors and of setups, row length of
+    the factors: odd, so that rows of different lanes start in different banks)."""
+    a, b, c, d = cp.a, cp.b, cp.c, cp.d
+    nab, ncd = ncart(a) * ncart(b), ncart(c) * ncart(d)
+    N = cp.Ltot // 2 + 1
+    half, split = form
+    ket = half or ncd >= nab
+    NL = ncd if ket else nab
+    r1, r2 = (a, b) if ket else (c, d)
+    NS = 1 if split is None else ncart(r1)
+    NO = ncart(r1) * ncart(r2) // NS
+    NT = 64 * ((NL * NS + 63) // 64)
+    row = (r1 + r2 + 1 if half else (r1 + 1) * (r2 + 1)) | 1
+    NI = ((c + 1) * (d + 1) if ket else (a + 1) * (b + 1)) * row
+    NB = max(1, min(max(NT, 128) // (3 * N), RYSW_LDS // (3 * N * NI * vbytes)))
+    NQB = max(1, min(max(NT, 128), 256) // (2 * N) // NB) * NB
+    return half, ket, NL, split, NO, NT, NB, NQB, row
+
+
+def emit_mode_RC(cp, name, form, real="double"):
+    """The workgroup Rys kernel with the quadrature's 1D factors in registers: a
+    thread owns one component pair of a shell pair (a "column") and all ERIs of
+    it, or those of one component of the other pair's first shell.  Per node it
+    reads the factors of its column once and multiplies them with compile-time
+    indices; in the half form it reads them before the transfers to B and makes
+    these itself: 21 LDS reads for the 100 ERIs of an [ff|ff] column and node
+    instead of 300, each with an offset to decode, which bound emit_mode_RW.
+    Setups, which wait for memory, are batched wider than factors, which fill LDS.
+    Every product and sum, and its order, is emit_mode_RW's, so the bits are
+    (times: rysc_forms)."""
+    a, b, c, d = cp.a, cp.b, cp.c, cp.d
+    n = cp.n_eriq
+    f32 = real == "float"
+    vb = 4 if f32 else 8
+    half, ket, NL, split, NO, NT, NB, NQB, row = rysc_shape(cp, form, vb)
+    NS = n // (NL * NO)
+    N = cp.Ltot // 2 + 1
+    NQ = 2 * N + 18
+    (l1, l2), (r1, r2) = ((c, d), (a, b)) if ket else ((a, b), (c, d))
+    NI = (l1 + 1) * (l2 + 1) * row
+    nbuf = max(NB * N * 3 * NI, (4 * n + vb - 1) // vb)      # the packed path stages int32 codes over it
+
+    def idx1(t):
+        if half:
+            return (t[1] * (l2 + 1) + t[2]) * row + t[0]
+        lp, rp = ((t[2], t[3]), (t[0], t[1])) if ket else ((t[0], t[1]), (t[2], t[3]))
+        return (lp[0] * (l2 + 1) + lp[1]) * row + rp[0] * (r2 + 1) + rp[1]
+    em = Emitter()
+    flops = [30 + 2 * N * 3 * RYS_DEG + 2 * N]    # setup, the node/weight series, the weights' prefactor
+    em("// class [%d%d|%d%d] computed as shells %s = [%d%d|%d%d], Rys quadrature (%d nodes), a workgroup of %d threads "
+       "per quartet, %d ERIs of a column per thread" % (cp.user + (cp.perm, a, b, c, d, N, NT, NO)))
+    tables = {}
+    for tag, L in (("l1", l1), ("l2", l2)) + (() if split is None else (("rs", r1),)):
+        tables[tag] = "%s_%s" % (name, tag)
+        em("static __constant__ int %s[%d] = {%s};" % (tables[tag], ncart(L), ", ".join(
+            str(x | y << 4 | z << 8) for x, y, z in comps(L))))
+    em("__global__ __launch_bounds__(%d) void %s(eri_class_args A)" % (NT, name))
+    em.block("")
+    em("__shared__ %s s_I[%d];   // [batch][node][axis][1D index]" % (real, nbuf))
+    em("__shared__ double s_q[%d];   // per primitive quartet: nodes, weights, C00/C00' parts, B parts" % (NQB * NQ))
+    em("__shared__ double s_red[%d];" % (NT // 64))
+    em("const int tid = threadIdx.x;")
+    em("const int64_t qi = ERI_BID;")
+    em("if (qi >= A.n_items) return;   // uniform over the workgroup")
+    em("const eri_item it = A.items[qi];")
+    em("const bool sb = it.bra < 0, sk = it.ket < 0;   // pair stored in swapped order")
+    em("const eri_shell_pair BP = A.pairs[it.bra & 0x7fffffff];")
+    em("const eri_shell_pair KP = A.pairs[it.ket & 0x7fffffff];")
+    em("const int nket = KP.nprim;")
+    em("const int npq = BP.nprim * nket;")
+    # the thread's column, and the rows of its factors per axis
+    em("const bool own = tid < %d;" % (NL * NS))
+    em("const int col = own ? tid %% %d : 0, i1 = col / %d, i2 = col %% %d, q1 = own ? tid / %d : 0;"
+       % (NL, ncart(l2), ncart(l2), NL))
+    em("const int p1 = %s[i1], p2 = %s[i2]%s;" % (tables["l1"], tables["l2"],
+                                                 "" if split is None else ", pr = %s[q1]" % tables["rs"]))
+    step = 1 if half else r2 + 1
+    for ax in range(3):
+        em("const int o%s = (((p1 >> %d) & 15) * %d + ((p2 >> %d) & 15)) * %d + %d%s;"
+           % ("xyz"[ax], 4 * ax, l2 + 1, 4 * ax, row, ax * NI,
+              "" if split is None else " + ((pr >> %d) & 15) * %d" % (4 * ax, step)))
+    em("double acc[%d];" % NO)
+    em("#pragma unroll")
+    em("for (int k = 0; k < %d; ++k) acc[k] = 0.0;" % NO)
+    emit_rys_setup(em, cp, real, NT, NQB, "nq")
+    em.block("for (int jj = 0; jj < nq; jj += %d)" % NB)
+    em("const int nb = min(%d, nq - jj);" % NB)
+    emit_rys_factors(em, cp, flops, real, NT, NI, idx1, NI > 64, "(jj + jb)", half)
+    em.block("for (int jb = 0; jb < nb; ++jb)")
+    if f32:
+        em("float t[%d];" % NO)
+        em("#pragma unroll")
+        em("for (int k = 0; k < %d; ++k) t[k] = 0.0f;" % NO)
+    em("#pragma unroll %d" % (N if NO * N <= 64 else 1))
+    em.block("for (int r = 0; r < %d; ++r)" % N)
+    em("const %s* I = s_I + (jb * %d + r) * %d;" % (real, N, 3 * NI))
+    # ERIs of the thread: components of r1, unless threads are split over it, and of r2
+    zero = [(0, 0, 0)]
+    outs = [(u, v) for u in (comps(r1) if split is None else zero) for v in comps(r2)]
+    for ax in range(3):
+        x = "xyz"[ax]
+        if half:
+            top = r1 + r2 if split is None else r2
+            for e in range(top + 1):
+                em("const %s %s%d_0 = I[o%s + %d];" % (real, x, e, x, e))
+            for j in range(1, r2 + 1):
+                for i in range(top + 1 - j):
+                    em("const %s %s%d_%d = %s%d_%d + (%s)BP.AB[%d] * %s%d_%d;" % (real, x, i, j, x, i + 1, j - 1, real, ax, x, i, j - 1))
+        else:
+            for i, j in sorted({(u[ax], v[ax]) for u, v in outs}):
+                em("const %s %s%d_%d = I[o%s + %d];" % (real, x, i, j, x, i * (r2 + 1) + j))
+    dst = "t" if f32 else "acc"
+    for k, (u, v) in enumerate(outs):
+        em("%s[%d] = fma(x%d_%d * y%d_%d, z%d_%d, %s[%d]);" % (dst, k, u[0], v[0], u[1], v[1], u[2], v[2], dst, k))
+    em.end()
+    if f32:
+        em("const double pf = s_q[(jj + jb) * %d + %d];" % (NQ, 2 * N + 17))
+        em("#pragma unroll")
+        em("for (int k = 0; k < %d; ++k) acc[k] = fma((double)t[k], pf, acc[k]);" % NO)
+        flops[0] += 2 * n
+    em.end()
+    em("if (jj + %d < nq) __syncthreads();   // the factors are consumed" % NB)
+    em.end()
+    em.end()
+    flops[0] += 3 * N * n
+    emit_slot(em, "qi")
+    em("const int64_t obase = oslot * %d;" % n)
+    st = user_strides(cp)
+
+    def stride(flag, x, y, same):
+        return "%s ? %d : %d" % (flag, y, x) if same else str(x)
+    em("const int s0 = %s, s1 = %s, s2 = %s, s3 = %s;" % (
+        stride("sb", st[0], st[1], a == b), stride("sb", st[1], st[0], a == b),
+        stride("sk", st[2], st[3], c == d), stride("sk", st[3], st[2], c == d)))
+    sl, sr = (("s2", "s3"), ("s0", "s1")) if ket else (("s0", "s1"), ("s2", "s3"))
+    em("const int ubase = i1 * %s + i2 * %s%s;" % (sl[0], sl[1], "" if split is None else " + q1 * %s" % sr[0]))
+    nr2 = ncart(r2)
+
+    def uix(k):
+        if split is not None:
+            return "ubase + %s * %s" % (k, sr[1])
+        return "ubase + %s / %d * %s + %s %% %d * %s" % (k, nr2, sr[0], k, nr2, sr[1])
+    em("double bmax = 0.0;")
+    em("#pragma unroll")
+    em("for (int k = 0; k < %d; ++k) bmax = own ? fmax(bmax, fabs(acc[k])) : 0.0;" % NO)
+    em.block("if (A.out_eri && own)")
+    for k in range(NO):
+        em("A.out_eri[obase + %s] = acc[%d];" % (uix(k), k))
+    em.end()
+    em.block("if (A.out_codes)")
+    em("for (int o = 32; o > 0; o >>= 1) bmax = fmax(bmax, __shfl_xor(bmax, o));")
+    em("if ((tid & 63) == 0) s_red[tid >> 6] = bmax;")
+    em("__syncthreads();")
+    em("bmax = s_red[0];")
+    em("#pragma unroll")
+    em("for (int w = 1; w < %d; ++w) bmax = fmax(bmax, s_red[w]);" % (NT // 64))
+    em("const double eps = bmax * A.cn;")
+    em("const double inv = eri_inverse_scale(eps);")
+    em("const bool slow = __builtin_isinf(inv);   // uniform")
+    em("if (tid == 0 && A.out_scales) A.out_scales[oslot] = eps;")
+    em.block("if (A.pack_bits)")
+    em("const int wide = A.pack_bits > 16;")
+    em.block("if (own)")
+    for k in range(NO):
+        em("eri_stage_code(s_I, %s, wide, eri_quantize(acc[%d], eps, inv, A.qmax));" % (uix(k), k))
+    em.end()
+    em("__syncthreads();")
+    em("eri_pack_group(s_I, %d, 1, A.pack_bits, A.pack_per, (int)A.pack_wpq, "
+       "reinterpret_cast<uint32_t*>(A.out_codes), gq, A.ring, tid, %d);" % (n, NT))
+    em.end()
+    em.block("else if (own && !slow && A.code_bytes == 2)")
+    for k in range(NO):
+        em("reinterpret_cast<int16_t*>(A.out_codes)[obase + %s] = (int16_t)eri_quantize_mul(acc[%d], inv, A.qmax);"
+           % (uix(k), k))
+    em.end()
+    em.block("else if (own)")
+    em("#pragma unroll")
+    em.block("for (int k = 0; k < %d; ++k)" % NO)
+    em("eri_store_code(A.out_codes, obase + %s, A.code_bytes, eri_quantize(acc[k], eps, inv, A.qmax));" % uix("k"))
+    em.end()
     em.end()
     em.end()
     em.end()
@@ -2250,6 +2503,7 @@ HEADER = """// Generated by codegen.py -- class-specialised ERI kernels.
 TAG_DEFAULT, TAG_ALT, TAG_OCC2, TAG_TWO_WAVES, TAG_SWAP = 0, 1, 2, 3, 4
 TAG_TWO_WAVES_OCC2 = 5
 TAG_TWO_WAVES_XCOL_OCC2 = 6
+TAG_COLUMNS, TAG_COLUMNS_SMALL = 14, 15    # workgroup Rys kernels with a column per thread: default, of small launches
 TAG_PRIM = 13        # primitive-parallel kernel of a small class (chosen by launch size, no tuner variant)
 # workgroup Rys kernels (RYSW_VARIANTS): 7 larger batches; 8, 9 twice the threads at 4 or 2 waves per
 # SIMD; 10, 11, 12 the node loop not unrolled (at 1 and 2 waves per SIMD, and twice the threads at 2)
@@ -2427,6 +2681,13 @@ def generate(outdir, precisions=("fp64",), classes=None, group=8, overrides=None
                 if k == 0:
                     lines_.append("    t[%d] = %s;" % (c5, info))
                 lines_.append("    v[%d] = %s;" % (c5 * MAXVAR + k, info))
+            if cp.Ltot < 2:
+                continue   # (a lane adds [ss|ss]'s and [ps|ss]'s z products unrounded)
+            form = rysc_lane_form(cp)
+            name += "_cs"
+            parts.append(emit_mode_RC(cp, name, form, real)[1])
+            lines_.append("    p[%d] = {(const void*)%s, 1, %d, 1, %d, %d, %d, %d, %d, %d, 0};" % (
+                c5, name, rysc_shape(cp, form)[5], cp.n_eriq, fpq, 3 * cp.n_eriq, pk, TAG_COLUMNS_SMALL, int(real == "float")))
         fname = "eri_register_%s" % rprec
         parts.append("void %s(eri_kernel_info* t, eri_kernel_info* v, eri_kernel_info* p)\n{\n%s\n}\n" % (fname, "\n".join(lines_)))
         fn = os.path.join(outdir, "eri_%s.hip" % rprec)
@@ -2444,11 +2705,27 @@ def generate(outdir, precisions=("fp64",), classes=None, group=8, overrides=None
                 plans[user] = cp
                 pk = cp.perm[0] | (cp.perm[1] << 2) | (cp.perm[2] << 4) | (cp.perm[3] << 6)
                 c5 = class_id5(*user)
-                k = 0
                 vb = 4 if real == "float" else 8
+                large, small = rysc_forms(cp)
+                for form, suffix, tag in ((large, "_c", TAG_COLUMNS), (small, "_cs", TAG_COLUMNS_SMALL)):
+                    if form is None:
+                        continue
+                    name = kernel_name(rprec, cp.user) + suffix
+                    _, src, fpq = emit_mode_RC(cp, name, form, real)
+                    parts.append(src)
+                    info = "{(const void*)%s, 1, %d, 1, %d, %d, %d, %d, %d, %d, 0}" % (
+                        name, rysc_shape(cp, form, vb)[5], cp.n_eriq, fpq, 3 * cp.n_eriq, pk, tag, int(real == "float"))
+                    if form is large and suffix == "_c":
+                        lines_.append("    t[%d] = v[%d] = %s;" % (c5, c5 * MAXVAR, info))
+                    else:
+                        lines_.append("    p[%d] = %s;" % (c5, info))
+                k = 0
                 for suffix, budget, occ, nts, unroll, tag in RYSW_VARIANTS:
                     if budget != RYSW_LDS and rysw_shape(cp, budget, vb) == rysw_shape(cp, RYSW_LDS, vb):
                         continue   # the larger budget changes nothing for this class
+                    if k == 0 and large is not None:
+                        k = 1
+                        continue   # variant 0 is the column kernel
                     name = kernel_name(rprec, cp.user) + suffix
                     _, src, fpq = emit_mode_RW(cp, name, budget, occ, real, nts, unroll)
                     parts.append(src)

@@ -17,7 +17,8 @@ struct eri_kernel_info {
                          // registers (the default of an f-f bra is the two-wavefront x-column form);
                          // workgroup Rys kernels: 7 larger batches of primitive quartets, 8 twice the threads
                          // at 4 waves per SIMD, 9 twice the threads at 2; 10, 11, 12 the node loop not
-                         // unrolled (1 and 2 waves per SIMD, twice the threads at 2); 13 primitive-parallel
+                         // unrolled (1 and 2 waves per SIMD, twice the threads at 2); 13 primitive-parallel;
+                         // 14 Rys columns (default), 15 those of small launches
     int32_t fp32;        // 1: VRR/HRR in FP32 (FP32-mixed kernel); 0: FP64
     int32_t pack_dyn;    // packed stream stages codes in dynamic LDS: 0 never, 1 always, 2 for n > 16
 };
@@ -37,7 +38,9 @@ const eri_kernel_info* eri_kernel_table(int precision);
 #define ERI_MAXVAR 8
 const eri_kernel_info* eri_kernel_variants(int precision);
 
-// Primitive-parallel kernels of the classes that take a lane per quartet
-// (per_block quartets a workgroup for each of its eri_class_args.groups turns;
-// the default kernel's orientation and bits); fn == nullptr for other classes.
+// Kernels that a rule on the launch takes in place of variant 0, with its
+// orientation and bits: primitive-parallel ones of the classes that take a lane
+// per quartet (per_block quartets a workgroup for each of its
+// eri_class_args.groups turns) and of the slot kernels, and the Rys columns of
+// small launches; fn == nullptr for other classes.
 const eri_kernel_info* eri_kernel_prim(int precision);

@@ -136,6 +136,7 @@ struct eri_plan {
     int64_t class_count[256] = {};
     int64_t class_ring[256] = {};
     int64_t class_maxpq[256] = {};   // most primitive quartets of one quartet
+    double class_pq[256] = {};       // primitive quartets of all
     int64_t class_qoff[257] = {};
     int64_t class_eoff[257] = {};
     double class_flops[256] = {};

@@ -338,6 +338,7 @@ static int create_explicit(eri_plan* p, const shell_set& s, const int32_t* quart
         const int64_t npq = (int64_t)pairs[bra[t]].nprim * pairs[ket[t]].nprim;
         p->n_prim_quartets += npq;
         p->class_maxpq[cls[t]] = std::max(p->class_maxpq[cls[t]], npq);
+        p->class_pq[cls[t]] += (double)npq;
         p->class_flops[cls[t]] += (double)npq * tab[class_id5_of(cls[t])].flops_pq + (double)tab[class_id5_of(cls[t])].flops_q;
     }
     p->class_qoff[0] = 0;
@@ -559,6 +560,7 @@ static int create_batched(eri_plan* p, const shell_set& s, const eri_plan_opts* 
                         q += n;
                         const int64_t npq = (int64_t)p->h_pairs[b].nprim * kprim[n];
                         p->class_maxpq[cid] = std::max(p->class_maxpq[cid], npq / n);
+                        p->class_pq[cid] += (double)npq;
                         p->n_prim_quartets += npq;
                         flops += (double)npq * tab[class_id5_of(cid)].flops_pq + (double)n * tab[class_id5_of(cid)].flops_q;
                     }
@@ -820,31 +822,44 @@ static size_t pack_lds(const eri_kernel_info& ki, const eri_class_args& a)
     return (size_t)ki.per_block * ki.n_eriq * (a.pack_bits > 16 ? 4 : 2);
 }
 
+// A launch of n quartets of class c in units of its deepest contraction: what a
+// kernel with an order of its own per quartet takes as long as, at least, is one
+// unit; what one that spreads the primitive quartets takes is their sum.
+static int64_t deep_quartets(const eri_plan* p, int c, int64_t n)
+{
+    if (!p->class_count[c] || !p->class_maxpq[c]) return 0;
+    return (int64_t)std::ceil((double)n * p->class_pq[c] / ((double)p->class_count[c] * (double)p->class_maxpq[c]));
+}
+
 // Whether a class that takes a lane per quartet runs its primitive-parallel
-// kernel for n quartets of up to maxpq primitive quartets.  A lane per quartet
-// walks its contraction in series and reads primitive pairs that lie apart
-// between the lanes; 16 lanes per quartet cost an LDS round trip per turn and
-// leave lanes idle in the HRR.  Measured (us, lane per quartet / 16 lanes, K
-// 1..3 a shell): [ss|ss] 48 / 10 at 1024 quartets, 54 / 33 at 32767, 252 / 143
-// at 524288; [pp|ps] 78 / 18, 86 / 54, 297 / 403; [dp|ps] (48 contracted sums)
-// 110 / 27, 116 / 74, 387 / 860, and at 131072 139 / 220; K = 12, 16384 quartets
-// of [dp|ps]: 29.8 / 12.4 ms.  With K = 1 there is no contraction to
-// split ([dp|ps], 32767 quartets: 17 / 52).
+// kernel for a launch of `deep` deepest contractions of maxpq primitive quartets.
+// A lane per quartet walks its contraction in series and reads primitive pairs
+// that lie apart between the lanes; 16 lanes per quartet cost an LDS round trip
+// per turn and leave lanes idle in the HRR, more of them the more sums a quartet
+// has.  Measured (us, lane per quartet / 16 lanes, K = 3 a shell): [ss|ss] 48 / 11 at
+// 2048 quartets, 80 / 41 at 32768, 105 / 57 at 65000; [pp|ps] (27 contracted sums)
+// 82 / 21, 107 / 75, 138 / 152; [dp|ps] (48) 112 / 29, 141 / 165, 176 / 290, and 119 /
+// 113 at 16384.  With K = 2 a quartet is one turn, 8192 and 16384 quartets: [pp|ps]
+// 26 / 20 and 27 / 30, [dp|ps] 38 / 39 and 40 / 67, at 4096 37 / 24.  With K = 1
+// there is no contraction to split.
 constexpr int ERI_TAG_PRIM = 13;
-constexpr int64_t ERI_PRIM_MAX = 65536;   // classes of more than 32 contracted sums
-static bool prim_better(int c, int64_t n, int64_t maxpq)
+static bool prim_better(int c, int64_t deep, int64_t maxpq)
 {
     auto sums = [](int x, int y) {
         int s = 0;
         for (int l = std::max(x, y); l <= x + y; ++l) s += ncart(l);
         return s;
     };
-    return maxpq >= 4 && (n < ERI_PRIM_MAX || sums(c >> 6, (c >> 4) & 3) * sums((c >> 2) & 3, c & 3) <= 32);
+    const int n = sums(c >> 6, (c >> 4) & 3) * sums((c >> 2) & 3, c & 3);
+    if (maxpq < 4) return false;
+    if (n <= 20) return true;
+    return deep <= (n <= 32 ? 32768 : 16384) / (maxpq <= 16 ? 4 : 1);
 }
 
 // Turns of its workgroups: one while that leaves the chip room (four quartets
 // a wavefront, sixteen wavefronts a CU), else four, which fill the lanes of the
-// HRR and the store better.
+// HRR and the store better (16384 quartets of K = 3, one / four turns: [ss|ss] 21 /
+// 32 us, [dd|ss] 61 / 64, [dp|ps] 113 / 80).
 static int prim_groups(int64_t n) { return n <= 16384 ? 1 : 4; }
 
 // A primitive-parallel kernel with 16 lanes per quartet (one wavefront; those of
@@ -898,6 +913,24 @@ static int orient_items(eri_plan* p, int c, const eri_kernel_info& ki, hipStream
 // Contractions of fewer than 8 primitive quartets have too few turns to gain.
 constexpr int64_t ERI_PRIM_GROUPS = 512;
 
+// Rys classes: deepest contractions up to which the column kernel of small
+// launches runs.  Both forms at 256 / 2048 quartets of K 1..3, a fifth as many
+// deepest ones (us, small / large): [ff|ff] 318 / 498, 671 / 549, [fd|fd] 131 / 196,
+// 266 / 276 where each pair has 60 components and more; [ff|ps] 30 / 53, 52 / 60, [dd|pp]
+// 27 / 43, 35 / 52, [dd|ps] 16 / 25, 20 / 28 elsewhere, and of K = 3 at 512 and 1024
+// [ff|ps] 50 / 55, 121 / 88, [dd|ps] 21 / 28, 29 / 32.  The classes up to L_tot = 4 else
+// take a lane per quartet, which walks its contraction in series: 4096 / 8192 /
+// 16384 quartets of K = 3 [pp|pp] 101 / 273, 173 / 270, 327 / 281, [ds|ss] 37 / 78,
+// 66 / 78, 119 / 89; with one primitive quartet there is nothing to share (256
+// [ds|ps] 10 / 8).
+constexpr int ERI_TAG_COLUMNS_SMALL = 15;
+static int64_t column_quartets(int c, int64_t maxpq)
+{
+    const int a = c >> 6, b = (c >> 4) & 3, k = (c >> 2) & 3, l = c & 3;
+    if (a + b + k + l <= 4) return maxpq >= 4 ? 8192 : 0;
+    return std::min(ncart(a) * ncart(b), ncart(k) * ncart(l)) >= 60 ? 256 : 512;
+}
+
 // Default kernel of a class of the plan for launches of n quartets: a kernel
 // with the bits of variant 0.  Above a chip full of workgroups the
 // half-register forms of the largest kernels, which hold twice as many, are
@@ -916,8 +949,9 @@ static const eri_kernel_info& default_kernel(const eri_plan* p, int c, int64_t n
             if (v[k].fn && v[k].tag == tag) return v[k];
     }
     const eri_kernel_info& prim = eri_kernel_prim(table_index(p->precision))[class_id5_of(c)];
-    const bool better = prim_lanes(prim) ? prim_better(c, n, p->class_maxpq[c])
-                                         : n <= ERI_PRIM_GROUPS * prim.per_block && p->class_maxpq[c] >= 8;
+    const bool better = prim.tag == ERI_TAG_COLUMNS_SMALL ? deep_quartets(p, c, n) <= column_quartets(c, p->class_maxpq[c])
+                        : prim_lanes(prim)                ? prim_better(c, deep_quartets(p, c, n), p->class_maxpq[c])
+                                                          : n <= ERI_PRIM_GROUPS * prim.per_block && p->class_maxpq[c] >= 8;
     return prim.fn && better ? prim : kernel_table(p->precision)[class_id5_of(c)];
 }
 

@@ -378,7 +378,7 @@ class Plan:
 
 # Name suffix of the generated kernel of each variant tag (eri_plan_info.class_tag)
 KERNEL_TAG_SUFFIX = {0: "", 1: "_a", 2: "_o2", 3: "_w2", 4: "_s", 5: "_w2o2", 6: "_w2xo2", 7: "_b", 8: "_w", 9: "_wo2",
-                     10: "_n", 11: "_no2", 12: "_nwo2", 13: "_p"}
+                     10: "_n", 11: "_no2", 12: "_nwo2", 13: "_p", 14: "_c", 15: "_cs"}
 
 
 def _ncart(L):
