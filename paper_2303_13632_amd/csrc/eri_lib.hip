@@ -1,8 +1,7 @@
 // Host side of the ERI library: plan builders (shell-pair / primitive-pair
 // tables, class-sorted work lists, Schwarz-screened batched work over a whole
-// shell set), launches of the generated class kernels (captured in a hipGraph
-// for batched plans), the standalone compression kernels and the C ABI of
-// include/eri.h.
+// shell set), launches of the generated class kernels (side by side on several
+// streams), the standalone compression kernels and the C ABI of include/eri.h.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -841,9 +840,11 @@ static int64_t deep_quartets(const eri_plan* p, int c, int64_t n)
 // 82 / 21, 107 / 75, 138 / 152; [dp|ps] (48) 112 / 29, 141 / 165, 176 / 290, and 119 /
 // 113 at 16384.  With K = 2 a quartet is one turn, 8192 and 16384 quartets: [pp|ps]
 // 26 / 20 and 27 / 30, [dp|ps] 38 / 39 and 40 / 67, at 4096 37 / 24.  With K = 1
-// there is no contraction to split.
+// there is no contraction to split.  In a large screened launch the quartets
+// share their pairs, so a wavefront's lanes read the same or neighbouring ones
+// (48 atoms, K 1..6: 9.7 million [ps|ss] 5.0 / 6.1 ms, 2.6 million [ds|ps] 3.1 / 4.1).
 constexpr int ERI_TAG_PRIM = 13;
-static bool prim_better(int c, int64_t deep, int64_t maxpq)
+static bool prim_better(int c, int64_t deep, int64_t maxpq, bool shared)
 {
     auto sums = [](int x, int y) {
         int s = 0;
@@ -852,7 +853,7 @@ static bool prim_better(int c, int64_t deep, int64_t maxpq)
     };
     const int n = sums(c >> 6, (c >> 4) & 3) * sums((c >> 2) & 3, c & 3);
     if (maxpq < 4) return false;
-    if (n <= 20) return true;
+    if (n <= 20) return !shared || deep <= 65536;
     return deep <= (n <= 32 ? 32768 : 16384) / (maxpq <= 16 ? 4 : 1);
 }
 
@@ -931,6 +932,25 @@ static int64_t column_quartets(int c, int64_t maxpq)
     return std::min(ncart(a) * ncart(b), ncart(k) * ncart(l)) >= 60 ? 256 : 512;
 }
 
+// Slot kernels that have a lane-per-quartet form (up to 144 ERIs): whether it runs
+// for `deep` deepest contractions of maxpq primitive quartets.  A slot's lanes
+// own ket components in the bra transfer, so kets of one or three leave most idle;
+// a lane per quartet needs the chip full of quartets, and more of them the longer
+// its contraction.  Slot / lane at 16384 and 65536 quartets of K = 1 and 16384 and
+// 40000 of K = 3 (us): [ff|ss] 353 / 38, 1360 / 88, 1388 / 213, 3308 / 249, [fd|ss]
+// 105 / 22, 390 / 38, 538 / 129, 1293 / 158, [dd|ps] 57 / 38, 189 / 69, 402 / 236,
+// 969 / 269, [fs|ds] 19 / 22, 50 / 37, 219 / 191, 484 / 232, [pp|pp] 15 / 31, 31 / 60,
+// 116 / 192, 256 / 232; and 4096 of K = 3: [ff|ss] 351 / 202, [fd|ss] 135 / 121, [dd|ps]
+// 113 / 218.
+constexpr int ERI_TAG_ALT = 1;
+static bool lane_better(int c, int64_t deep, int64_t maxpq)
+{
+    const int few = std::min(ncart(c >> 6) * ncart((c >> 4) & 3), ncart((c >> 2) & 3) * ncart(c & 3));
+    if (few == 1) return deep > 4096;
+    if (few == 3) return deep > 14336;
+    return deep > 49152 && maxpq >= 64;
+}
+
 // Default kernel of a class of the plan for launches of n quartets: a kernel
 // with the bits of variant 0.  Above a chip full of workgroups the
 // half-register forms of the largest kernels, which hold twice as many, are
@@ -948,11 +968,17 @@ static const eri_kernel_info& default_kernel(const eri_plan* p, int c, int64_t n
         for (int k = 1; k < ERI_MAXVAR && tag && p->precision <= ERI_FP32_MIXED; ++k)
             if (v[k].fn && v[k].tag == tag) return v[k];
     }
+    const eri_kernel_info& def = kernel_table(p->precision)[class_id5_of(c)];
+    if (p->precision == ERI_FP64 && def.mode == 1 && lane_better(c, deep_quartets(p, c, n), p->class_maxpq[c])) {
+        const eri_kernel_info* v = eri_kernel_variants(table_index(p->precision)) + (int64_t)class_id5_of(c) * ERI_MAXVAR;
+        for (int k = 1; k < ERI_MAXVAR; ++k)
+            if (v[k].fn && v[k].tag == ERI_TAG_ALT && v[k].mode == 0) return v[k];
+    }
     const eri_kernel_info& prim = eri_kernel_prim(table_index(p->precision))[class_id5_of(c)];
     const bool better = prim.tag == ERI_TAG_COLUMNS_SMALL ? deep_quartets(p, c, n) <= column_quartets(c, p->class_maxpq[c])
-                        : prim_lanes(prim)                ? prim_better(c, deep_quartets(p, c, n), p->class_maxpq[c])
+                        : prim_lanes(prim)                ? prim_better(c, deep_quartets(p, c, n), p->class_maxpq[c], p->batched)
                                                           : n <= ERI_PRIM_GROUPS * prim.per_block && p->class_maxpq[c] >= 8;
-    return prim.fn && better ? prim : kernel_table(p->precision)[class_id5_of(c)];
+    return prim.fn && better ? prim : def;
 }
 
 // Kernel of a class launch: the autotuner's variant, else the default.

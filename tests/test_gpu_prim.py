@@ -58,3 +58,19 @@ def test_slot_classes(L):
     for n, k in ((1, 16), (3, 5), (2, 2), (17, 0), (257, 0)):
         _compare(L, n, k)
     _compare(L, 19, 0, forms=((3, True), (8, True), (12, True), (24, True), (8, False), (32, False)))
+
+
+@pytest.mark.parametrize("L,n,k", [((3, 3, 0, 0), 4097, 1), ((0, 0, 2, 3), 4097, 2), ((2, 2, 1, 0), 14337, 1),
+                                   ((0, 1, 1, 3), 14337, 2), ((1, 1, 2, 0), 49153, 3)])
+def test_lanes_of_large_launches(L, n, k):
+    """Above the rule's size a class with a lane-per-quartet form takes it: the values
+    are those of the slot kernels, bit for bit."""
+    cid = W.class_id(*L)
+    shells, quartets = W.random_class_quartets(*L, n, n + cid, k_fixed=k)
+    values = []
+    for q in (quartets, quartets[: n - 1]):
+        plan = eri.Plan(shells, q, bits=16)
+        tag, out = _outputs(plan, cid, 0)
+        assert (tag == 1) == (len(q) == n)
+        values.append(plan.to_user(out[0].cpu().numpy()[: plan.n_eri]))
+    assert np.array_equal(values[0][: len(values[1])], values[1])
