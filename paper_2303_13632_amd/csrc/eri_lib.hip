@@ -912,7 +912,14 @@ static int orient_items(eri_plan* p, int c, const eri_kernel_info& ki, hipStream
 // [dp|dp] 75 / 42, [dd|dd] 128 / 76, [fd|fd] 234 / 117); at 1024 quartets the two
 // are equal for [dd|dd] and [fd|fd], and beyond that the exchange is only a cost.
 // Contractions of fewer than 8 primitive quartets have too few turns to gain.
-constexpr int64_t ERI_PRIM_GROUPS = 512;
+// Where all are deep, a workgroup a CU is the limit: the largest of these kernels
+// hold one wavefront per SIMD (256 and 403 quartets of K = 5: [dd|dd] 957 / 524 and
+// 1005 / 1005, [dp|fp] 493 / 291 and 524 / 569, [fp|fp] 807 / 499 and 864 / 965).
+constexpr int64_t ERI_PRIM_GROUPS = 512, ERI_PRIM_DEEP_GROUPS = 256;
+static bool waves_better(const eri_kernel_info& prim, int64_t n, int64_t deep, int64_t maxpq)
+{
+    return n <= ERI_PRIM_GROUPS * prim.per_block && deep <= ERI_PRIM_DEEP_GROUPS * prim.per_block && maxpq >= 8;
+}
 
 // Rys classes: deepest contractions up to which the column kernel of small
 // launches runs.  Both forms at 256 / 2048 quartets of K 1..3, a fifth as many
@@ -977,7 +984,7 @@ static const eri_kernel_info& default_kernel(const eri_plan* p, int c, int64_t n
     const eri_kernel_info& prim = eri_kernel_prim(table_index(p->precision))[class_id5_of(c)];
     const bool better = prim.tag == ERI_TAG_COLUMNS_SMALL ? deep_quartets(p, c, n) <= column_quartets(c, p->class_maxpq[c])
                         : prim_lanes(prim)                ? prim_better(c, deep_quartets(p, c, n), p->class_maxpq[c], p->batched)
-                                                          : n <= ERI_PRIM_GROUPS * prim.per_block && p->class_maxpq[c] >= 8;
+                                                          : waves_better(prim, n, deep_quartets(p, c, n), p->class_maxpq[c]);
     return prim.fn && better ? prim : def;
 }
 
