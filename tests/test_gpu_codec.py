@@ -1,6 +1,6 @@
 """Standalone compress / decompress at the edges of their work split: blocks
 around one group of four values, around the size that one wavefront takes
-(1024), around what a workgroup holds in registers (10240), empty blocks, and
+(2556), around what a workgroup holds in registers (10240), empty blocks, and
 arrays whose base is not aligned to a group."""
 import numpy as np
 import pytest
@@ -11,8 +11,8 @@ from paper_2303_13632_amd import eri
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-EDGES = [1, 0, 2, 3, 4, 5, 7, 255, 256, 257, 1020, 1023, 1024, 1025, 1027, 3600, 10000, 10236, 10239, 10240, 10241,
-         10243, 20001, 1, 1, 0]
+EDGES = [1, 0, 2, 3, 4, 5, 7, 255, 256, 257, 1020, 1023, 1024, 1025, 1027, 2553, 2555, 2556,
+         2557, 2559, 2560, 3600, 10000, 10236, 10239, 10240, 10241, 10243, 20001, 1, 1, 0]
 
 
 @pytest.mark.parametrize("bits", [2, 8, 9, 16, 17, 32])
