@@ -354,9 +354,11 @@ int eri_unpack_host(int32_t bits, const void* packed, int64_t n_blocks, const in
  * host, the layout of eri_plan_create) of the plan's shell set, keeping its
  * quartet set, its orientation choices and, for ERI_PLAN_ALL_QUARTETS plans,
  * its Schwarz screening as they were decided at creation.  The pair tables
- * (eq. 3 Gaussian products) are recomputed and uploaded (synchronous); the
- * next eri_compute / eri_backward uses the new geometry.  This is what a
- * geometry step or a finite-difference probe of the same quartet set needs.
+ * (eq. 3 Gaussian products) are recomputed and uploaded (synchronous, once all
+ * work on the device is done: calls of the plan that are still in flight, on
+ * any stream, run on the old geometry); the next eri_compute / eri_backward uses
+ * the new one.  This is what a geometry step or a finite-difference probe of the
+ * same quartet set needs.
  * Either pointer may be NULL (that part unchanged), not both.
  * ERI_EINVAL for a non-positive exponent (checked first: nothing changes),
  * ERI_EHIP on upload failure. */

@@ -1911,6 +1911,17 @@ extern "C" int eri_plan_set_geometry(eri_plan* p, const double* xyz, const doubl
     int cur = 0;
     ERI_HIP_TRY(hipGetDevice(&cur));
     if (cur != p->device) ERI_HIP_TRY(hipSetDevice(p->device));
+    // The tables are overwritten in place, by copies that the null stream orders
+    // behind the device's ordinary streams but not behind non-blocking ones, nor
+    // behind a graph replayed on one; eri_compute and eri_backward return with
+    // their launches still to run.  So the device finishes first, whichever
+    // streams the plan was used on.
+    const hipError_t idle = hipDeviceSynchronize();
+    if (idle != hipSuccess) {
+        g_last_hip = (int)idle;
+        if (cur != p->device) (void)hipSetDevice(cur);
+        return ERI_EHIP;
+    }
     int rc = ERI_OK;
     try {
         if (xyz) std::copy(xyz, xyz + 3 * ns, p->sh_xyz.begin());

@@ -1,0 +1,72 @@
+"""Calls of one plan that follow each other without a synchronisation: each
+gives what it gives alone, on whichever streams they are."""
+import numpy as np
+import pytest
+
+from paper_2303_13632_amd import eri, workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+DELAY = 20_000_000     # cycles that keep a stream busy: some milliseconds
+
+
+def _list_shells(n=40, seed=5):
+    return W.random_shells(10, lmax=2, seed=seed, box=3.0), \
+        np.random.default_rng(seed).integers(0, 10, size=(n, 4)).astype(np.int32)
+
+
+def _plan(kind):
+    if kind == "screened":
+        return eri.Plan(W.molecule_basis(n_heavy=1, n_h=3, lattice=(2, 2, 1), seed=9), None, bits=0)
+    if kind == "long class":
+        return eri.Plan(*W.random_class_quartets(1, 0, 0, 0, 2500, 6, k_choices=(1, 2)), bits=0)
+    return eri.Plan(*_list_shells(), bits=0)
+
+
+def _call(plan, kind, seed):
+    """A closure that makes one pass on the current stream and returns its outputs."""
+    rng = np.random.default_rng(seed)
+    if kind == "screened":
+        D = torch.tensor(W.random_density(plan.nbf, seed=seed), device="cuda")
+        return lambda: plan.backward(density=D)
+    if kind == "values":
+        def values():
+            out = plan.alloc(codes=False)[0].zero_()
+            plan.compute(out)
+            return (out,)
+        return values
+    dl = torch.tensor(rng.uniform(-1.0, 1.0, plan.out_values), device="cuda")
+    return lambda: plan.backward(dl=dl)
+
+
+def _near(got, ref):
+    for g, r in zip(got, ref):
+        assert (g - r).abs().max().item() <= 1e-11 * r.abs().max().item()
+
+
+@pytest.mark.parametrize("kind", ["list", "screened", "long class", "values"])
+def test_set_geometry_behind_the_calls_in_flight(kind):
+    """set_geometry after a call on a stream of its own that has not run yet:
+    the call is of the old geometry, the next one of the new."""
+    plan = _plan(kind)
+    call = _call(plan, kind, 3)
+    x0 = np.asarray(plan.shells["xyz"]).copy()
+    x1 = x0 + np.random.default_rng(4).uniform(-0.2, 0.2, x0.shape)
+    refs = []
+    for x in (x0, x1):
+        plan.set_geometry(xyz=x)
+        refs.append(call())
+        torch.cuda.synchronize()
+    assert (refs[0][0] - refs[1][0]).abs().max().item() > 1e-3 * refs[0][0].abs().max().item()
+    plan.set_geometry(xyz=x0)
+    stream = torch.cuda.Stream()
+    got = []
+    with torch.cuda.stream(stream):
+        for x in (x1, x0, x1):
+            torch.cuda._sleep(DELAY)
+            got.append(call())
+            plan.set_geometry(xyz=x)
+    stream.synchronize()
+    for g, r in zip(got, (refs[0], refs[1], refs[0])):
+        _near(g, r)
