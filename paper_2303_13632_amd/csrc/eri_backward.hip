@@ -867,22 +867,11 @@ int run_class(eri_plan* p, eri_bwd_state* st, int c, hipStream_t strm, const bwd
 
 }  // namespace
 
-extern "C" int eri_backward(eri_plan* p, void* stream, const double* dl_deri, const double* density, int64_t nbf,
-                            double* grad_centers, double* grad_exps, double* energy)
+// The call on the plan's device, its arguments checked.
+static int backward_on(eri_plan* p, hipStream_t strm, const double* dl_deri, const double* density, int64_t nbf,
+                       double* grad_centers, double* grad_exps, double* energy)
 {
-    if (!p || (grad_centers == nullptr) != (grad_exps == nullptr)) return ERI_EINVAL;
-    if (!grad_centers && !energy) return ERI_EINVAL;
-    if ((dl_deri == nullptr) == (density == nullptr)) return ERI_EINVAL;
-    for (int32_t l : p->sh_L)
-        if (l > BWD_MAXL) return ERI_EUNSUPPORTED;
-    if (dl_deri && p->batched)
-        for (int c = 0; c < 256; ++c)
-            if (p->class_ring[c] != p->class_count[c]) return ERI_ESTATE;
-    int cur = 0;
-    ERI_HIP_TRY(hipGetDevice(&cur));
-    if (cur != p->device) ERI_HIP_TRY(hipSetDevice(p->device));
     int rc = ERI_OK;
-    hipStream_t strm = (hipStream_t)stream;
     bool listed = false, other = false;
     for (int c = 0; c < 256; ++c) {
         listed = listed || adj_listed(p, c);
@@ -896,10 +885,7 @@ extern "C" int eri_backward(eri_plan* p, void* stream, const double* dl_deri, co
         // classes of few quartets: all in one launch
         rc = eri_adj_backward(p, strm, dl_deri, density, nbf, grad_centers, grad_exps, energy);
     }
-    if (rc != ERI_OK || !other) {
-        if (cur != p->device) (void)hipSetDevice(cur);
-        return rc;
-    }
+    if (rc != ERI_OK || !other) return rc;
     if (p->bwd && grad_centers && !p->bwd->full) {
         eri_bwd_free(p->bwd);
         p->bwd = nullptr;
@@ -934,6 +920,30 @@ extern "C" int eri_backward(eri_plan* p, void* stream, const double* dl_deri, co
     if (rc == ERI_OK && energy) {
         hipLaunchKernelGGL(eri_bwd_energy_out_kernel, dim3(1), dim3(64), 0, strm, st->d_eacc, energy);
         if (hipGetLastError() != hipSuccess) rc = ERI_EHIP;
+    }
+    return rc;
+}
+
+extern "C" int eri_backward(eri_plan* p, void* stream, const double* dl_deri, const double* density, int64_t nbf,
+                            double* grad_centers, double* grad_exps, double* energy)
+{
+    if (!p || (grad_centers == nullptr) != (grad_exps == nullptr)) return ERI_EINVAL;
+    if (!grad_centers && !energy) return ERI_EINVAL;
+    if ((dl_deri == nullptr) == (density == nullptr)) return ERI_EINVAL;
+    for (int32_t l : p->sh_L)
+        if (l > BWD_MAXL) return ERI_EUNSUPPORTED;
+    if (dl_deri && p->batched)
+        for (int c = 0; c < 256; ++c)
+            if (p->class_ring[c] != p->class_count[c]) return ERI_ESTATE;
+    int cur = 0;
+    ERI_HIP_TRY(hipGetDevice(&cur));
+    if (cur != p->device) ERI_HIP_TRY(hipSetDevice(p->device));
+    hipStream_t strm = (hipStream_t)stream;
+    int rc = plan_enter(p, strm);
+    if (rc == ERI_OK) {
+        rc = backward_on(p, strm, dl_deri, density, nbf, grad_centers, grad_exps, energy);
+        const int left = plan_leave(p, strm);
+        if (rc == ERI_OK) rc = left;
     }
     if (cur != p->device) (void)hipSetDevice(cur);
     return rc;

@@ -172,7 +172,16 @@ struct eri_plan {
     eri_bwd_state* bwd = nullptr;
     eri_coul_state* coul = nullptr;
     eri_adj_state* adj = nullptr;
+    hipEvent_t turn = nullptr;          // behind the last call that used the plan's buffers (plan_enter)
 };
+
+// Calls that use buffers which the plan holds (items of a screened plan, staging
+// of scale blocks, the adjoint's workspaces) take turns on the device: between
+// plan_enter and plan_leave, `st` runs behind the last such call, whichever
+// stream that was on.  A captured call takes no part: its replays are the
+// program's to order.
+int plan_enter(eri_plan* p, hipStream_t st);
+int plan_leave(eri_plan* p, hipStream_t st);
 
 // The density form of eri_backward for screened plans (eri_coulomb.hip).
 int eri_coul_backward(eri_plan* p, hipStream_t strm, const double* density, int64_t nbf, double* grad_c, double* grad_e,

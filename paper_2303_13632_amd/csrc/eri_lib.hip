@@ -233,6 +233,36 @@ static side_set* side_take(eri_plan* p, hipStream_t st)
     return &s;
 }
 
+// Whether a call on `st` is being captured into a graph.
+static bool is_capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+int plan_enter(eri_plan* p, hipStream_t st)
+{
+    if (p->turn && !is_capturing(st)) ERI_HIP_TRY(hipStreamWaitEvent(st, p->turn, 0));
+    return ERI_OK;
+}
+
+int plan_leave(eri_plan* p, hipStream_t st)
+{
+    if (is_capturing(st)) return ERI_OK;
+    if (!p->turn) ERI_HIP_TRY(hipEventCreateWithFlags(&p->turn, hipEventDisableTiming));
+    ERI_HIP_TRY(hipEventRecord(p->turn, st));
+    return ERI_OK;
+}
+
+// Whether eri_compute's work uses buffers of the plan: items of a screened
+// plan, or the values of scale blocks over several quartets.
+static bool uses_buffers(const eri_plan* p, const double* out_eri, const void* out_codes)
+{
+    return p->batched || (p->scale_block > 1 && out_codes && !out_eri);
+}
+
 static void plan_free(eri_plan* p)
 {
     if (!p) return;
@@ -248,6 +278,7 @@ static void plan_free(eri_plan* p)
     if (p->bwd) eri_bwd_free(p->bwd);
     if (p->coul) eri_coul_free(p->coul);
     if (p->adj) eri_adj_free(p->adj);
+    if (p->turn) (void)hipEventDestroy(p->turn);
     if (cur != p->device) (void)hipSetDevice(cur);
     delete p;
 }
@@ -1155,23 +1186,18 @@ static int launch_all(eri_plan* p, hipStream_t st, side_set* side, double* out_e
     return ERI_OK;
 }
 
-// A call that is being captured keeps to the caller's stream.
-static bool is_capturing(hipStream_t st)
-{
-    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return true;
-}
-
 static int compute_on(eri_plan* p, hipStream_t st, double* out_eri, void* out_codes, double* out_scales)
 {
+    const bool turn = uses_buffers(p, out_eri, out_codes);
+    if (turn) ERI_TRY(plan_enter(p, st));
     int classes = 0;
     for (int c = 0; c < 256; ++c) classes += p->class_count[c] > 0;
+    // a call that is being captured keeps to the caller's stream
     side_set* side = classes > 1 && !is_capturing(st) ? side_take(p, st) : nullptr;
     const int rc = launch_all(p, st, side, out_eri, out_codes, out_scales);
     if (side) side->mu.unlock();
-    return rc;
+    const int left = turn ? plan_leave(p, st) : ERI_OK;
+    return rc != ERI_OK ? rc : left;
 }
 
 extern "C" int eri_compute(eri_plan* p, void* stream, double* out_eri, void* out_codes, double* out_scales)
@@ -1222,10 +1248,15 @@ extern "C" int eri_compute_noalloc(eri_plan* p, void* stream, double* out_eri, v
     int cur = 0;
     ERI_HIP_TRY(hipGetDevice(&cur));
     if (cur != p->device) ERI_HIP_TRY(hipSetDevice(p->device));
+    // (a screened plan's items go to the array here, so its own buffer is not used)
+    const bool turn = !p->batched && uses_buffers(p, out_eri, out_codes);
     eri_item* items = nullptr;
     if (p->batched) rc = scratch_items(p->device, &items);
+    if (turn) rc = plan_enter(p, (hipStream_t)stream);
     for (int c = 0; c < 256 && rc == ERI_OK; ++c)
         rc = launch_class(p, c, (hipStream_t)stream, out_eri, out_codes, out_scales, items, ERI_NOALLOC_MAX_ITEMS);
+    const int left = turn ? plan_leave(p, (hipStream_t)stream) : ERI_OK;
+    if (rc == ERI_OK) rc = left;
     if (cur != p->device) (void)hipSetDevice(cur);
     return rc;
 }
@@ -1239,7 +1270,13 @@ extern "C" int eri_compute_class(eri_plan* p, int32_t c, void* stream, double* o
     int cur = 0;
     ERI_HIP_TRY(hipGetDevice(&cur));
     if (cur != p->device) ERI_HIP_TRY(hipSetDevice(p->device));
-    rc = launch_class(p, c, (hipStream_t)stream, out_eri, out_codes, out_scales);
+    const bool turn = uses_buffers(p, out_eri, out_codes);
+    if (turn) rc = plan_enter(p, (hipStream_t)stream);
+    if (rc == ERI_OK) {
+        rc = launch_class(p, c, (hipStream_t)stream, out_eri, out_codes, out_scales);
+        const int left = turn ? plan_leave(p, (hipStream_t)stream) : ERI_OK;
+        if (rc == ERI_OK) rc = left;
+    }
     if (cur != p->device) (void)hipSetDevice(cur);
     return rc;
 }
@@ -1412,9 +1449,9 @@ extern "C" int eri_plan_tune(eri_plan* p, void* stream, int64_t sample_quartets,
     int cur = 0;
     ERI_HIP_TRY(hipGetDevice(&cur));
     if (cur != p->device) ERI_HIP_TRY(hipSetDevice(p->device));
-    int rc;
+    int rc = plan_enter(p, (hipStream_t)stream);   // (it ends with the stream synchronised)
     try {
-        rc = tune_plan(p, (hipStream_t)stream, sample_quartets, trials, cache_path);
+        if (rc == ERI_OK) rc = tune_plan(p, (hipStream_t)stream, sample_quartets, trials, cache_path);
     } catch (const std::bad_alloc&) {
         rc = ERI_ENOMEM;
     }

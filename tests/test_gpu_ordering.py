@@ -70,3 +70,49 @@ def test_set_geometry_behind_the_calls_in_flight(kind):
     stream.synchronize()
     for g, r in zip(got, (refs[0], refs[1], refs[0])):
         _near(g, r)
+
+
+@pytest.mark.parametrize("kind", ["list", "screened", "long class"])
+def test_backward_on_two_streams(kind):
+    """The adjoint's workspaces belong to the plan: calls on different streams take turns."""
+    plan = _plan(kind)
+    calls = [_call(plan, kind, s) for s in (11, 12)]
+    refs = []
+    for call in calls:
+        refs.append(call())
+        torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    got = []
+    for i in range(8):
+        with torch.cuda.stream(streams[i % 2]):
+            got.append(calls[i % 2]())
+    torch.cuda.synchronize()
+    for i, g in enumerate(got):
+        _near(g, refs[i % 2])
+        assert torch.equal(g[2], refs[i % 2][2])
+
+
+@pytest.mark.parametrize("form", ["screened", "scale blocks"])
+def test_compute_on_two_streams(form):
+    """Quartet items of a screened plan and staged values of scale blocks likewise."""
+    if form == "screened":
+        plan = eri.Plan(W.molecule_basis(n_heavy=2, n_h=4, lattice=(3, 2, 1), seed=13), None, bits=16, chunk_quartets=3000)
+    else:
+        plan = eri.Plan(*W.merge([W.random_class_quartets(*W.class_of(c), 300, c) for c in (0, 85, 98, 170)]), bits=16,
+                        scale_block=5)
+    ref = [t.zero_() for t in plan.alloc(eri=False)[1:]]
+    plan.compute(None, *ref)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    outs = [[t.zero_() for t in plan.alloc(eri=False)[1:]] for _ in range(6)]
+    torch.cuda.synchronize()
+    for i, out in enumerate(outs):
+        with torch.cuda.stream(streams[i % 2]):
+            plan.compute(None, *out)
+            if form == "screened":
+                plan.compute_class(0, None, *out)
+            else:
+                plan.compute_noalloc(None, *out)
+    torch.cuda.synchronize()
+    for out in outs:
+        assert all(torch.equal(o, r) for o, r in zip(out, ref))
