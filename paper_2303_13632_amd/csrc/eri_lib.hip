@@ -219,9 +219,14 @@ static side_set* side_take(eri_plan* p, hipStream_t st)
     if (!s.mu.try_lock()) return nullptr;
     hipError_t e = hipSuccess;
     bool busy = false;
+    // Making streams and asking for an event spoil a capture of another stream,
+    // unless this thread says that they have no part in it.
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool asked = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     if (!s.made) e = side_make(s);
     if (e == hipSuccess && s.used && s.last != st)
         for (int k = 0; k < ERI_SIDE_STREAMS && !busy; ++k) busy = hipEventQuery(s.join[k]) != hipSuccess;
+    if (asked) (void)hipThreadExchangeStreamCaptureMode(&mode);
     if (e != hipSuccess || busy) {
         (void)hipGetLastError();
         if (!s.made) side_clear(s);
@@ -244,15 +249,13 @@ static bool is_capturing(hipStream_t st)
 
 int plan_enter(eri_plan* p, hipStream_t st)
 {
-    if (p->turn && !is_capturing(st)) ERI_HIP_TRY(hipStreamWaitEvent(st, p->turn, 0));
+    if (!is_capturing(st)) ERI_HIP_TRY(hipStreamWaitEvent(st, p->turn, 0));
     return ERI_OK;
 }
 
 int plan_leave(eri_plan* p, hipStream_t st)
 {
-    if (is_capturing(st)) return ERI_OK;
-    if (!p->turn) ERI_HIP_TRY(hipEventCreateWithFlags(&p->turn, hipEventDisableTiming));
-    ERI_HIP_TRY(hipEventRecord(p->turn, st));
+    if (!is_capturing(st)) ERI_HIP_TRY(hipEventRecord(p->turn, st));
     return ERI_OK;
 }
 
@@ -693,8 +696,10 @@ extern "C" int eri_plan_create(eri_plan** out, int64_t n_shells, const int32_t* 
     int cur = 0;
     hipError_t e = hipGetDevice(&cur);
     if (e == hipSuccess && cur != p->device) e = hipSetDevice(p->device);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&p->turn, hipEventDisableTiming);
     if (e != hipSuccess) {
         g_last_hip = (int)e;
+        if (cur != p->device) (void)hipSetDevice(cur);
         delete p;
         return ERI_EHIP;
     }

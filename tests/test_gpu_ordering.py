@@ -116,3 +116,38 @@ def test_compute_on_two_streams(form):
     torch.cuda.synchronize()
     for out in outs:
         assert all(torch.equal(o, r) for o, r in zip(out, ref))
+
+
+def _many_classes(seed):
+    return eri.Plan(*W.merge([W.random_class_quartets(*W.class_of(c), 60, seed * 1000 + c) for c in range(0, 256, 5)]), bits=16)
+
+
+@pytest.mark.parametrize("form", ["list", "screened"])
+def test_beside_a_capture(form):
+    """While a stream is being captured (in the mode that forbids the whole
+    process unsafe calls), calls on other streams leave the capture whole."""
+    plan = _many_classes(1)
+    other = _many_classes(2) if form == "list" else \
+        eri.Plan(W.molecule_basis(n_heavy=2, n_h=4, lattice=(3, 2, 1), seed=17), None, bits=16)
+    refs = []
+    for p in (plan, other):
+        out = [t.zero_() for t in p.alloc()]
+        p.compute_noalloc(*out)          # class after class: the side streams are still to be made or free
+        torch.cuda.synchronize()
+        refs.append(out)
+    out, out2 = ([t.zero_() for t in p.alloc()] for p in (plan, other))
+    busy, aside = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode="global"):
+        plan.compute(*out)
+        for stream in (busy, aside, busy):
+            other.compute(*out2, stream=stream)
+    for t in out:
+        t.zero_()
+    torch.cuda.synchronize()
+    for _ in range(2):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(o, r) for o, r in zip(out, refs[0]))
+    assert all(torch.equal(o, r) for o, r in zip(out2, refs[1]))
