@@ -33,6 +33,9 @@ def emit_kernel(lt, ls, grad):
     """Each lane holds one target primitive pair; the wavefront walks the
     source pairs of its job, whose record (exponent, centre, signed Hermite
     coefficients) is the same for every lane: scalar loads and scalar operands.
+    A lane skips the sources outside its target's range: a factor of zero would
+    carry an infinite or NaN charge of a pair that the target shares no quartet
+    with into its potential.
     R is built along z for each (x, y), along y for each x, then x, so that
     besides V only three pairs of columns are live, and every R_k at m = 0 is
     used for all t + t' = k at once.  The potentials of orders up to LT are
@@ -72,12 +75,13 @@ def emit_kernel(lt, ls, grad):
             em("    double V%d = 0.0;" % k)
     em("    double e_hi = 0.0, e_lo = 0.0;")
     em("    for (int j = job.lo; j < job.hi; ++j) {")
+    em("        if (j < lo || j >= hi) continue;")
     em("        const double* __restrict__ sr = A.rec + job.srec + (int64_t)(j - job.s0) * %d;" % (4 + len(S)))
     em("        const double q = sr[0];")
     em("        const double X = Px - sr[1], Y = Py - sr[2], Z = Pz - sr[3];")
     em("        const double ir = eri_coul_rsqrt(p + q);")
     em("        const double rho = p * q * ir * ir;")
-    em("        const double pref = j >= lo && j < hi ? ERI_TWO_PI_52 * ir : 0.0;")
+    em("        const double pref = ERI_TWO_PI_52 * ir;")
     em("        double F[%d];" % (N + 1))
     em("        eri_boys_lds<%d>(rho * fma(X, X, fma(Y, Y, Z * Z)), F, s_boys);" % N)
     em("        const double b = -2.0 * rho;")

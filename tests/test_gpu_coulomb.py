@@ -89,3 +89,29 @@ def test_many_targets():
     lhs = float((gc * np.asarray(sh["xyz"])).sum() - 2.0 * (ge * sh["exps"]).sum())
     size = np.abs(gc * np.asarray(sh["xyz"])).sum() + 2.0 * np.abs(ge * sh["exps"]).sum()
     assert abs(lhs + E) <= 1e-10 * size
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+@pytest.mark.parametrize("ls", [(0, 0, 0), (1, 0, 2), (2, 2, 2)])
+def test_density_of_pairs_without_a_common_quartet(ls, value):
+    """Of a strong shell a and weak shells e and c the plan keeps (aa|aa),
+    (ae|aa) and (ac|aa): what the density holds for the pair ae does not reach
+    the gradient of c."""
+    from paper_2303_13632_amd import eri
+    sh = _shells(ls, [3, 2, 2], 91, 1.0)
+    sh["exps"][:] = [0.8, 1.3, 2.1, 0.9, 1.7, 1.1, 1.4]
+    sh["coefs"][:] = [1.0, 0.5, 0.7, 1e-5, 1e-5, 1e-5, 1e-5]
+    plan = eri.Plan(sh, None, bits=0, schwarz=1e-7)
+    q = np.concatenate([plan.class_quartet_list(c) for c in range(256) if plan.class_quartets[c]])
+    have = {tuple(sorted((tuple(sorted(x[:2])), tuple(sorted(x[2:]))))) for x in q.tolist()}
+    aa, ae, ac = (0, 0), (0, 1), (0, 2)
+    assert have == {(aa, aa), (aa, ae), (aa, ac)}
+    n = [W.ncart(l) for l in ls]
+    D = W.random_density(plan.nbf, seed=92)
+    ref = plan.backward(density=torch.tensor(D, device="cuda"))[:2]
+    D[:n[0], n[0]:n[0] + n[1]] = value
+    D[n[0]:n[0] + n[1], :n[0]] = value
+    got = plan.backward(density=torch.tensor(D, device="cuda"))[:2]
+    for g, r in zip((got[0][2], got[1][5:]), (ref[0][2], ref[1][5:])):
+        assert (g - r).abs().max().item() <= 1e-12 * r.abs().max().item()
+    assert not torch.isfinite(got[0][1]).any()
