@@ -297,11 +297,14 @@ int eri_decompress(int32_t bits, const void* codes, const double* scales, int64_
  * order), so the summation order (and the last bits of the gradients) may vary
  * between calls; L is summed in a fixed order with compensated (two-sum)
  * arithmetic, so *energy is the same on every call with the same inputs.
- * Device memory held for it: with Hermite potentials, up to 165 doubles per
- * primitive pair, 56 bytes per job and 32 MB of slices; otherwise the derived
- * pair tables, item buffers of up to 2^22 quartets per pass, the contraction
- * maps, the slices (at most 128 MB) and, for a density, up to 1 GiB of
- * D_ab D_cd rows per pass.
+ * Device memory held for it: with Hermite potentials, up to 123 doubles and
+ * 4 bytes per primitive pair, 72 bytes per job (at most 64 target against 8 to
+ * 8192 source primitive pairs), 8 bytes per pair list entry and slices of at
+ * most 32 MB; for classes in one launch 8 bytes per quartet of the plan, 36
+ * per workgroup and slices of at most 32 MB; otherwise the derived pair tables, item
+ * buffers of up to 2^22 quartets per pass, the contraction maps, the slices (at
+ * most 128 MB) and, for a density, up to 1 GiB of D_ab D_cd rows per pass.
+ * Slices are at least one copy of the gradient.
  * Returns ERI_EUNSUPPORTED when a shell of the plan has L > 2 (the exponent
  * derivative of an L shell needs L+2 integrals, computed up to g),
  * ERI_ESTATE for dl_deri with a plan whose output ring holds fewer quartets

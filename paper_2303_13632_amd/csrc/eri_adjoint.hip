@@ -37,7 +37,8 @@ namespace {
 
 constexpr int ADJ_IB = 8;           // target primitive pairs whose Boys values are staged together
 constexpr int64_t ADJ_WORK = 4096;  // workgroups aimed at (16 a CU)
-constexpr int ADJ_SLICES = 64;
+constexpr int ADJ_SLICES_MAX = 64;
+constexpr int64_t ADJ_SLICE_DOUBLES = (int64_t)1 << 22;   // gradient slices in all (32 MB; they span every shell of the plan)
 
 // One class of the list.
 struct adj_class {
@@ -453,6 +454,7 @@ struct eri_adj_state {
     double* d_energy = nullptr;
     double* d_part = nullptr;
     int64_t nbf = 0, n_grad = 0;
+    int n_slices = 1;
 };
 
 void eri_adj_free(eri_adj_state* s)
@@ -556,13 +558,14 @@ static int adj_build(eri_plan* p, eri_adj_state* st)
     for (int64_t s = 0; s < ns; ++s) bf[s + 1] = bf[s] + ncart(p->sh_L[s]);
     st->nbf = bf[ns];
     st->n_grad = 3 * ns + (int64_t)p->sh_exps.size();
+    st->n_slices = (int)std::max<int64_t>(1, std::min<int64_t>(ADJ_SLICES_MAX, ADJ_SLICE_DOUBLES / std::max<int64_t>(1, st->n_grad)));
     ERI_TRY(upload(p, (void**)&st->d_items, items.empty() ? nullptr : items.data(), items.size() * sizeof(eri_item)));
     ERI_TRY(upload(p, (void**)&st->d_cls, cls.empty() ? nullptr : cls.data(), cls.size() * sizeof(adj_class)));
     ERI_TRY(upload(p, (void**)&st->d_work, list.empty() ? nullptr : list.data(), list.size() * sizeof(adj_work)));
     ERI_TRY(upload(p, (void**)&st->d_bf, bf.data(), bf.size() * sizeof(int64_t)));
     ERI_TRY(upload(p, (void**)&st->d_poff, p->sh_off.empty() ? nullptr : p->sh_off.data(), p->sh_off.size() * sizeof(int64_t)));
     ERI_TRY(upload(p, (void**)&st->d_energy, nullptr, 2 * (size_t)st->n_shares * sizeof(double)));
-    ERI_TRY(upload(p, (void**)&st->d_part, nullptr, (size_t)ADJ_SLICES * st->n_grad * sizeof(double)));
+    ERI_TRY(upload(p, (void**)&st->d_part, nullptr, (size_t)st->n_slices * st->n_grad * sizeof(double)));
     return ERI_OK;
 }
 
@@ -600,9 +603,9 @@ int eri_adj_backward(eri_plan* p, hipStream_t strm, const double* dl, const doub
     a.part = st->d_part;
     a.slice_stride = st->n_grad;
     a.ns3 = 3 * (int64_t)p->sh_L.size();
-    a.n_slices = ADJ_SLICES;
+    a.n_slices = st->n_slices;
     a.energy = st->d_energy;
-    if (grad_c) ERI_TRY(eri_grad_zero(st->d_part, ADJ_SLICES * st->n_grad, strm));
+    if (grad_c) ERI_TRY(eri_grad_zero(st->d_part, st->n_slices * st->n_grad, strm));
     a.cls = st->d_cls;
     for (int k = 0; k < 2; ++k) {
         const int n = grad_c ? st->n[k] : st->n0[k];
@@ -612,7 +615,7 @@ int eri_adj_backward(eri_plan* p, hipStream_t strm, const double* dl, const doub
         const void* fn = k ? (const void*)adj_list_kernel<64> : (const void*)adj_list_kernel<256>;
         ERI_HIP_TRY(hipLaunchKernel(fn, dim3(n), dim3(k ? 64 : 256), args, st->lds[k], strm));
     }
-    if (grad_c) ERI_TRY(eri_grad_reduce(st->d_part, ADJ_SLICES, st->n_grad, a.ns3, grad_c, grad_e, strm));
+    if (grad_c) ERI_TRY(eri_grad_reduce(st->d_part, st->n_slices, st->n_grad, a.ns3, grad_c, grad_e, strm));
     if (energy) ERI_TRY(eri_energy_add(st->d_energy, st->n_shares, energy, strm));
     return ERI_OK;
 }
