@@ -415,7 +415,7 @@ int build(eri_plan* p, eri_coul_state* st)
     for (int64_t s = 0; s < ns; ++s) bf[s + 1] = bf[s] + ncart(p->sh_L[s]);
     st->nbf = bf[ns];
     st->n_grad = 3 * ns + (int64_t)p->sh_exps.size();
-    st->n_slices = (int)std::max<int64_t>(1, std::min<int64_t>(COUL_SLICES_MAX, COUL_SLICE_DOUBLES / st->n_grad));
+    st->n_slices = (int)std::max<int64_t>(1, std::min<int64_t>(COUL_SLICES_MAX, COUL_SLICE_DOUBLES / std::max<int64_t>(1, st->n_grad)));
     ERI_TRY(upload(p, (void**)&st->d_jobs, jobs.empty() ? nullptr : jobs.data(), jobs.size() * sizeof(eri_coul_job)));
     ERI_TRY(upload(p, (void**)&st->d_ranges, ranges.empty() ? nullptr : ranges.data(), ranges.size() * sizeof(eri_coul_range)));
     ERI_TRY(upload(p, (void**)&st->d_prim_pair, prim_pair.empty() ? nullptr : prim_pair.data(), prim_pair.size() * sizeof(int32_t)));

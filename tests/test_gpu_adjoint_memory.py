@@ -35,3 +35,16 @@ def test_slices_of_a_list_over_many_shells():
     assert np.abs(gc.cpu().numpy() - gx).max() <= 1e-10 * np.abs(gx).max()
     assert np.abs(ge.cpu().numpy() - gex).max() <= 1e-10 * np.abs(gex).max()
     assert abs(en.item() - E) <= 1e-10 * abs(E)
+
+
+@pytest.mark.parametrize("batched", [False, True])
+def test_no_shells(batched):
+    """A plan over no shells has L = 0, with and without a gradient."""
+    plan = eri.Plan(W._pack([], [], np.zeros((0, 3)), [], []), None if batched else np.zeros((0, 4), np.int32), bits=0)
+    room = torch.full((4,), 2.0, dtype=torch.float64, device="cuda")
+    ptr = ctypes.c_void_p(room.data_ptr())
+    for grad in (None, ptr):
+        energy = ctypes.c_void_p(room.data_ptr() + 8)
+        assert eri.load().eri_backward(plan._h, None, None, ptr, 0, grad, grad, energy) == eri.ERI_OK
+    torch.cuda.synchronize()
+    assert (room == 2.0).all()
