@@ -871,33 +871,33 @@ int run_class(eri_plan* p, eri_bwd_state* st, int c, hipStream_t strm, const bwd
 static int backward_on(eri_plan* p, hipStream_t strm, const double* dl_deri, const double* density, int64_t nbf,
                        double* grad_centers, double* grad_exps, double* energy)
 {
-    int rc = ERI_OK;
+    // every quartet of a screened set with Gbar = D D: Hermite potentials
+    if (p->batched && density) return eri_coul_backward(p, strm, density, nbf, grad_centers, grad_exps, energy);
     bool listed = false, other = false;
     for (int c = 0; c < 256; ++c) {
         listed = listed || adj_listed(p, c);
         other = other || (p->class_count[c] && !adj_listed(p, c));
     }
-    if (p->batched && density) {
-        // every quartet of a screened set with Gbar = D D: Hermite potentials
-        rc = eri_coul_backward(p, strm, density, nbf, grad_centers, grad_exps, energy);
-        other = false;
-    } else if (listed || !other) {
-        // classes of few quartets: all in one launch
-        rc = eri_adj_backward(p, strm, dl_deri, density, nbf, grad_centers, grad_exps, energy);
-    }
-    if (rc != ERI_OK || !other) return rc;
-    if (p->bwd && grad_centers && !p->bwd->full) {
-        eri_bwd_free(p->bwd);
-        p->bwd = nullptr;
-    }
-    if (!p->bwd) {
-        try {
-            rc = build_state(p, p->bwd, grad_centers != nullptr);
-        } catch (const std::bad_alloc&) {
-            rc = ERI_ENOMEM;
+    int rc = ERI_OK;
+    // the derived classes' tables first: a call that fails for them adds nothing
+    if (other) {
+        if (p->bwd && grad_centers && !p->bwd->full) {
+            eri_bwd_free(p->bwd);
+            p->bwd = nullptr;
         }
+        if (!p->bwd) {
+            try {
+                rc = build_state(p, p->bwd, grad_centers != nullptr);
+            } catch (const std::bad_alloc&) {
+                rc = ERI_ENOMEM;
+            }
+        }
+        if (rc == ERI_OK && density && nbf != p->bwd->nbf) rc = ERI_EINVAL;
     }
-    if (rc == ERI_OK && density && nbf != p->bwd->nbf) rc = ERI_EINVAL;
+    // classes of few quartets: all in one launch
+    if (rc == ERI_OK && (listed || !other))
+        rc = eri_adj_backward(p, strm, dl_deri, density, nbf, grad_centers, grad_exps, energy);
+    if (rc != ERI_OK || !other) return rc;
     eri_bwd_state* st = p->bwd;
     const bwd_call call{dl_deri, density, grad_centers, grad_exps, energy};
     if (rc == ERI_OK && grad_centers) {
