@@ -97,7 +97,6 @@ struct eri_bwd_state {
     double* d_eitem = nullptr;    // per quartet of a pass: its contribution to L
     double* d_eacc = nullptr;     // running total of L: (high, low) double-double
     int32_t* h_pin = nullptr;     // pinned host word for scan totals
-    std::vector<int8_t> var = std::vector<int8_t>(ERI_NCLASS5, -1);   // launch variant per derived class
     eri_item* d_usorted = nullptr;   // a pass's user items ordered by primitive-quartet count
     int32_t* d_key = nullptr;        // sort keys / values (4 arrays of chunk_cap)
     void* d_sort_tmp = nullptr;
@@ -661,14 +660,15 @@ static int derive_items(eri_bwd_state* st, hipStream_t strm, const eri_item* uit
 // Launch variant of a derived class: the first pass that meets the class
 // times each variant once on up to 65536 of its items (derived in that
 // variant's bra/ket order, after a warm-up launch) and keeps the fastest for
-// the rest of the plan's life.
-static int pick_variant(eri_bwd_state* st, int c5, const eri_class_args& full, hipStream_t strm,
+// the rest of the plan's life, also where the tables are built again: L must
+// not change its bits with a timing.
+static int pick_variant(eri_plan* p, eri_bwd_state* st, int c5, const eri_class_args& full, hipStream_t strm,
                         const eri_item* uitems, const int32_t* origin, int pos, int kind, const int Lp[4],
                         const eri_kernel_info*& out)
 {
     const eri_kernel_info* var = eri_kernel_variants(0) + (int64_t)c5 * ERI_MAXVAR;
-    if (st->var[c5] >= 0) {
-        out = &var[st->var[c5]];
+    if (p->bwd_var[c5] >= 0) {
+        out = &var[p->bwd_var[c5]];
         return ERI_OK;
     }
     int nv = 0;
@@ -709,7 +709,7 @@ static int pick_variant(eri_bwd_state* st, int c5, const eri_class_args& full, h
         (void)hipEventDestroy(e1);
         if (rc != ERI_OK) return rc;
     }
-    st->var[c5] = (int8_t)best;
+    p->bwd_var[c5] = (int8_t)best;
     out = &var[best];
     return ERI_OK;
 }
@@ -768,7 +768,7 @@ static int run_kind(eri_plan* p, eri_bwd_state* st, int c, hipStream_t strm, con
     eri_class_args t = a;
     t.adj.grad = st->d_spare;
     t.adj.n_slices = 1;
-    ERI_TRY(pick_variant(st, class_id5(Lp[0], Lp[1], Lp[2], Lp[3]), t, strm, uitems, origin, pos, kind, Lp, kv));
+    ERI_TRY(pick_variant(p, st, class_id5(Lp[0], Lp[1], Lp[2], Lp[3]), t, strm, uitems, origin, pos, kind, Lp, kv));
     ERI_TRY(derive_items(st, strm, uitems, m, origin, pos, kind, Lp, *kv));
     const int64_t grid = (m + kv->per_block - 1) / kv->per_block;
     if (grid > INT32_MAX) return ERI_EUNSUPPORTED;

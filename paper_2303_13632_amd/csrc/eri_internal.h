@@ -170,6 +170,7 @@ struct eri_plan {
     std::vector<double> sh_xyz, sh_exps, sh_coefs;
     std::vector<int64_t> sh_off;
     eri_bwd_state* bwd = nullptr;
+    std::vector<int8_t> bwd_var = std::vector<int8_t>(ERI_NCLASS5, -1);   // launch variant of each derived class
     eri_coul_state* coul = nullptr;
     eri_adj_state* adj = nullptr;
     hipEvent_t turn = nullptr;          // behind the last call that used the plan's buffers (plan_enter)
