@@ -272,9 +272,9 @@ int eri_decompress(int32_t bits, const void* codes, const double* scales, int64_
  * (density: device FP64, row-major nbf x nbf, basis functions numbered shell
  * by shell in shell order with the component order above), the scalar is
  *   L = sum over planned quartets of w_q sum_(abcd) Gbar (ab|cd),
- * with w_q = 1 for explicit plans and, for ERI_PLAN_ALL_QUARTETS plans with a
- * density, the degeneracy of the unique quartet (2 for a != b, 2 for c != d,
- * 2 for (ab) != (cd)), so that L = sum_(mu nu lam sig) D D (mu nu|lam sig).
+ * with w_q = 1 for explicit plans and, for ERI_PLAN_ALL_QUARTETS plans, the
+ * degeneracy of the unique quartet (2 for a != b, 2 for c != d, 2 for (ab) !=
+ * (cd)), so that with a density L = sum_(mu nu lam sig) D D (mu nu|lam sig).
  * Exactly one of dl_deri and density is given.  The call ADDS dL/dR to
  * grad_centers (device, 3 per shell, the shell's centre xyz: an atom's gradient
  * is the sum over its shells) and dL/dalpha to
@@ -288,8 +288,10 @@ int eri_decompress(int32_t bits, const void* codes, const double* scales, int64_
  * density they are contracted, primitive pair by primitive pair, with the
  * pair's potential in Hermite Gaussians, which is summed over all quartets of
  * the plan that hold the pair; for an explicit plan's classes of at most 2048
- * quartets with the potential of the quartet's other pair under Gbar, all of
- * them in one launch.  Otherwise they are contracted ERIs of derived shells
+ * quartets, unless their contractions are too deep for it to pay, with the
+ * potential of the quartet's other pair under Gbar, all of them in one launch
+ * (L of such classes from it too, or from the class's own kernel, whichever is
+ * faster).  Otherwise they are contracted ERIs of derived shells
  * computed by the FP64 class kernels, which multiply each derived ERI
  * into Gbar as it is produced (no derived integral is stored), the fourth
  * centre's derivative following from translation invariance.  Gradient

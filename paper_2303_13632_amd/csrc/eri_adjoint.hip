@@ -19,11 +19,12 @@
 // (eri_backward.hip) launches some 30 kernels per class and waits for the
 // stream once per class and exponent; 256 quartets of s, p, d shells took
 // 29.5 ms there (values and gradient), 0.9 ms here.  That path shares the recurrences of a class over
-// many quartets and wins on classes of many quartets (ERI_ADJ_MAX).
+// many quartets and wins on classes of many or deep ones (eri_adj_routes).
 // Bound by the serial chain of a workgroup (levels of R, LDS round trips).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <new>
 #include <vector>
@@ -53,7 +54,7 @@ struct adj_class {
 struct adj_work {
     int32_t item, cls;
     int16_t side, i0, in, pad;
-    int32_t share;      // place of its share of L (side 0)
+    int32_t share;      // place of its share of L, or -1 (side 1; classes whose L comes from elsewhere)
 };
 
 struct adj_args {
@@ -419,7 +420,7 @@ __global__ __launch_bounds__(NT) void adj_list_kernel(adj_args A)
         if (tid < w) s_red[tid] += s_red[tid + w];
         __syncthreads();
     }
-    if (tid == 0 && W.side == 0) {
+    if (tid == 0 && W.share >= 0) {
         A.energy[2 * (int64_t)W.share] = s_red[0];
         A.energy[2 * (int64_t)W.share + 1] = 0.0;
     }
@@ -445,7 +446,7 @@ struct eri_adj_state {
     adj_class* d_cls = nullptr;
     adj_work* d_work = nullptr;
     int64_t n_shares = 0;
-    // the launches: 256 threads and 64, each its side 0 work first (an L alone needs no other)
+    // the launches: 256 threads and 64, each the work with a share of L first (an L alone needs no other)
     int64_t first[2] = {0, 0};
     int n0[2] = {0, 0}, n[2] = {0, 0};
     int lds[2] = {0, 0};               // bytes
@@ -466,12 +467,73 @@ void eri_adj_free(eri_adj_state* s)
     delete s;
 }
 
+// Which classes of a list come here, and for which of them L does too, from
+// what they cost here and through the derived classes (us).
+//   A gradient costs a class here its primitive quartets, at a rate that is the
+// same from some ten thousand of them on.  Through the derived classes it is
+// some 30 launches and waits, a chain of launches that each last as long as the
+// deepest contraction, and a smaller rate, which a d-d pair (g-d pairs among its
+// derived ones) raises by a share per derived item.  Measured here / there in ms:
+// 2048 quartets of K = 1 [pp|pp] 0.13 / 0.51, [dd|dd] 0.34 / 1.5; of K 1..3 0.49 / 0.88
+// and 2.9 / 3.8; 1024 of K = 6 [ps|ps] 3.3 / 5.2, [pp|pp] 14.0 / 6.1, [dp|dp] 35.8 / 12.8;
+// 256 of K = 6 0.85 / 5.1, 3.7 / 5.5, 9.7 / 8.7; 256 of K = 10 [ss|ss] 3.5 / 28, [pp|pp]
+// 26 / 36, [dp|dp] 69 / 61.  Over the 36 classes of pair types, 64 to 2048 quartets
+// and K up to 10 the choice costs at most 16% of the better time.
+//   L alone is some half of the work here (one launch for all classes, so that
+// only the longest chain over the source pairs counts), and there one launch of
+// each class's own kernel: 2048 quartets of K = 1 [pp|pp] 55 / 23 us, [dd|dd] 160 / 45;
+// of K 1..3 [ss|ss] 74 / 59, [pp|pp] 245 / 57, [dd|dd] 1474 / 159; 4 of them 33 / 55, 85 / 50,
+// 303 / 110; 256 of K = 6 281 / 704, 1812 / 570, 13800 / 1650.  Calls with and without a
+// gradient take L from the same place, so that it has the same bits in both;
+// with a gradient it is a by-product here and costs a second stream there (12 us,
+// or up to a seventh of a launch that fills the chip).  So it comes from there
+// only where that is clearly the cheaper place for all of the list: of 191 lists
+// of one class L alone then takes 0.56 of the time that it takes here, and at most
+// twice that of the class's own kernel.
+//   Above ERI_ADJ_MAX quartets stand the rates that the line was drawn by: 4096 /
+// 16384 of K 1..3 [pp|pp] 0.89 / 3.28 and 0.94 / 1.50 ms, [dp|dp] 2.41 / 9.21 and 1.83 / 4.13.
+constexpr int64_t ERI_ADJ_MAX = 2048;
+
+void eri_adj_routes(eri_plan* p)
+{
+    // ns per primitive quartet by the types of the two pairs: ss, ps, pp, ds, dp, dd
+    static const double rates[6][6] = {{1.4, 1.7, 3.3, 3.1, 8.8, 13.5},     {1.7, 2.4, 4.8, 4.6, 9.7, 14.5},
+                                       {3.3, 4.8, 10.3, 10.0, 12.9, 27.7},  {3.1, 4.6, 10.0, 9.7, 12.8, 27.5},
+                                       {8.8, 9.7, 12.9, 12.8, 26.9, 37.6},  {13.5, 14.5, 27.7, 27.5, 37.6, 77.0}};
+    // us per primitive quartet of a chain through a class's own kernel, by the smaller pair
+    static const double step[6] = {0.22, 0.31, 0.45, 0.45, 0.78, 1.24};
+    auto type = [](int x, int y) {
+        const int hi = std::max(x, y), lo = std::min(x, y);
+        return hi == 0 ? 0 : hi == 1 ? 1 + lo : 3 + lo;
+    };
+    double work = 0.0, longest = 0.0, energy_there = 0.0;
+    for (int c = 0; c < 256; ++c) {
+        p->adj_listed[c] = p->adj_energy[c] = false;
+        const int L[4] = {c >> 6, (c >> 4) & 3, (c >> 2) & 3, c & 3};
+        if (p->class_count[c] == 0 || p->class_count[c] > ERI_ADJ_MAX || *std::max_element(L, L + 4) > 2) continue;
+        const int x = type(L[0], L[1]), y = type(L[2], L[3]);
+        const double rate = rates[x][y], n = (double)p->class_count[c], pq = p->class_pq[c], deep = (double)p->class_maxpq[c];
+        const double ne = (double)(adj_nc(L[0]) * adj_nc(L[1]) * adj_nc(L[2]) * adj_nc(L[3]));
+        const double items = 6.0 + 8.0 * std::sqrt(std::sqrt(pq / n));   // derived items of a quartet
+        p->adj_listed[c] = 1e-3 * rate * pq < 430.0 + 0.4 * ne + (2.6 + 0.005 * ne) * deep + 1.8e-5 * ne * pq +
+                                                  (std::max(x, y) == 5 ? 0.015 * items * n : 0.0);
+        if (!p->adj_listed[c]) continue;
+        work += 1e-3 * (0.1 + 0.54 * rate) * pq + 5e-3 * n;
+        longest = std::max(longest, (1.7 + 0.48 * rate) * std::sqrt(deep));
+        // (up to L_tot = 2 a lane walks the contraction, else a slot of lanes)
+        energy_there += 32.0 + (L[0] + L[1] + L[2] + L[3] <= 2 ? 0.58 : step[std::min(x, y)]) * deep + 1e-5 * ne * n +
+                        5e-7 * ne * pq;
+    }
+    const bool here = 10.0 + std::max(work, longest) <= energy_there;
+    for (int c = 0; c < 256; ++c) p->adj_energy[c] = here && p->adj_listed[c];
+}
+
 static int adj_build(eri_plan* p, eri_adj_state* st)
 {
     const int64_t nq = p->n_quartets, ns = (int64_t)p->sh_L.size();
     auto listed = [&](int64_t q) {
         const int32_t* u = p->quartets.data() + 4 * q;
-        return adj_listed(p, p->sh_L[u[0]] * 64 + p->sh_L[u[1]] * 16 + p->sh_L[u[2]] * 4 + p->sh_L[u[3]]);
+        return p->adj_listed[p->sh_L[u[0]] * 64 + p->sh_L[u[1]] * 16 + p->sh_L[u[2]] * 4 + p->sh_L[u[3]]];
     };
     // the record of an ordered shell pair: the plan holds one of its two orders
     std::vector<eri_item> items(nq);
@@ -507,7 +569,7 @@ static int adj_build(eri_plan* p, eri_adj_state* st)
         }
     const int per = (int)std::min<int64_t>(256, std::max<int64_t>(1, targets / ADJ_WORK));
     for (int c = 0; c < 256; ++c) {
-        if (!adj_listed(p, c)) continue;
+        if (!p->adj_listed[c]) continue;
         adj_class e;
         std::memset(&e, 0, sizeof(e));
         const int L[4] = {c >> 6, (c >> 4) & 3, (c >> 2) & 3, c & 3};
@@ -520,6 +582,7 @@ static int adj_build(eri_plan* p, eri_adj_state* st)
         e.jc = 4;
         while (e.jc > 1 && adj_lds(L, e.jc).end * 8 > 60 * 1024) e.jc /= 2;
         const int k = std::max(u[0], u[1]) <= ADJ_NARROW ? 1 : 0;
+        const bool shares = p->adj_energy[c];
         st->lds[k] = std::max(st->lds[k], adj_lds(L, e.jc).end * 8);
         for (int64_t q = e.first; q < e.first + p->class_count[c]; ++q) {
             int np[2];
@@ -531,7 +594,7 @@ static int adj_build(eri_plan* p, eri_adj_state* st)
                 for (int i = 0; i < np[side]; i += per) {
                     entry x;
                     x.w = adj_work{(int32_t)q, (int32_t)cls.size(), (int16_t)side, (int16_t)i,
-                                   (int16_t)std::min(per, np[side] - i), 0, 0};
+                                   (int16_t)std::min(per, np[side] - i), 0, side == 0 && shares ? 0 : -1};
                     const double step = (double)u[side] * adj_nherm(side ? lb : lk) / (k ? 64 : 256) + 1000.0;
                     x.cost = x.w.in * (double)np[side ^ 1] * step;
                     work[k].push_back(x);
@@ -541,14 +604,14 @@ static int adj_build(eri_plan* p, eri_adj_state* st)
     }
     std::vector<adj_work> list;
     for (int k = 0; k < 2; ++k) {
-        // side 0 first, then the longest first
+        // those with a share of L first, then the longest first
         std::stable_sort(work[k].begin(), work[k].end(), [](const entry& x, const entry& y) {
-            return x.w.side != y.w.side ? x.w.side < y.w.side : x.cost > y.cost;
+            return x.w.share != y.w.share ? x.w.share > y.w.share : x.cost > y.cost;
         });
         st->first[k] = (int64_t)list.size();
         st->n[k] = (int)work[k].size();
         for (entry& x : work[k])
-            if (x.w.side == 0) {
+            if (x.w.share >= 0) {
                 x.w.share = (int32_t)st->n_shares++;
                 ++st->n0[k];
             }
@@ -616,6 +679,6 @@ int eri_adj_backward(eri_plan* p, hipStream_t strm, const double* dl, const doub
         ERI_HIP_TRY(hipLaunchKernel(fn, dim3(n), dim3(k ? 64 : 256), args, st->lds[k], strm));
     }
     if (grad_c) ERI_TRY(eri_grad_reduce(st->d_part, st->n_slices, st->n_grad, a.ns3, grad_c, grad_e, strm));
-    if (energy) ERI_TRY(eri_energy_add(st->d_energy, st->n_shares, energy, strm));
+    if (energy && st->n_shares) ERI_TRY(eri_energy_add(st->d_energy, st->n_shares, energy, strm));
     return ERI_OK;
 }

@@ -768,7 +768,17 @@ static int run_kind(eri_plan* p, eri_bwd_state* st, int c, hipStream_t strm, con
     eri_class_args t = a;
     t.adj.grad = st->d_spare;
     t.adj.n_slices = 1;
-    ERI_TRY(pick_variant(p, st, class_id5(Lp[0], Lp[1], Lp[2], Lp[3]), t, strm, uitems, origin, pos, kind, Lp, kv));
+    const int c5 = class_id5(Lp[0], Lp[1], Lp[2], Lp[3]);
+    if (!p->adj_listed[c]) {
+        ERI_TRY(pick_variant(p, st, c5, t, strm, uitems, origin, pos, kind, Lp, kv));
+    } else if (ki.mode == 0) {
+        // L of few quartets: the form with a slot of lanes per quartet where a
+        // class of lanes has one (512 [ds|ds] of K 1..3: 129 -> 62 us), with the same
+        // bits: L must not depend on a timing
+        const eri_kernel_info* var = eri_kernel_variants(0) + (int64_t)c5 * ERI_MAXVAR;
+        for (int k = 1; k < ERI_MAXVAR; ++k)
+            if (var[k].fn && var[k].mode == 1 && var[k].tag == 1) kv = &var[k];
+    }
     ERI_TRY(derive_items(st, strm, uitems, m, origin, pos, kind, Lp, *kv));
     const int64_t grid = (m + kv->per_block - 1) / kv->per_block;
     if (grid > INT32_MAX) return ERI_EUNSUPPORTED;
@@ -814,20 +824,25 @@ int run_class(eri_plan* p, eri_bwd_state* st, int c, hipStream_t strm, const bwd
             uitems = st->d_uall + p->class_qoff[c] + q0;
         }
         // order the pass by primitive-quartet count, so that the lanes of a
-        // wavefront (and the slots of a workgroup) loop over similar counts
-        const unsigned gm = (unsigned)((m + 255) / 256);
-        int32_t* key_in = st->d_key;
-        int32_t* idx_in = st->d_key + st->chunk_cap;
-        int32_t* key_out = st->d_key + 2 * st->chunk_cap;
-        int32_t* orig = st->d_key + 3 * st->chunk_cap;
-        hipLaunchKernelGGL(eri_bwd_key_kernel, dim3(gm), dim3(256), 0, strm, uitems, m, st->d_pairs, key_in, idx_in);
-        ERI_HIP_TRY(hipGetLastError());
-        size_t tmp = st->sort_tmp_bytes;
-        ERI_HIP_TRY(hipcub::DeviceRadixSort::SortPairs(st->d_sort_tmp, tmp, key_in, key_out, idx_in, orig, (int)m, 0,
-                                                       16, strm));
-        hipLaunchKernelGGL(eri_bwd_gather_kernel, dim3(gm), dim3(256), 0, strm, uitems, m, orig, st->d_usorted);
-        ERI_HIP_TRY(hipGetLastError());
-        uitems = st->d_usorted;
+        // wavefront (and the slots of a workgroup) loop over similar counts; a
+        // class of few quartets, of which only L is asked here, stays in plan
+        // order (bra, then ket counts)
+        int32_t* orig = nullptr;
+        if (!p->adj_listed[c]) {
+            const unsigned gm = (unsigned)((m + 255) / 256);
+            int32_t* key_in = st->d_key;
+            int32_t* idx_in = st->d_key + st->chunk_cap;
+            int32_t* key_out = st->d_key + 2 * st->chunk_cap;
+            orig = st->d_key + 3 * st->chunk_cap;
+            hipLaunchKernelGGL(eri_bwd_key_kernel, dim3(gm), dim3(256), 0, strm, uitems, m, st->d_pairs, key_in, idx_in);
+            ERI_HIP_TRY(hipGetLastError());
+            size_t tmp = st->sort_tmp_bytes;
+            ERI_HIP_TRY(hipcub::DeviceRadixSort::SortPairs(st->d_sort_tmp, tmp, key_in, key_out, idx_in, orig, (int)m, 0,
+                                                           16, strm));
+            hipLaunchKernelGGL(eri_bwd_gather_kernel, dim3(gm), dim3(256), 0, strm, uitems, m, orig, st->d_usorted);
+            ERI_HIP_TRY(hipGetLastError());
+            uitems = st->d_usorted;
+        }
         if (call.dens) {
             const int64_t tot = m * n_eriq;
             const unsigned gg = (unsigned)std::min<int64_t>((tot + 255) / 256, 65536);
@@ -873,55 +888,75 @@ static int backward_on(eri_plan* p, hipStream_t strm, const double* dl_deri, con
 {
     // every quartet of a screened set with Gbar = D D: Hermite potentials
     if (p->batched && density) return eri_coul_backward(p, strm, density, nbf, grad_centers, grad_exps, energy);
-    bool listed = false, other = false;
+    // listed: something for the launch over the short classes; grad, other: a
+    // gradient, or L too, by derived classes
+    bool listed = false, grad = false, other = false;
     for (int c = 0; c < 256; ++c) {
-        listed = listed || adj_listed(p, c);
-        other = other || (p->class_count[c] && !adj_listed(p, c));
+        if (!p->class_count[c]) continue;
+        listed = listed || (grad_centers ? p->adj_listed[c] : p->adj_energy[c]);
+        grad = grad || (grad_centers && !p->adj_listed[c]);
+        other = other || (energy && !p->adj_energy[c]);
     }
+    other = other || grad;
     int rc = ERI_OK;
     // the derived classes' tables first: a call that fails for them adds nothing
     if (other) {
-        if (p->bwd && grad_centers && !p->bwd->full) {
+        if (p->bwd && grad && !p->bwd->full) {
             eri_bwd_free(p->bwd);
             p->bwd = nullptr;
         }
         if (!p->bwd) {
             try {
-                rc = build_state(p, p->bwd, grad_centers != nullptr);
+                rc = build_state(p, p->bwd, grad);
             } catch (const std::bad_alloc&) {
                 rc = ERI_ENOMEM;
             }
         }
         if (rc == ERI_OK && density && nbf != p->bwd->nbf) rc = ERI_EINVAL;
     }
-    // classes of few quartets: all in one launch
+    if (rc != ERI_OK) return rc;
+    eri_bwd_state* st = p->bwd;
+    auto derived = [&](hipStream_t on, bool of_listed) {
+        for (int c = 0; c < 256; ++c) {
+            if (!p->class_count[c] || p->adj_listed[c] != of_listed) continue;
+            const bwd_call call{dl_deri, density, of_listed ? nullptr : grad_centers, of_listed ? nullptr : grad_exps,
+                                p->adj_energy[c] ? nullptr : energy};
+            if (call.grad_c || call.energy) ERI_TRY(run_class(p, st, c, on, call));
+        }
+        return (int)ERI_OK;
+    };
+    // classes of few quartets: all in one launch; where L comes from their own
+    // kernels, those run beside it (a chain per class that leaves the chip idle)
+    side_set* side = nullptr;
+    hipStream_t aside = strm;
+    if (other && energy) {
+        if (listed && grad_centers) aside = side_fork(p, strm, side);
+        hipLaunchKernelGGL(eri_bwd_zero_kernel, dim3(1), dim3(256), 0, aside, st->d_eacc, (int64_t)2);
+        if (hipGetLastError() != hipSuccess) rc = ERI_EHIP;
+        if (rc == ERI_OK) rc = derived(aside, true);
+    }
     if (rc == ERI_OK && (listed || !other))
         rc = eri_adj_backward(p, strm, dl_deri, density, nbf, grad_centers, grad_exps, energy);
+    const int joined = side_join(strm, side);
+    if (rc == ERI_OK) rc = joined;
     if (rc != ERI_OK || !other) return rc;
-    eri_bwd_state* st = p->bwd;
-    const bwd_call call{dl_deri, density, grad_centers, grad_exps, energy};
-    if (rc == ERI_OK && grad_centers) {
+    if (grad) {
         hipLaunchKernelGGL(eri_bwd_zero_kernel, dim3(1024), dim3(256), 0, strm, st->d_part,
                            (int64_t)st->n_slices * st->n_grad);
-        if (hipGetLastError() != hipSuccess) rc = ERI_EHIP;
+        ERI_HIP_TRY(hipGetLastError());
     }
-    if (rc == ERI_OK && energy) {
-        hipLaunchKernelGGL(eri_bwd_zero_kernel, dim3(1), dim3(256), 0, strm, st->d_eacc, (int64_t)2);
-        if (hipGetLastError() != hipSuccess) rc = ERI_EHIP;
-    }
-    for (int c = 0; c < 256 && rc == ERI_OK; ++c)
-        if (p->class_count[c] && !adj_listed(p, c)) rc = run_class(p, st, c, strm, call);
-    if (rc == ERI_OK && grad_centers) {
+    ERI_TRY(derived(strm, false));
+    if (grad) {
         hipLaunchKernelGGL(eri_bwd_reduce_kernel, dim3((unsigned)((st->n_grad + 255) / 256)), dim3(256), 0, strm,
                            st->d_part, st->n_slices, st->n_grad, 3 * (int64_t)p->sh_L.size(), grad_centers,
                            grad_exps);
-        if (hipGetLastError() != hipSuccess) rc = ERI_EHIP;
+        ERI_HIP_TRY(hipGetLastError());
     }
-    if (rc == ERI_OK && energy) {
+    if (energy) {
         hipLaunchKernelGGL(eri_bwd_energy_out_kernel, dim3(1), dim3(64), 0, strm, st->d_eacc, energy);
-        if (hipGetLastError() != hipSuccess) rc = ERI_EHIP;
+        ERI_HIP_TRY(hipGetLastError());
     }
-    return rc;
+    return ERI_OK;
 }
 
 extern "C" int eri_backward(eri_plan* p, void* stream, const double* dl_deri, const double* density, int64_t nbf,

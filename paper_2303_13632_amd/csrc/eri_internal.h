@@ -173,7 +173,10 @@ struct eri_plan {
     std::vector<int8_t> bwd_var = std::vector<int8_t>(ERI_NCLASS5, -1);   // launch variant of each derived class
     eri_coul_state* coul = nullptr;
     eri_adj_state* adj = nullptr;
-    hipEvent_t turn = nullptr;          // behind the last call that used the plan's buffers (plan_enter)
+    bool adj_listed[256] = {}, adj_energy[256] = {};   // short-list adjoint: the gradient, and L, of a class
+    // the last call that used the plan's buffers (plan_enter): on the null stream, or `turn` is behind it
+    enum { TURN_NONE, TURN_NULL, TURN_EVENT } turn_of = TURN_NONE;
+    hipEvent_t turn = nullptr;
 };
 
 // Calls that use buffers which the plan holds (items of a screened plan, staging
@@ -184,17 +187,20 @@ struct eri_plan {
 int plan_enter(eri_plan* p, hipStream_t st);
 int plan_leave(eri_plan* p, hipStream_t st);
 
+// A side stream that runs beside `st` from here on, or `st` itself where none is
+// free; side_join puts `st` behind it.  Between the two no other call that uses
+// side streams is made by this thread.
+struct side_set;
+hipStream_t side_fork(eri_plan* p, hipStream_t st, side_set*& side);
+int side_join(hipStream_t st, side_set* side);
+
 // The density form of eri_backward for screened plans (eri_coulomb.hip).
 int eri_coul_backward(eri_plan* p, hipStream_t strm, const double* density, int64_t nbf, double* grad_c, double* grad_e,
                       double* energy);
 
-// eri_backward of an explicit plan's classes of at most ERI_ADJ_MAX quartets
-// (eri_adjoint.hip; the others go through eri_backward.hip).  The line lies where
-// one class alone takes as long either way: at 1024 / 4096 / 16384 quartets of
-// [pp|pp] 0.31 / 0.89 / 3.28 ms here, 0.96 / 0.94 / 1.50 ms there, of [dp|dp] 0.76 / 2.41 /
-// 9.21 and 1.34 / 1.83 / 4.13 ms, of [dd|dd] 1.69 / 5.53 / 21.3 and 3.37 / 7.87 / 27.7 ms.
-constexpr int64_t ERI_ADJ_MAX = 2048;
-inline bool adj_listed(const eri_plan* p, int c) { return !p->batched && p->class_count[c] && p->class_count[c] <= ERI_ADJ_MAX; }
+// eri_backward of an explicit plan's classes in adj_listed (eri_adjoint.hip; the
+// others go through eri_backward.hip), and which those are.
+void eri_adj_routes(eri_plan* p);
 int eri_adj_backward(eri_plan* p, hipStream_t strm, const double* dl, const double* density, int64_t nbf, double* grad_c,
                      double* grad_e, double* energy);
 

@@ -247,15 +247,48 @@ static bool is_capturing(hipStream_t st)
     return true;
 }
 
+// (The null stream needs no event of each call: it is always there to be asked
+// for one when another stream comes next.  An event and a wait per call took 3 of
+// the 17 us of a short list's L.)
 int plan_enter(eri_plan* p, hipStream_t st)
 {
-    if (!is_capturing(st)) ERI_HIP_TRY(hipStreamWaitEvent(st, p->turn, 0));
+    if (p->turn_of == eri_plan::TURN_NONE || (p->turn_of == eri_plan::TURN_NULL && !st) || is_capturing(st)) return ERI_OK;
+    if (p->turn_of == eri_plan::TURN_NULL) ERI_HIP_TRY(hipEventRecord(p->turn, nullptr));
+    ERI_HIP_TRY(hipStreamWaitEvent(st, p->turn, 0));
     return ERI_OK;
 }
 
 int plan_leave(eri_plan* p, hipStream_t st)
 {
-    if (!is_capturing(st)) ERI_HIP_TRY(hipEventRecord(p->turn, st));
+    if (!st) {
+        p->turn_of = eri_plan::TURN_NULL;
+    } else if (!is_capturing(st)) {
+        ERI_HIP_TRY(hipEventRecord(p->turn, st));
+        p->turn_of = eri_plan::TURN_EVENT;
+    }
+    return ERI_OK;
+}
+
+hipStream_t side_fork(eri_plan* p, hipStream_t st, side_set*& side)
+{
+    side = is_capturing(st) ? nullptr : side_take(p, st);
+    if (!side) return st;
+    if (hipEventRecord(side->fork, st) == hipSuccess && hipStreamWaitEvent(side->st[0], side->fork, 0) == hipSuccess)
+        return side->st[0];
+    (void)hipGetLastError();
+    side->mu.unlock();
+    side = nullptr;
+    return st;
+}
+
+int side_join(hipStream_t st, side_set* side)
+{
+    if (!side) return ERI_OK;
+    hipError_t e = hipEventRecord(side->join[0], side->st[0]);
+    if (e == hipSuccess) e = hipStreamWaitEvent(st, side->join[0], 0);
+    if (e != hipSuccess) (void)hipStreamSynchronize(side->st[0]);   // (in order all the same)
+    side->mu.unlock();
+    ERI_HIP_TRY(e);
     return ERI_OK;
 }
 
@@ -713,6 +746,7 @@ extern "C" int eri_plan_create(eri_plan** out, int64_t n_shells, const int32_t* 
         p->sh_exps.assign(exps, exps + nprim_all);
         p->sh_coefs.assign(coefs, coefs + nprim_all);
         rc = batched ? create_batched(p, s, opts) : create_explicit(p, s, quartets, n_quartets);
+        if (!batched) eri_adj_routes(p);
         // scale blocks: G consecutive quartets of a class share one scale
         const int64_t G = p->scale_block;
         int64_t stage = 0;
