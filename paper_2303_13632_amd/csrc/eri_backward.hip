@@ -545,16 +545,20 @@ int build_state(eri_plan* p, eri_bwd_state*& out, bool full)
     for (int64_t s = 0; s < ns; ++s) bf[s + 1] = bf[s] + ncart(orig.L[s]);
     st->nbf = bf[ns];
     // ---- pass sizes ------------------------------------------------------------
+    // (of the classes that come here at all)
+    auto comes = [&](int c) { return p->class_count[c] && !(p->adj_listed[c] && p->adj_energy[c]); };
     int64_t maxcount = 0;
-    for (int c = 0; c < 256; ++c) maxcount = std::max(maxcount, p->class_count[c]);
+    for (int c = 0; c < 256; ++c)
+        if (comes(c)) maxcount = std::max(maxcount, p->class_count[c]);
     for (int l = 0; l <= BWD_MAXL; ++l) st->kmax_all = std::max(st->kmax_all, st->kmax[l]);
     // passes take up to BWD_CHUNK_MAX quartets (nothing per derived ERI is stored)
     st->chunk_cap = std::max<int64_t>(1, std::min(maxcount, BWD_CHUNK_MAX));
     if (p->pass_cap > 0) st->chunk_cap = std::min(st->chunk_cap, p->pass_cap);
-    // density form: a pass of class c holds at most BWD_GBAR_MAX / n_eriq(c)
-    // quartets (its D_ab D_cd rows)
-    for (int c = 0; c < 256; ++c) {
-        if (!p->class_count[c]) continue;
+    // density form (explicit plans): a pass of class c holds at most
+    // BWD_GBAR_MAX / n_eriq(c) quartets (its D_ab D_cd rows, allocated at the
+    // first call with a density)
+    for (int c = 0; c < 256 && !p->batched; ++c) {
+        if (!comes(c)) continue;
         const int64_t ne = (int64_t)ncart(c >> 6) * ncart((c >> 4) & 3) * ncart((c >> 2) & 3) * ncart(c & 3);
         const int64_t q = std::min({p->class_count[c], st->chunk_cap, std::max<int64_t>(1, BWD_GBAR_MAX / ne)});
         st->gbar_elems = std::max(st->gbar_elems, q * ne);
@@ -562,7 +566,7 @@ int build_state(eri_plan* p, eri_bwd_state*& out, bool full)
     // ---- contraction maps ----------------------------------------------------
     std::vector<int32_t> maps;
     for (int c = 0; c < 256; ++c) {
-        if (!p->class_count[c]) continue;
+        if (!comes(c)) continue;
         const int L[4] = {c >> 6, (c >> 4) & 3, (c >> 2) & 3, c & 3};
         for (int kind = DK_BASE; kind <= DK_E2; ++kind)
             for (int pos = 0; pos < 4; ++pos) {
@@ -610,8 +614,7 @@ int build_state(eri_plan* p, eri_bwd_state*& out, bool full)
         }
     }
     up((void**)&st->d_sort_tmp, nullptr, std::max<size_t>(st->sort_tmp_bytes, 64));
-    up((void**)&st->d_maps, maps.data(), maps.size() * sizeof(int32_t));
-    up((void**)&st->d_gbar, nullptr, (size_t)std::max<int64_t>(st->gbar_elems, 1) * sizeof(double));
+    up((void**)&st->d_maps, maps.empty() ? nullptr : maps.data(), maps.size() * sizeof(int32_t));
     if (full) {
         st->n_slices = (int)std::max<int64_t>(1, std::min<int64_t>(BWD_SLICES_MAX, BWD_SLICE_DOUBLES / st->n_grad));
         up((void**)&st->d_part, nullptr, (size_t)st->n_slices * st->n_grad * sizeof(double));
@@ -913,6 +916,8 @@ static int backward_on(eri_plan* p, hipStream_t strm, const double* dl_deri, con
             }
         }
         if (rc == ERI_OK && density && nbf != p->bwd->nbf) rc = ERI_EINVAL;
+        if (rc == ERI_OK && density && !p->bwd->d_gbar)
+            rc = upload(p, (void**)&p->bwd->d_gbar, nullptr, (size_t)p->bwd->gbar_elems * sizeof(double));
     }
     if (rc != ERI_OK) return rc;
     eri_bwd_state* st = p->bwd;

@@ -48,3 +48,19 @@ def test_no_shells(batched):
         assert eri.load().eri_backward(plan._h, None, None, ptr, 0, grad, grad, energy) == eri.ERI_OK
     torch.cuda.synchronize()
     assert (room == 2.0).all()
+
+
+def test_no_density_rows_without_a_density():
+    """The D_ab D_cd rows of a pass are held from the first call with a density on,
+    and for the classes that use them: not for [pp|pp] here, whose 200 quartets have
+    more values than the 2600 of the class that does."""
+    sh = W.random_shells(12, lmax=2, seed=50, k_choices=(1, 2))
+    by = [np.flatnonzero(sh["L"] == l) for l in range(3)]
+    rng = np.random.default_rng(51)
+    q = [[rng.choice(by[l]) for l in L] for L, n in (((1, 0, 0, 0), 2600), ((1, 1, 1, 1), 200)) for _ in range(n)]
+    plan = eri.Plan(sh, np.array(q, np.int32), bits=0)
+    plan.backward(dl=torch.ones(plan.out_values, dtype=torch.float64, device="cuda"))
+    before = _device_bytes(plan)
+    for _ in range(2):
+        plan.backward(density=torch.tensor(W.random_density(plan.nbf, seed=52), device="cuda"))
+        assert _device_bytes(plan) - before == 2600 * 3 * 8
