@@ -241,8 +241,11 @@ int eri_compute_class(eri_plan* plan, int32_t class_id, void* stream, double* ou
  * the first min(class_quartets, sample_quartets) quartets are computed with
  * each variant `trials` times on `stream` (outputs to scratch memory the call
  * allocates and frees; the plan's codes width is kept) and the fastest mean
- * time wins.  With cache_path, choices stored there under the key
- * "<precision>:<class id>:<bits>" are used without timing, and the file is
+ * time wins.  Variant 0 is the kernel that the class's launches take by rule on
+ * their size and depth (class_tag), also where the sample is smaller.  With
+ * cache_path, choices stored there under the key "<precision>:<class id>:<bits>",
+ * or "<precision>:<class id>:d<tag>:<bits>" where that kernel is not the class's
+ * ordinary one, are used without timing, and the file is
  * rewritten with every choice made.  Synchronises the stream.  All variants of a class
  * compute the same integrals in the same orientation and layout; their
  * values may differ in the last bits (other operation order).

@@ -1058,6 +1058,12 @@ static const eri_kernel_info& default_kernel(const eri_plan* p, int c, int64_t n
     return prim.fn && better ? prim : def;
 }
 
+// Quartets of one launch of a class: what default_kernel goes by.
+static int64_t launch_quartets(const eri_plan* p, int c)
+{
+    return p->batched ? class_piece(p, c) : p->class_count[c];
+}
+
 // Kernel of a class launch: the autotuner's variant, else the default.
 static const eri_kernel_info& class_kernel(const eri_plan* p, int c)
 {
@@ -1066,7 +1072,7 @@ static const eri_kernel_info& class_kernel(const eri_plan* p, int c)
         const eri_kernel_info& v = eri_kernel_variants(table_index(p->precision))[c5 * ERI_MAXVAR + p->class_var[c]];
         if (v.fn) return v;
     }
-    return default_kernel(p, c, p->batched ? class_piece(p, c) : p->class_count[c]);
+    return default_kernel(p, c, launch_quartets(p, c));
 }
 
 // Compression of one class's FP64 values in blocks of S consecutive values
@@ -1323,11 +1329,19 @@ extern "C" int eri_compute_class(eri_plan* p, int32_t c, void* stream, double* o
 // ---------------------------------------------------------------------------
 // Autotuner: timed trials of each class's launch variants on a sample
 // ---------------------------------------------------------------------------
+// A choice holds for the default kernel that it was made against, which a rule
+// takes by the launch's size and depth: where that is not the class's ordinary
+// kernel, its tag is in the key.
 static std::string tune_key(const eri_plan* p, int c)
 {
     char buf[64];
     static const char* const pname[] = {"fp64", "mixed", "rys", "rys32"};
-    std::snprintf(buf, sizeof(buf), "%s:%d:%d", pname[table_index(p->precision)], c, p->bits);
+    const char* prec = pname[table_index(p->precision)];
+    const eri_kernel_info& def = default_kernel(p, c, launch_quartets(p, c));
+    if (def.fn == kernel_table(p->precision)[class_id5_of(c)].fn)
+        std::snprintf(buf, sizeof(buf), "%s:%d:%d", prec, c, p->bits);
+    else
+        std::snprintf(buf, sizeof(buf), "%s:%d:d%d:%d", prec, c, def.tag, p->bits);
     return buf;
 }
 
@@ -1446,7 +1460,8 @@ static int tune_plan(eri_plan* p, hipStream_t st, int64_t sample, int trials, co
         int bestk = 0;
         for (int k = 0; k < ERI_MAXVAR && rc == ERI_OK; ++k) {
             if (!var[c5 * ERI_MAXVAR + k].fn) continue;
-            const eri_kernel_info& ki = k ? var[c5 * ERI_MAXVAR + k] : default_kernel(p, c, n);
+            // variant 0 is the kernel that the class's launches take, not the sample's
+            const eri_kernel_info& ki = k ? var[c5 * ERI_MAXVAR + k] : default_kernel(p, c, launch_quartets(p, c));
             // the sample's items in this variant's orientation
             if (!p->batched) {
                 rc = orient_items(p, c, ki, st);
