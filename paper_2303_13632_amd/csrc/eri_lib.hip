@@ -1528,25 +1528,35 @@ extern "C" int eri_plan_set_variants(eri_plan* p, const int32_t* v)
 }
 
 // ---------------------------------------------------------------------------
-// Standalone compression / decompression.  Bound by HBM: 8 bytes of value and
-// one container per code, each moved once.
-//   A workgroup of four wavefronts takes four consecutive blocks.  Blocks of
-// more than ERI_CODEC_WAVE values go through all 256 threads, the others
-// through one wavefront each: a quartet of small shells has too few values
-// for a workgroup, one of four f shells (10000) too many for the loads that
-// one wavefront keeps in flight.  A thread moves aligned groups of four
-// values (32 bytes of values, one vector store of codes) and keeps the groups
-// of its block in registers between the maximum (eq. 9) and the codes
-// (eq. 10), so the values are read once; only blocks beyond 10240 values are
-// read twice.  Groups have W = 4 values where the arrays' bases are aligned to
-// one (checked on the host), else one.
-//   131072 blocks of random classes (82M values, int16): one 64-thread
-// workgroup per block that read the values twice and decided about 1/eps value
-// by value took 369 us to compress and 265 us to decompress (2.2 and 3.1 TB/s);
-// this form takes 216 and 224 us (3.8 and 3.7 TB/s; a copy reaches 5.0).
+// Standalone compression / decompression.  Bound by HBM for large blocks (8 bytes
+// of value and one container per code, each moved once), by the chain offsets,
+// values, maximum, codes of a block for small ones, of which as many as possible
+// must be in flight.
+//   A workgroup of four wavefronts takes 4, 8 or 16 consecutive blocks.  Blocks of
+// more values than ERI_CODEC_WAVE go through all 256 threads, the others through
+// one wavefront each: one of four f shells (10000) has too many for the loads that
+// one wavefront keeps in flight.  A thread moves aligned groups of W = 4 values
+// (32 bytes, one vector store of codes; W = 1 where the arrays' bases are not
+// aligned to one, which the host checks) and keeps them in registers between the
+// maximum (eq. 9) and the codes (eq. 10), so the values are read once; only what
+// is beyond 8192 values (10240) of a block is read twice.  A wavefront takes four
+// small blocks at once: up to ERI_CODEC_QUARTER values by a quarter of its lanes
+// each, up to ERI_CODEC_GROUP side by side.  Few blocks (ERI_CODEC_MANY) leave
+// compute units idle with 16 a workgroup; many small ones need them.
+//   Against one 64-thread workgroup per block that reads the values twice and
+// decides about 1/eps value by value, int16, us before / now: 131072 blocks of random
+// classes (82M values) 348 / 168 to compress (3.9 / 4.9 TB/s) and 294 / 191 to decompress; a
+// million of one value 218 / 127 and 211 / 114; 200000 of 36 47 / 33 and 45 / 29; 100000 of
+// 81 33 / 31 and 24 / 24; 60000 of 216 33 / 26 and 22 / 22; 20000 of 1296 68 / 40 and 40 / 40; 3000
+// of 10000 156 / 50 and 120 / 68.  (One block per wavefront throughout took 647, 142
+// and 73 us for the small ones.)  12000 to 40000 blocks of 81 to 216 values stay 2 us behind it.
 // ---------------------------------------------------------------------------
-constexpr int ERI_CODEC_WAVE = 2556;   // at most 640 aligned groups: ten a lane
-constexpr int ERI_CODEC_PER = 4;
+constexpr int ERI_CODEC_WAVE = 2044;   // at most 512 aligned groups: eight a lane
+constexpr int ERI_CODEC_WAVE_FEW = 2556;   // 640: ten
+constexpr int ERI_CODEC_GROUP = 252;   // at most 64 aligned groups: one a lane
+constexpr int ERI_CODEC_QUARTER = 60;  // at most 16: one a lane of a quarter
+constexpr int64_t ERI_CODEC_MANY = 16384;   // blocks from which a compressing workgroup takes 8 of them, not four; four times that: 16
+constexpr int ERI_CODEC_UNPACK = 4;    // of a decompressing one
 
 template <typename T, int W>
 struct eri_group {
@@ -1572,68 +1582,79 @@ struct eri_groups {
     }
 };
 
-// One block through NT threads (t of NT; a whole wavefront or the workgroup,
-// all of which take this call), up to NG groups of each thread in registers.
-// Loads past the last group repeat it (the maximum does not mind).
+// One block of [lo, hi) through NT threads (t of NT: a quarter of a wavefront, a
+// wavefront, or the workgroup): NG groups of each thread in registers, those
+// beyond read again for the codes.  Loads past the last group repeat it (the
+// maximum does not mind).
 template <typename CT, int W, int NT, int NG>
-__device__ __forceinline__ void eri_compress_span(const double* __restrict__ x, int64_t lo, int64_t hi, int t,
-                                                  CT* __restrict__ codes, double* __restrict__ scale, double cn,
-                                                  double qmax, double* s_m)
-{
-    const eri_groups<W> G(lo, hi, t);
-    const auto* xg = reinterpret_cast<const eri_group<double, W>*>(x) + G.g0;
-    auto* cg = reinterpret_cast<eri_group<CT, W>*>(codes) + G.g0;
-    const bool held = G.ng <= NT * NG;
-    const int ng = held ? (int)G.ng : 0;
+struct eri_span {
+    static constexpr bool rest = NT == 256 || (NT == 64 && NG > 4 && W == 1);   // may be given more than it holds
+    eri_groups<W> G;
+    int ng, t;
     eri_group<double, W> v[NG];
-    const double e = G.edge >= 0 ? x[G.edge] : 0.0;
-    double m = fabs(e);
-#pragma unroll
-    for (int k = 0; k < NG; ++k)
-        if (k * NT < ng) v[k] = xg[min(t + k * NT, ng - 1)];
-#pragma unroll
-    for (int k = 0; k < NG; ++k)
-        if (k * NT < ng)
-#pragma unroll
-            for (int i = 0; i < W; ++i) m = fmax(m, fabs(v[k].v[i]));
-    if (!held)
-        for (int64_t g = t; g < G.ng; g += NT)
-#pragma unroll
-            for (int i = 0; i < W; ++i) m = fmax(m, fabs(xg[g].v[i]));
-    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
-    if (NT > 64) {
-        __syncthreads();   // the previous block's maxima are read
-        if ((t & 63) == 0) s_m[t >> 6] = m;
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < NT / 64; ++w) m = fmax(m, s_m[w]);
-    }
-    const double eps = m * cn;
-    const double inv = eri_inverse_scale(eps);
-    if (t == 0) *scale = eps;
-    auto code = [&](auto quantize) {
-        if (G.edge >= 0) codes[G.edge] = (CT)quantize(e);
-        auto put = [&](const eri_group<double, W>& u, int64_t g) {
-            eri_group<CT, W> q;
-#pragma unroll
-            for (int i = 0; i < W; ++i) q.v[i] = (CT)quantize(u.v[i]);
-            cg[g] = q;
-        };
+    double e;
+
+    __device__ __forceinline__ eri_span(const double* __restrict__ x, int64_t lo, int64_t hi, int t_) : G(lo, hi, t_), t(t_)
+    {
+        const auto* xg = reinterpret_cast<const eri_group<double, W>*>(x) + G.g0;
+        ng = (int)(G.ng < NT * NG ? G.ng : NT * NG);
+        e = G.edge >= 0 ? x[G.edge] : 0.0;
 #pragma unroll
         for (int k = 0; k < NG; ++k)
-            if (k * NT < ng && t + k * NT < ng) put(v[k], t + k * NT);
-        if (!held)
-            for (int64_t g = t; g < G.ng; g += NT) put(xg[g], g);
-    };
-    // one decision per block: 1/eps overflows only where eps is subnormal
-    if (__builtin_amdgcn_readfirstlane(__builtin_isinf(inv) ? 1 : 0))
-        code([&](double y) { return eri_quantize(y, eps, inv, qmax); });
-    else
-        code([&](double y) { return eri_quantize_mul(y, inv, qmax); });
-}
+            if (k * NT < ng) v[k] = xg[min(t + k * NT, ng - 1)];
+    }
+
+    // largest magnitude of the thread's values
+    __device__ __forceinline__ double largest(const double* __restrict__ x) const
+    {
+        const auto* xg = reinterpret_cast<const eri_group<double, W>*>(x) + G.g0;
+        double m = fabs(e);
+#pragma unroll
+        for (int k = 0; k < NG; ++k)
+            if (k * NT < ng)
+#pragma unroll
+                for (int i = 0; i < W; ++i) m = fmax(m, fabs(v[k].v[i]));
+        if (rest)
+            for (int64_t g = t + NT * NG; g < G.ng; g += NT)
+#pragma unroll
+                for (int i = 0; i < W; ++i) m = fmax(m, fabs(xg[g].v[i]));
+        return m;
+    }
+
+    // codes under the block's largest magnitude m
+    __device__ __forceinline__ void store(const double* __restrict__ x, double m, CT* __restrict__ codes,
+                                          double* __restrict__ scale, double cn, double qmax) const
+    {
+        const auto* xg = reinterpret_cast<const eri_group<double, W>*>(x) + G.g0;
+        auto* cg = reinterpret_cast<eri_group<CT, W>*>(codes) + G.g0;
+        const double eps = m * cn;
+        const double inv = eri_inverse_scale(eps);
+        if (t == 0) *scale = eps;
+        auto code = [&](auto quantize) {
+            if (G.edge >= 0) codes[G.edge] = (CT)quantize(e);
+            auto put = [&](const eri_group<double, W>& u, int64_t g) {
+                eri_group<CT, W> q;
+#pragma unroll
+                for (int i = 0; i < W; ++i) q.v[i] = (CT)quantize(u.v[i]);
+                cg[g] = q;
+            };
+#pragma unroll
+            for (int k = 0; k < NG; ++k)
+                if (k * NT < ng && t + k * NT < ng) put(v[k], t + k * NT);
+            if (rest)
+                for (int64_t g = t + NT * NG; g < G.ng; g += NT) put(xg[g], g);
+        };
+        // one decision per wavefront: 1/eps overflows only where eps is subnormal
+        if (__any(__builtin_isinf(inv) ? 1 : 0))
+            code([&](double y) { return eri_quantize(y, eps, inv, qmax); });
+        else
+            code([&](double y) { return eri_quantize_mul(y, inv, qmax); });
+    }
+};
 
 // Offsets of a workgroup's blocks: one load, lane l holds off[b0 + l]
-// (l <= ERI_CODEC_PER), so that the walk over the blocks waits once.
+// (l <= ERI_CODEC_PER; lanes beyond nb hold the end), so that the walk over the
+// blocks waits once.
 __device__ __forceinline__ int64_t eri_codec_offsets(const int64_t* __restrict__ off, int64_t b0, int nb)
 {
     const int l = threadIdx.x & 63;
@@ -1647,30 +1668,89 @@ __device__ __forceinline__ int64_t eri_uniform(int64_t v, int lane)
     return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-template <typename CT, int W>
-__global__ __launch_bounds__(256) void eri_compress_kernel(const double* __restrict__ x, const int64_t* __restrict__ off,
+// Values of the largest of n blocks from block b on.
+template <int n>
+__device__ __forceinline__ int64_t eri_codec_largest(int64_t o, int b)
+{
+    int64_t m = 0, lo = eri_uniform(o, b);
+#pragma unroll
+    for (int k = 1; k <= n; ++k) {
+        const int64_t hi = eri_uniform(o, b + k);
+        m = hi - lo > m ? hi - lo : m;
+        lo = hi;
+    }
+    return m;
+}
+
+template <typename CT, int W, int PER>
+__global__ __launch_bounds__(256, PER == 4 ? 2 : 4) void eri_compress_kernel(const double* __restrict__ x, const int64_t* __restrict__ off,
                                                            int64_t n_blocks, CT* __restrict__ codes,
                                                            double* __restrict__ scales, double cn, double qmax)
 {
+    // up to where a wavefront takes a block, and the groups that a thread holds
+    constexpr int WAVE = PER == 4 ? ERI_CODEC_WAVE_FEW : ERI_CODEC_WAVE,
+                  NG = W == 1 ? 20 : PER == 4 ? 10 : 8;
     __shared__ double s_m[4];
-    const int64_t b0 = (int64_t)blockIdx.x * ERI_CODEC_PER;
-    const int nb = (int)(n_blocks - b0 < ERI_CODEC_PER ? n_blocks - b0 : ERI_CODEC_PER);
+    const int64_t b0 = (int64_t)blockIdx.x * PER;
+    const int nb = (int)(n_blocks - b0 < PER ? n_blocks - b0 : PER);
     const int64_t o = eri_codec_offsets(off, b0, nb);
-    for (int b = 0; b < nb; ++b) {
-        const int64_t lo = eri_uniform(o, b), hi = eri_uniform(o, b + 1);
-        if (hi - lo > ERI_CODEC_WAVE)
-            eri_compress_span<CT, W, 256, 40 / W>(x, lo, hi, (int)threadIdx.x, codes, scales + b0 + b, cn, qmax, s_m);
-    }
-    const int b = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if (b < nb) {
-        const int64_t lo = eri_uniform(o, b), hi = eri_uniform(o, b + 1);
-        if (hi - lo <= ERI_CODEC_WAVE)
-            eri_compress_span<CT, W, 64, 40 / W>(x, lo, hi, (int)(threadIdx.x & 63), codes, scales + b0 + b, cn, qmax, s_m);
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t largest = eri_codec_largest<PER>(o, 0);
+    if (largest > WAVE)
+        for (int b = 0; b < nb; ++b) {
+            const int64_t lo = eri_uniform(o, b), hi = eri_uniform(o, b + 1);
+            if (hi - lo <= WAVE) continue;
+            const eri_span<CT, W, 256, NG> S(x, lo, hi, (int)threadIdx.x);
+            double m = S.largest(x);
+            for (int k = 32; k > 0; k >>= 1) m = fmax(m, __shfl_xor(m, k));
+            __syncthreads();   // the previous block's maxima are read
+            if (l == 0) s_m[w] = m;
+            __syncthreads();
+            S.store(x, fmax(fmax(s_m[0], s_m[1]), fmax(s_m[2], s_m[3])), codes, scales + b0 + b, cn, qmax);
+        }
+    // four blocks a wavefront at once where they are small (of a workgroup's four
+    // or eight: through as many wavefronts as that takes), else one after the other
+    const bool four = PER == 16 || largest <= ERI_CODEC_GROUP;
+    if (four && w >= PER / 4) return;
+    const int own = four ? 4 : PER / 4, bw = own * w;
+    const int64_t top = four ? eri_codec_largest<4>(o, bw) : ERI_CODEC_WAVE;
+    if (top <= ERI_CODEC_QUARTER) {
+        const int b = bw + (l >> 4);
+        const int64_t lo = __shfl(o, b), hi = __shfl(o, b + 1);
+        const eri_span<CT, W, 16, 4 / W> S(x, lo, hi, l & 15);
+        double m = S.largest(x);
+        for (int k = 8; k > 0; k >>= 1) m = fmax(m, __shfl_xor(m, k));
+        if (b < nb) S.store(x, m, codes, scales + b0 + b, cn, qmax);
+    } else if (top <= ERI_CODEC_GROUP) {
+        typedef eri_span<CT, 1, 64, 4> span;
+        auto lo = [&](int j) { return eri_uniform(o, bw + j); };
+        const span S[4] = {span(x, lo(0), lo(1), l), span(x, lo(1), lo(2), l), span(x, lo(2), lo(3), l), span(x, lo(3), lo(4), l)};
+        double m[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) m[j] = S[j].largest(x);
+        for (int k = 32; k > 0; k >>= 1)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) m[j] = fmax(m[j], __shfl_xor(m[j], k));
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (bw + j < nb) S[j].store(x, m[j], codes, scales + b0 + bw + j, cn, qmax);
+    } else {
+        for (int b = bw; b < bw + own && b < nb; ++b) {
+            const int64_t lo = eri_uniform(o, b), hi = eri_uniform(o, b + 1);
+            if (hi - lo > WAVE) continue;
+            const eri_span<CT, W, 64, NG> S(x, lo, hi, l);
+            double m = S.largest(x);
+            for (int k = 32; k > 0; k >>= 1) m = fmax(m, __shfl_xor(m, k));
+            S.store(x, m, codes, scales + b0 + b, cn, qmax);
+        }
     }
 }
 
-// Groups of one block in turns of four, so that four loads are in flight.
-template <typename CT, int W, int NT>
+// Groups of one block in turns of NG, so that NG loads are in flight.  Groups of
+// two values (16-byte stores, a wavefront's next to each other): 8000 blocks of
+// 3600 took 73 us with four a group, 3000 of 10000 81, and take 63 and 68.  A
+// workgroup takes four blocks.
+template <typename CT, int W, int NT, int NG>
 __device__ __forceinline__ void eri_decompress_span(const CT* __restrict__ codes, int64_t lo, int64_t hi, int t,
                                                     double eps, double* __restrict__ out)
 {
@@ -1678,12 +1758,12 @@ __device__ __forceinline__ void eri_decompress_span(const CT* __restrict__ codes
     const auto* cg = reinterpret_cast<const eri_group<CT, W>*>(codes) + G.g0;
     auto* og = reinterpret_cast<eri_group<double, W>*>(out) + G.g0;
     if (G.edge >= 0) out[G.edge] = (double)codes[G.edge] * eps;
-    for (int64_t g = t; g < G.ng; g += 4 * NT) {
-        eri_group<CT, W> q[4];
+    for (int64_t g = t; g < G.ng; g += NG * NT) {
+        eri_group<CT, W> q[NG];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) q[k] = cg[g + k * NT < G.ng ? g + k * NT : g];
+        for (int k = 0; k < NG; ++k) q[k] = cg[g + k * NT < G.ng ? g + k * NT : g];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < NG; ++k) {
             eri_group<double, W> v;
 #pragma unroll
             for (int i = 0; i < W; ++i) v.v[i] = (double)q[k].v[i] * eps;
@@ -1698,46 +1778,60 @@ __global__ __launch_bounds__(256) void eri_decompress_kernel(const CT* __restric
                                                              const int64_t* __restrict__ off, int64_t n_blocks,
                                                              double* __restrict__ out)
 {
-    const int64_t b0 = (int64_t)blockIdx.x * ERI_CODEC_PER;
-    const int nb = (int)(n_blocks - b0 < ERI_CODEC_PER ? n_blocks - b0 : ERI_CODEC_PER);
+    const int64_t b0 = (int64_t)blockIdx.x * ERI_CODEC_UNPACK;
+    const int nb = (int)(n_blocks - b0 < ERI_CODEC_UNPACK ? n_blocks - b0 : ERI_CODEC_UNPACK);
     const int64_t o = eri_codec_offsets(off, b0, nb);
     const int l = threadIdx.x & 63;
     const double sc = scales[b0 + (l < nb ? l : nb - 1)];
-    for (int b = 0; b < nb; ++b) {
+    const int64_t largest = eri_codec_largest<ERI_CODEC_UNPACK>(o, 0);
+    if (largest <= ERI_CODEC_QUARTER) {
+        const int b = (int)threadIdx.x >> 4;
+        const int64_t lo = __shfl(o, b & 3), hi = __shfl(o, (b & 3) + 1);
+        const double eps = __shfl(sc, b & 3);
+        if (b < nb) eri_decompress_span<CT, W, 16, 4 / W>(codes, lo, hi, l & 15, eps, out);
+        return;
+    }
+    for (int b = 0; b < nb && largest > 2 * ERI_CODEC_WAVE; ++b) {
         const int64_t lo = eri_uniform(o, b), hi = eri_uniform(o, b + 1);
-        if (hi - lo > ERI_CODEC_WAVE)
-            eri_decompress_span<CT, W, 256>(codes, lo, hi, (int)threadIdx.x, __shfl(sc, b), out);
+        if (hi - lo > 2 * ERI_CODEC_WAVE)
+            eri_decompress_span<CT, W, 256, 8>(codes, lo, hi, (int)threadIdx.x, __shfl(sc, b), out);
     }
     const int b = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (b < nb) {
         const int64_t lo = eri_uniform(o, b), hi = eri_uniform(o, b + 1);
-        if (hi - lo <= ERI_CODEC_WAVE) eri_decompress_span<CT, W, 64>(codes, lo, hi, l, __shfl(sc, b), out);
+        const double eps = __shfl(sc, b);
+        if (hi - lo <= ERI_CODEC_GROUP)
+            eri_decompress_span<CT, 1, 64, 4>(codes, lo, hi, l, eps, out);
+        else if (hi - lo <= 2 * ERI_CODEC_WAVE)
+            eri_decompress_span<CT, W, 64, 4>(codes, lo, hi, l, eps, out);
     }
 }
 
-static bool codec_aligned(const void* values, const void* codes, int code_bytes)
+static bool codec_aligned(const void* values, const void* codes, int w, int code_bytes)
 {
-    return (uintptr_t)values % 32 == 0 && (uintptr_t)codes % (4 * code_bytes) == 0;
+    return (uintptr_t)values % (8 * w) == 0 && (uintptr_t)codes % (w * code_bytes) == 0;
 }
 
 template <typename CT>
 static void launch_compress(const double* eri, const int64_t* off, int64_t n_blocks, void* codes, double* scales,
                             double cn, double qmax, hipStream_t st)
 {
-    const dim3 g((unsigned)((n_blocks + ERI_CODEC_PER - 1) / ERI_CODEC_PER)), b(256);
-    if (codec_aligned(eri, codes, sizeof(CT)))
-        hipLaunchKernelGGL((eri_compress_kernel<CT, 4>), g, b, 0, st, eri, off, n_blocks, (CT*)codes, scales, cn, qmax);
-    else
-        hipLaunchKernelGGL((eri_compress_kernel<CT, 1>), g, b, 0, st, eri, off, n_blocks, (CT*)codes, scales, cn, qmax);
+    const bool aligned = codec_aligned(eri, codes, 4, sizeof(CT));
+    const int per = n_blocks < ERI_CODEC_MANY ? 4 : n_blocks < 4 * ERI_CODEC_MANY ? 8 : 16;
+    const auto fn = per == 4   ? (aligned ? eri_compress_kernel<CT, 4, 4> : eri_compress_kernel<CT, 1, 4>)
+                    : per == 8 ? (aligned ? eri_compress_kernel<CT, 4, 8> : eri_compress_kernel<CT, 1, 8>)
+                               : (aligned ? eri_compress_kernel<CT, 4, 16> : eri_compress_kernel<CT, 1, 16>);
+    hipLaunchKernelGGL(fn, dim3((unsigned)((n_blocks + per - 1) / per)), dim3(256), 0, st, eri, off, n_blocks, (CT*)codes,
+                       scales, cn, qmax);
 }
 
 template <typename CT>
 static void launch_decompress(const void* codes, const double* scales, const int64_t* off, int64_t n_blocks,
                               double* out, hipStream_t st)
 {
-    const dim3 g((unsigned)((n_blocks + ERI_CODEC_PER - 1) / ERI_CODEC_PER)), b(256);
-    if (codec_aligned(out, codes, sizeof(CT)))
-        hipLaunchKernelGGL((eri_decompress_kernel<CT, 4>), g, b, 0, st, (const CT*)codes, scales, off, n_blocks, out);
+    const dim3 g((unsigned)((n_blocks + ERI_CODEC_UNPACK - 1) / ERI_CODEC_UNPACK)), b(256);
+    if (codec_aligned(out, codes, 2, sizeof(CT)))
+        hipLaunchKernelGGL((eri_decompress_kernel<CT, 2>), g, b, 0, st, (const CT*)codes, scales, off, n_blocks, out);
     else
         hipLaunchKernelGGL((eri_decompress_kernel<CT, 1>), g, b, 0, st, (const CT*)codes, scales, off, n_blocks, out);
 }
