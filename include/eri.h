@@ -126,8 +126,9 @@ typedef struct {
                                      class with an f-f bra is the two-wavefront x-column kernel;
                                      7-12 launch forms of the Rys workgroup kernels (_b, _w, _wo2,
                                      _n, _no2, _nwo2), 13 primitive-parallel (_p: by rule, small
-                                     launches), 14 Rys columns (_c: the default), 15 those of small
-                                     launches (_cs: by rule) */
+                                     launches), 14 Rys columns (_c: the default; the
+                                     table-driven kernel, 0, then comes last and by rule), 15
+                                     columns of small launches (_cs: by rule) */
     int32_t class_fp32[256];      /* 1: the class's recurrences run in FP32 (FP32-mixed plans, classes
                                      whose FP32 error was measured within 1e-8 Ha); 0: FP64 */
     int32_t scale_block;          /* G of eri_plan_opts (1 = per quartet) */

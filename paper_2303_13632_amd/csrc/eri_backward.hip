@@ -660,18 +660,22 @@ static int derive_items(eri_bwd_state* st, hipStream_t strm, const eri_item* uit
     return ERI_OK;
 }
 
-// Launch variant of a derived class: the first pass that meets the class
-// times each variant once on up to 65536 of its items (derived in that
-// variant's bra/ket order, after a warm-up launch) and keeps the fastest for
-// the rest of the plan's life, also where the tables are built again: L must
-// not change its bits with a timing.
+// Launch variant of a derived class, one for the exponent kinds, whose launches
+// have an item per primitive with the other shells' contractions, and one for
+// the rest (4096 [ss|dd] of K = 5, 4096 items of 625 primitive quartets / 20480 of 125,
+// us: lanes 553 / 540, slots 639 / 145).  The first pass that meets it times each
+// variant once on up to 65536 of its items (derived in that variant's bra/ket
+// order, after a warm-up launch) and keeps the fastest for the rest of the plan's
+// life, also where the tables are built again: L must not change its bits with a
+// timing.
 static int pick_variant(eri_plan* p, eri_bwd_state* st, int c5, const eri_class_args& full, hipStream_t strm,
                         const eri_item* uitems, const int32_t* origin, int pos, int kind, const int Lp[4],
                         const eri_kernel_info*& out)
 {
     const eri_kernel_info* var = eri_kernel_variants(0) + (int64_t)c5 * ERI_MAXVAR;
-    if (p->bwd_var[c5] >= 0) {
-        out = &var[p->bwd_var[c5]];
+    int8_t& chosen = p->bwd_var[2 * c5 + (origin ? 1 : 0)];
+    if (chosen >= 0) {
+        out = &var[chosen];
         return ERI_OK;
     }
     int nv = 0;
@@ -712,7 +716,7 @@ static int pick_variant(eri_plan* p, eri_bwd_state* st, int c5, const eri_class_
         (void)hipEventDestroy(e1);
         if (rc != ERI_OK) return rc;
     }
-    p->bwd_var[c5] = (int8_t)best;
+    chosen = (int8_t)best;
     out = &var[best];
     return ERI_OK;
 }

@@ -170,7 +170,7 @@ struct eri_plan {
     std::vector<double> sh_xyz, sh_exps, sh_coefs;
     std::vector<int64_t> sh_off;
     eri_bwd_state* bwd = nullptr;
-    std::vector<int8_t> bwd_var = std::vector<int8_t>(ERI_NCLASS5, -1);   // launch variant of each derived class
+    std::vector<int8_t> bwd_var = std::vector<int8_t>(2 * ERI_NCLASS5, -1);   // launch variants of the derived classes
     eri_coul_state* coul = nullptr;
     eri_adj_state* adj = nullptr;
     bool adj_listed[256] = {}, adj_energy[256] = {};   // short-list adjoint: the gradient, and L, of a class
