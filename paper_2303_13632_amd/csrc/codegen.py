@@ -1995,7 +1995,8 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1, pw=1):
         emit_adj_slot(em, ket_hrr_chunk, bra_hrr_chunk, NCH, "lane", "ls", "sbase", LW, "active", "slot", NSLOT,
                       NSLOT * NTE * CH, NSU - NSLOT * NTE * CH)
     em("double bmax = 0.0;")
-    held = hold_values(NCH, NCD, LW * pw, NAB, waves)
+    # (classes with a g shell are launched in their adjoint form only)
+    held = hold_values(NCH, NCD, LW * pw, NAB, waves) and max(cp.user) <= 3
     hl = "(ls + %d * wv)" % LW if pw > 1 else "ls"   # first ket index of a lane
     assert held or pw == 1, name
     if held:
@@ -2380,7 +2381,7 @@ def emit_mode_W2(cp, prec, name, lds_budget=None, waves=1, layout="parity"):
         emit_adj_slot(em, ket_hrr_chunk, bra_hrr_chunk, NCH, "tid", "tid", "0", 128, "active", "0", 1,
                       NTE * CH, NSU - NTE * CH)
     em("double bmax = 0.0;")
-    held = hold_values(NCH, NCD, 128, len(ab_list), waves)
+    held = hold_values(NCH, NCD, 128, len(ab_list), waves) and max(cp.user) <= 3
     if held:
         ket_hrr_chunk(0)
         emit_held_hrr(em, cp, NCD, 128, "tid", lambda e: "(%s)s_t[%d][j]" % (real, tgt_index[e]), ab_list,
