@@ -1742,8 +1742,15 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1, pw=1):
     em("const int nbra = active ? BP.nprim : 0;")
     em("const int nket = KP.nprim;")
     em("const int sbase = slot * %d;" % EP)
-    # lanes of an unused tail slot read the first slot's staging (never stored)
-    em("const int pbase = slot < %d ? sbase : 0;" % NSLOT)
+    if NSLOT == 1 and pw == 1 and max(cp.user) <= 3:
+        # a zero that the compiler keeps in a vector register: with a scalar address
+        # every staged primitive quartet's loads wait for a move of it (403
+        # [fd|ps] of K = 5 281 us, 270 so)
+        em("int pbase;")
+        em("asm volatile(\"v_mov_b32 %0, 0\" : \"=v\"(pbase));")
+    else:
+        # lanes of an unused tail slot read the first slot's staging (never stored)
+        em("const int pbase = slot < %d ? sbase : 0;" % NSLOT)
     for s_ in range(S):
         em("const int ex%d = %s[ls][%d], ey%d = %s[ls][%d], ez%d = %s[ls][%d];"
            % (s_, tbl, 8 * s_, s_, tbl, 8 * s_ + 1, s_, tbl, 8 * s_ + 2))
