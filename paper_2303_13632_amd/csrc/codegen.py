@@ -1708,6 +1708,11 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1, pw=1):
     elif waves > 1:
         # at least `waves` wavefronts per SIMD: the register budget halves
         em("__global__ __launch_bounds__(64, %d) void %s(eri_class_args A)" % (waves, name))
+    elif max(cp.user) <= 3 and NCD <= 3 and hold_values(NCH, NCD, LW, NAB, 2):
+        # the held values (60 of an f-d bra) are the kernel's peak there, and more
+        # than two wavefronts a SIMD hold: 3000 [fd|ss] of K = 4 256 us, 217 so; with
+        # larger kets the bound costs the recurrences (3000 [fp|dd] of K = 4 842, 940)
+        em("__global__ __launch_bounds__(64, 2) void %s(eri_class_args A)" % name)
     else:
         em("__global__ __launch_bounds__(64) void %s(eri_class_args A)" % name)
     em.block("")
