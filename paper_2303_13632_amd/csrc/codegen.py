@@ -102,7 +102,7 @@ def kernel_name(prec, user, alt=False):
 
 # classes with one g shell and s, p, d on the others: the exponent derivatives
 # of d shells (L + 2) in the adjoint
-MAXVAR = 8   # launch variants per class (ERI_MAXVAR)
+MAXVAR = 9   # launch variants per class (ERI_MAXVAR)
 
 G_CLASSES = [c for c in itertools.product(range(5), repeat=4) if sorted(c)[-1] == 4 and sorted(c)[-2] <= 2]
 
@@ -2733,12 +2733,11 @@ def generate(outdir, precisions=("fp64",), classes=None, group=8, overrides=None
                     else:
                         lines_.append("    p[%d] = %s;" % (c5, info))
                 k = 0
-                for suffix, budget, occ, nts, unroll, tag in RYSW_VARIANTS:
+                if large is not None:
+                    k = 1   # variant 0 is the column kernel; the first of these comes last
+                for suffix, budget, occ, nts, unroll, tag in RYSW_VARIANTS[k:] + RYSW_VARIANTS[:k]:
                     if budget != RYSW_LDS and rysw_shape(cp, budget, vb) == rysw_shape(cp, RYSW_LDS, vb):
                         continue   # the larger budget changes nothing for this class
-                    if k == 0 and large is not None:
-                        k = 1
-                        continue   # variant 0 is the column kernel
                     name = kernel_name(rprec, cp.user) + suffix
                     _, src, fpq = emit_mode_RW(cp, name, budget, occ, real, nts, unroll)
                     parts.append(src)

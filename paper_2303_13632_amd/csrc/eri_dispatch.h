@@ -18,7 +18,8 @@ struct eri_kernel_info {
                          // workgroup Rys kernels: 7 larger batches of primitive quartets, 8 twice the threads
                          // at 4 waves per SIMD, 9 twice the threads at 2; 10, 11, 12 the node loop not
                          // unrolled (1 and 2 waves per SIMD, twice the threads at 2); 13 primitive-parallel;
-                         // 14 Rys columns (default), 15 those of small launches
+                         // 14 Rys columns (default; 0, table-driven, is then the last variant), 15 those
+                         // of small launches
     int32_t fp32;        // 1: VRR/HRR in FP32 (FP32-mixed kernel); 0: FP64
     int32_t pack_dyn;    // packed stream stages codes in dynamic LDS: 0 never, 1 always, 2 for n > 16
 };
@@ -35,7 +36,7 @@ const eri_kernel_info* eri_kernel_table(int precision);
 // k = 0 the default launch of the table above; unused entries have fn == nullptr.
 // Variants share the output layout; a variant may compute the class with bra
 // and ket exchanged (perm), which the plan's items must follow.
-#define ERI_MAXVAR 8
+#define ERI_MAXVAR 9
 const eri_kernel_info* eri_kernel_variants(int precision);
 
 // Kernels that a rule on the launch takes in place of variant 0, with its

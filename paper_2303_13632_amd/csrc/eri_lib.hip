@@ -991,22 +991,45 @@ static bool waves_better(const eri_kernel_info& prim, int64_t n, int64_t deep, i
     return n <= ERI_PRIM_GROUPS * prim.per_block && deep <= ERI_PRIM_DEEP_GROUPS * prim.per_block && maxpq >= 8;
 }
 
-// Rys classes: deepest contractions up to which the column kernel of small
-// launches runs.  Both forms at 256 / 2048 quartets of K 1..3, a fifth as many
-// deepest ones (us, small / large): [ff|ff] 318 / 498, 671 / 549, [fd|fd] 131 / 196,
-// 266 / 276 where each pair has 60 components and more; [ff|ps] 30 / 53, 52 / 60, [dd|pp]
-// 27 / 43, 35 / 52, [dd|ps] 16 / 25, 20 / 28 elsewhere, and of K = 3 at 512 and 1024
-// [ff|ps] 50 / 55, 121 / 88, [dd|ps] 21 / 28, 29 / 32.  The classes up to L_tot = 4 else
-// take a lane per quartet, which walks its contraction in series: 4096 / 8192 /
-// 16384 quartets of K = 3 [pp|pp] 101 / 273, 173 / 270, 327 / 281, [ds|ss] 37 / 78,
-// 66 / 78, 119 / 89; with one primitive quartet there is nothing to share (256
-// [ds|ps] 10 / 8).
-constexpr int ERI_TAG_COLUMNS_SMALL = 15;
-static int64_t column_quartets(int c, int64_t maxpq)
+// Rys classes: the kernel of a launch of `deep` deepest contractions of maxpq
+// primitive quartets, the tag of the column kernel of small launches, of the
+// column kernel (variant 0 of most classes) or 0 for the table-driven one.  The
+// first shares a quartet's sums among the most threads, the second does the
+// transfers once per node, and the third has the least to do before the sums.
+// Measured, table / columns / columns of small launches (us):
+//   from L_tot 5 on the small form is ahead up to 512 deep, or 256 where each pair
+//   has 60 components and more or a quartet 540 ERIs and more: 256 and 2048 of
+//   K 1..3 [ff|ff] 873 / 498 / 318 and 1626 / 549 / 671, [fd|fd] 321 / 196 / 131 and 491 /
+//   276 / 266; up to 768 in FP64 and 1024 in FP32 for classes of 109 (FP64) to 216
+//   ERIs and [dd|pp] with contractions (3000 of K 1..3 [dd|pp] 45 / 53 / 38, FP32 35 / 46 / 30);
+//   past that, the table is ahead where contractions are single and a quartet has up
+//   to 180 ERIs, or a pair of 30 components is on both sides ([fs|fs] of K = 1, 40000
+//   quartets 43 / 76, [fp|fp] 278 / 376), and for launches of a middle depth of kets
+//   of few components or bras of ten (FP64, 3000 of K 1..3: [fs|dd] 45 / 51 / 50,
+//   [fd|ds] 45 / 50 / 52; FP32, to 1024: 34 / 45 / 38, 35 / 45 / 39, [ff|ds] 59 / 71 / 91);
+//   everywhere else columns are.
+// Classes up to L_tot = 4 take a lane per quartet in place of the latter two, which
+// walks its contraction in series: 4096 / 8192 / 16384 quartets of K = 3, small
+// columns and lane, [pp|pp] 101 / 273, 173 / 270, 327 / 281, [ds|ss] 37 / 78, 66 / 78,
+// 119 / 89; with one primitive quartet there is nothing to share (256 [ds|ps] 10 / 8).
+constexpr int ERI_TAG_COLUMNS = 14, ERI_TAG_COLUMNS_SMALL = 15;
+static int rys_tag(int c, int64_t deep, int64_t maxpq, bool has_small, bool single, bool fp32)
 {
     const int a = c >> 6, b = (c >> 4) & 3, k = (c >> 2) & 3, l = c & 3;
-    if (a + b + k + l <= 4) return maxpq >= 4 ? 8192 : 0;
-    return std::min(ncart(a) * ncart(b), ncart(k) * ncart(l)) >= 60 ? 256 : 512;
+    if (a + b + k + l <= 4) return has_small && maxpq >= 4 && deep <= 8192 ? ERI_TAG_COLUMNS_SMALL : ERI_TAG_COLUMNS;
+    const int bra = ncart(a) * ncart(b), ket = ncart(k) * ncart(l), n = bra * ket;
+    const int hi = std::max(bra, ket), lo = std::min(bra, ket);
+    const bool large = lo >= 60;
+    const bool thin = n >= 300 && n <= 600 && (lo <= 6 || (lo == 10 && hi == 36));
+    int64_t small = 512, table = 0;
+    if (large) small = fp32 ? 1024 : single ? 512 : 256;
+    else if (single) small = n >= 540 || (fp32 && n > 180) ? 256 : 512;
+    else if (n <= 216 || (hi == 36 && lo == 9)) small = fp32 ? 1024 : n > 108 ? 768 : 512;
+    else if (n >= 540 || (thin && (fp32 || lo > 3))) small = 256;
+    if (single) table = n <= 180 || (hi == 30 && lo == 30) ? INT64_MAX : n <= 360 ? 512 : fp32 ? 256 : 0;
+    else if (thin || (hi == 36 && lo == 6)) table = fp32 ? 1024 : n < 600 ? 768 : 0;
+    if (fp32 && hi == 60 && lo == 3) table = single ? INT64_MAX : 8192;
+    return has_small && deep <= small ? ERI_TAG_COLUMNS_SMALL : deep <= table ? 0 : ERI_TAG_COLUMNS;
 }
 
 // Slot kernels that have a lane-per-quartet form (up to 144 ERIs): whether it runs
@@ -1052,9 +1075,17 @@ static const eri_kernel_info& default_kernel(const eri_plan* p, int c, int64_t n
             if (v[k].fn && v[k].tag == ERI_TAG_ALT && v[k].mode == 0) return v[k];
     }
     const eri_kernel_info& prim = eri_kernel_prim(table_index(p->precision))[class_id5_of(c)];
-    const bool better = prim.tag == ERI_TAG_COLUMNS_SMALL ? deep_quartets(p, c, n) <= column_quartets(c, p->class_maxpq[c])
-                        : prim_lanes(prim)                ? prim_better(c, deep_quartets(p, c, n), p->class_maxpq[c], p->batched)
-                                                          : waves_better(prim, n, deep_quartets(p, c, n), p->class_maxpq[c]);
+    if (def.tag == ERI_TAG_COLUMNS || prim.tag == ERI_TAG_COLUMNS_SMALL) {
+        const bool single = p->class_pq[c] < 2 * p->class_count[c];
+        const int tag = rys_tag(c, deep_quartets(p, c, n), p->class_maxpq[c], prim.fn != nullptr, single, p->precision == ERI_RYS_FP32);
+        if (tag == ERI_TAG_COLUMNS_SMALL) return prim;
+        const eri_kernel_info* v = eri_kernel_variants(table_index(p->precision)) + (int64_t)class_id5_of(c) * ERI_MAXVAR;
+        for (int k = 1; k < ERI_MAXVAR && !tag; ++k)
+            if (v[k].fn && v[k].tag == 0) return v[k];
+        return def;
+    }
+    const bool better = prim_lanes(prim) ? prim_better(c, deep_quartets(p, c, n), p->class_maxpq[c], p->batched)
+                                         : waves_better(prim, n, deep_quartets(p, c, n), p->class_maxpq[c]);
     return prim.fn && better ? prim : def;
 }
 
