@@ -775,7 +775,7 @@ extern "C" int eri_plan_create(eri_plan** out, int64_t n_shells, const int32_t* 
     return ERI_OK;
 }
 
-static const eri_kernel_info& class_kernel(const eri_plan* p, int c);
+static const eri_kernel_info& class_kernel(const eri_plan* p, int c, bool values = false);
 
 extern "C" int eri_plan_info_get(const eri_plan* p, eri_plan_info* info)
 {
@@ -1056,14 +1056,20 @@ static bool lane_better(int c, int64_t deep, int64_t maxpq)
 // half-register forms of the largest kernels, which hold twice as many, are
 // ahead where they spill little: two wavefronts of an f-f bra with a ket of L
 // 2..4 (averages at 1024 / 8192 quartets: [ff|dd]-like 146 / 634 us at full registers,
-// 166 / 481 at half), and [fd|fd] (237 / 483 and 243 / 373).
-constexpr int64_t ERI_HALF_MIN = 2048;
-static const eri_kernel_info& default_kernel(const eri_plan* p, int c, int64_t n)
+// 166 / 481 at half), and [fd|fd] (237 / 483 and 243 / 373).  With single contractions the
+// HRR and the stores are the time, and half the registers gain only in launches
+// that store codes alone, of an f-f bra and many quartets (full / half, K = 1, 2048
+// and 16384: [fd|fd] codes 29 / 52 and 161 / 199, with values 35 / 66 and 220 / 334;
+// [ff|dd] codes 57 / 57 and 352 / 292, with values 69 / 88 and 437 / 611).
+constexpr int64_t ERI_HALF_MIN = 2048, ERI_HALF_SINGLE_MIN = 8192;
+static const eri_kernel_info& default_kernel(const eri_plan* p, int c, int64_t n, bool values = false)
 {
-    if (n >= ERI_HALF_MIN) {
+    const bool single = p->class_pq[c] < 2 * p->class_count[c];
+    const bool codes_only = p->bits > 0 && !values;
+    if (n >= (single ? ERI_HALF_SINGLE_MIN : ERI_HALF_MIN) && (!single || codes_only)) {
         const int lb = (c >> 6) + ((c >> 4) & 3), lk = ((c >> 2) & 3) + (c & 3);
         const int hi = std::max(lb, lk), lo = std::min(lb, lk);
-        const int tag = hi == 6 && lo >= 2 && lo <= 4 ? 6 : hi == 5 && lo == 5 ? 2 : 0;
+        const int tag = hi == 6 && lo >= 2 && lo <= 4 ? 6 : hi == 5 && lo == 5 && !single ? 2 : 0;
         const eri_kernel_info* v = eri_kernel_variants(table_index(p->precision)) + (int64_t)class_id5_of(c) * ERI_MAXVAR;
         for (int k = 1; k < ERI_MAXVAR && tag && p->precision <= ERI_FP32_MIXED; ++k)
             if (v[k].fn && v[k].tag == tag) return v[k];
@@ -1076,7 +1082,6 @@ static const eri_kernel_info& default_kernel(const eri_plan* p, int c, int64_t n
     }
     const eri_kernel_info& prim = eri_kernel_prim(table_index(p->precision))[class_id5_of(c)];
     if (def.tag == ERI_TAG_COLUMNS || prim.tag == ERI_TAG_COLUMNS_SMALL) {
-        const bool single = p->class_pq[c] < 2 * p->class_count[c];
         const int tag = rys_tag(c, deep_quartets(p, c, n), p->class_maxpq[c], prim.fn != nullptr, single, p->precision == ERI_RYS_FP32);
         if (tag == ERI_TAG_COLUMNS_SMALL) return prim;
         const eri_kernel_info* v = eri_kernel_variants(table_index(p->precision)) + (int64_t)class_id5_of(c) * ERI_MAXVAR;
@@ -1095,15 +1100,16 @@ static int64_t launch_quartets(const eri_plan* p, int c)
     return p->batched ? class_piece(p, c) : p->class_count[c];
 }
 
-// Kernel of a class launch: the autotuner's variant, else the default.
-static const eri_kernel_info& class_kernel(const eri_plan* p, int c)
+// Kernel of a class launch: the autotuner's variant, else the default (values:
+// the launch stores FP64 values).
+static const eri_kernel_info& class_kernel(const eri_plan* p, int c, bool values)
 {
     const int c5 = class_id5_of(c);
     if (p->class_var[c] > 0) {
         const eri_kernel_info& v = eri_kernel_variants(table_index(p->precision))[c5 * ERI_MAXVAR + p->class_var[c]];
         if (v.fn) return v;
     }
-    return default_kernel(p, c, launch_quartets(p, c));
+    return default_kernel(p, c, launch_quartets(p, c), values);
 }
 
 // Compression of one class's FP64 values in blocks of S consecutive values
@@ -1136,7 +1142,7 @@ static int launch_class(eri_plan* p, int c, hipStream_t st, double* out_eri, voi
 {
     const int64_t n = p->class_count[c];
     if (n == 0) return ERI_OK;
-    const eri_kernel_info& ki = class_kernel(p, c);
+    const eri_kernel_info& ki = class_kernel(p, c, out_eri != nullptr);
     eri_class_args a;
     fill_args(p, c, a, out_eri, out_codes, out_scales);
     if (!p->batched) {
