@@ -1752,7 +1752,7 @@ def emit_mode_W(cp, prec, name, lds_budget=None, waves=1, pw=1):
         # every staged primitive quartet's loads wait for a move of it (403
         # [fd|ps] of K = 5 281 us, 270 so)
         em("int pbase;")
-        em("asm volatile(\"v_mov_b32 %0, 0\" : \"=v\"(pbase));")
+        em("asm(\"v_mov_b32 %0, 0\" : \"=v\"(pbase));")
     else:
         # lanes of an unused tail slot read the first slot's staging (never stored)
         em("const int pbase = slot < %d ? sbase : 0;" % NSLOT)
