@@ -117,7 +117,8 @@ typedef struct {
     int32_t class_block[256];     /* its threads per workgroup */
     int32_t class_per_block[256]; /* its quartets per workgroup */
     int32_t class_n_variants[256];/* launch variants available: 0 .. n-1 */
-    int32_t class_tag[256];       /* kernel of the variant in use: 0 default, 1 alternate mapping
+    int32_t class_tag[256];       /* kernel of the variant in use (variant 0: of calls that store codes
+                                     alone, if the plan has codes): 0 default, 1 alternate mapping
                                      (name suffix _a), 2 half-register slots (suffix _o2),
                                      3 two-wavefront slots (suffix _w2), 4 bra and ket exchanged
                                      (suffix _s), 5 two-wavefront slots at half the registers

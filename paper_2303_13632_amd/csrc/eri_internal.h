@@ -98,7 +98,6 @@ int upload(eri_plan* p, void** dst, const void* src, size_t bytes);
 // is the concatenation of its entries.
 struct eri_batch_class {
     int cid = -1;
-    bool swap = false;              // kernel's computed bra is P2
     int64_t n_quartets = 0;
     int64_t seg_lo = 0, seg_hi = 0; // range in the plan's segment arrays
     int64_t ket_lo = 0;             // first ket pair (global index) of the ket group

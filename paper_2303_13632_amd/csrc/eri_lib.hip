@@ -602,7 +602,6 @@ static int create_batched(eri_plan* p, const shell_set& s, const eri_plan_opts* 
                     if (!tab[class_id5_of(cid)].fn) return ERI_EUNSUPPORTED;
                     eri_batch_class bc;
                     bc.cid = cid;
-                    bc.swap = (tab[class_id5_of(cid)].perm & 3) >= 2;
                     bc.ket_lo = k0;
                     bc.qoff = p->class_count[cid];
                     bc.seg_lo = (int64_t)p->h_seg_p1.size();
