@@ -1034,8 +1034,9 @@ static int rys_tag(int c, int64_t deep, int64_t maxpq, bool has_small, bool sing
 // Slot kernels that have a lane-per-quartet form (up to 144 ERIs): whether it runs
 // for `deep` deepest contractions of maxpq primitive quartets.  A slot's lanes
 // own ket components in the bra transfer, so kets of one or three leave most idle;
-// a lane per quartet needs the chip full of quartets, and more of them the longer
-// its contraction.  Slot / lane at 16384 and 65536 quartets of K = 1 and 16384 and
+// a lane per quartet needs the chip full of quartets.  The lines go by the smaller
+// pair's components and lie where no class of theirs loses, so some turn earlier
+// than their line: [ff|ss] and [fd|ss] with contractions, [fs|ds].  Slot / lane at 16384 and 65536 quartets of K = 1 and 16384 and
 // 40000 of K = 3 (us): [ff|ss] 353 / 38, 1360 / 88, 1388 / 213, 3308 / 249, [fd|ss]
 // 105 / 22, 390 / 38, 538 / 129, 1293 / 158, [dd|ps] 57 / 38, 189 / 69, 402 / 236,
 // 969 / 269, [fs|ds] 19 / 22, 50 / 37, 219 / 191, 484 / 232, [pp|pp] 15 / 31, 31 / 60,
