@@ -28,7 +28,8 @@ struct eri_coul_job {
 struct eri_coul_args {
     const eri_coul_job* jobs;
     int64_t n_jobs;
-    const double* rec;               // per primitive pair: p, P, (-1)^|t| H_t
+    const double* full;              // per primitive pair: p, P, (-1)^|t| H_t
+    const double* rec;               // the same, -p and zeros where an H_t is not finite
     const eri_coul_range* ranges;
     const int32_t* prim_pair;        // shell pair of each primitive pair
     double* pot;

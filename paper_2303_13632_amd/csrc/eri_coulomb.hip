@@ -81,7 +81,8 @@ struct coul_pair_args {
     const double* dens;
     int64_t nbf;
     int64_t prim0, n;        // primitive pairs of the class
-    double* rec;             // the class's records
+    double* full;            // the class's records
+    double* rec;             // and those without charges that are not finite
     const double* pot;       // the class's potentials
     int64_t pot_stride;
     double* part;
@@ -163,16 +164,19 @@ __global__ __launch_bounds__(64) void coul_charge_kernel(coul_pair_args A)
                                 H[herm_index(t, u, v)] = fma(xy, E[2][az][bz][v], H[herm_index(t, u, v)]);
                         }
                 }
+    bool finite = true;
+    for (int t = 0; t < nherm(N); ++t) finite = finite && isfinite(H[t]);
     double* __restrict__ r = A.rec + i * (4 + nherm(N));
-    r[0] = B.p;
-    r[1] = B.P[0];
-    r[2] = B.P[1];
-    r[3] = B.P[2];
+    double* __restrict__ f = A.full + i * (4 + nherm(N));
+    f[0] = B.p;
+    r[0] = finite ? B.p : -B.p;
+    for (int x = 0; x < 3; ++x) r[1 + x] = f[1 + x] = B.P[x];
     for (int t = 0; t <= N; ++t)
         for (int u = 0; u <= N - t; ++u)
             for (int v = 0; v <= N - t - u; ++v) {
                 const int k = herm_index(t, u, v);
-                r[4 + k] = (t + u + v) & 1 ? -H[k] : H[k];
+                f[4 + k] = (t + u + v) & 1 ? -H[k] : H[k];
+                r[4 + k] = finite ? f[4 + k] : 0.0;
             }
 }
 // One thread per primitive pair and pair of Cartesian components (blockIdx.y):
@@ -421,7 +425,7 @@ int build(eri_plan* p, eri_coul_state* st)
     ERI_TRY(upload(p, (void**)&st->d_prim_pair, prim_pair.empty() ? nullptr : prim_pair.data(), prim_pair.size() * sizeof(int32_t)));
     ERI_TRY(upload(p, (void**)&st->d_bf, bf.data(), bf.size() * sizeof(int64_t)));
     ERI_TRY(upload(p, (void**)&st->d_poff, p->sh_off.empty() ? nullptr : p->sh_off.data(), p->sh_off.size() * sizeof(int64_t)));
-    ERI_TRY(upload(p, (void**)&st->d_rec, nullptr, (size_t)st->n_rec * sizeof(double)));
+    ERI_TRY(upload(p, (void**)&st->d_rec, nullptr, 2 * (size_t)st->n_rec * sizeof(double)));
     ERI_TRY(upload(p, (void**)&st->d_pot, nullptr, (size_t)st->n_pot * sizeof(double)));
     ERI_TRY(upload(p, (void**)&st->d_energy, nullptr, 2 * jobs.size() * sizeof(double)));
     ERI_TRY(upload(p, (void**)&st->d_part, nullptr, (size_t)st->n_slices * st->n_grad * sizeof(double)));
@@ -501,7 +505,8 @@ int eri_coul_backward(eri_plan* p, hipStream_t strm, const double* density, int6
         for (int c = 0; c < NCLS; ++c) {
             a.prim0 = st->prim0[c];
             a.n = st->prim0[c + 1] - st->prim0[c];
-            a.rec = st->d_rec + st->rec0[c];
+            a.full = st->d_rec + st->rec0[c];
+            a.rec = a.full + st->n_rec;
             a.pot = st->d_pot + st->pot0[c];
             a.pot_stride = a.n;
             ERI_TRY(launch(fn[c], (a.n + 63) / 64, components ? ncart(CLS_LA[c]) * ncart(CLS_LB[c]) : 1, 64, &a, strm));
@@ -514,7 +519,8 @@ int eri_coul_backward(eri_plan* p, hipStream_t strm, const double* density, int6
         eri_coul_args c;
         c.jobs = st->d_jobs + st->job0[k];
         c.n_jobs = st->job0[k + 1] - st->job0[k];
-        c.rec = st->d_rec;
+        c.full = st->d_rec;
+        c.rec = st->d_rec + st->n_rec;
         c.ranges = st->d_ranges;
         c.prim_pair = st->d_prim_pair;
         c.pot = st->d_pot;
