@@ -304,7 +304,7 @@ int eri_decompress(int32_t bits, const void* codes, const double* scales, int64_
  * order), so the summation order (and the last bits of the gradients) may vary
  * between calls; L is summed in a fixed order with compensated (two-sum)
  * arithmetic, so *energy is the same on every call with the same inputs.
- * Device memory held for it: with Hermite potentials, up to 123 doubles and
+ * Device memory held for it: with Hermite potentials, up to 162 doubles and
  * 4 bytes per primitive pair, 72 bytes per job (at most 64 target against 8 to
  * 8192 source primitive pairs), 8 bytes per pair list entry and slices of at
  * most 32 MB; for classes in one launch 8 bytes per quartet of the plan, 36
